@@ -9,6 +9,8 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
+#include "mg_attn.h"
+
 namespace mg {
 
 // Q, O, dO, dQ are [B][H][Lq][d]; K, V, dK, dV are [B][H][Lk][d]; LSE and D
@@ -42,6 +44,15 @@ hipError_t launch_fwd_bf16(const AttnProblem &p, const uint16_t *Q, const uint16
 // P rounded to f16 as matrix-core inputs, f32 accumulation.
 hipError_t launch_fwd_accel(const AttnProblem &p, const float *Q, const float *K,
                             const float *V, float *O, float *LSE, hipStream_t s);
+
+// Forward for few query rows (use_few_rows), every contract; round_f16 is the
+// accelerated one.
+bool use_few_rows(const AttnProblem &p, mg_contract_t contract);
+hipError_t launch_fwd_few_f32(const AttnProblem &p, const float *Q, const float *K,
+                              const float *V, float *O, float *LSE, bool round_f16,
+                              hipStream_t s);
+hipError_t launch_fwd_few_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
+                               const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s);
 
 // Backward step 1: D_i = sum_k dO_ik O_ik (f32 out, one per row).
 hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const float *dO,

@@ -214,7 +214,16 @@ mg_status_t mg_attn_fwd_cross(const void *Q, const void *K, const void *V, void 
     MG_TRY(check_tensors({{Q, "Q"}, {K, "K"}, {V, "V"}, {O, "O"}, {LSE, "LSE"}}));
     MG_TRY(check_key_len(key_len));
     const mg::AttnProblem p{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
-    if (contract == MG_CONTRACT_STRICT_F32) {
+    if (mg::use_few_rows(p, contract)) {
+        MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
+            if (contract == MG_CONTRACT_FAST_BF16)
+                return mg::launch_fwd_few_bf16(p, (const uint16_t *)Q, (const uint16_t *)K,
+                                               (const uint16_t *)V, (uint16_t *)O, LSE, stream);
+            return mg::launch_fwd_few_f32(p, (const float *)Q, (const float *)K,
+                                          (const float *)V, (float *)O, LSE,
+                                          contract == MG_CONTRACT_ACCELERATED, stream);
+        }));
+    } else if (contract == MG_CONTRACT_STRICT_F32) {
         MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
             return mg::launch_fwd_f32(p, (const float *)Q, (const float *)K, (const float *)V,
                                       (float *)O, LSE, stream);
