@@ -15,8 +15,13 @@
  *
  * Arithmetic contracts (Sec. 4.2 "Arithmetic contracts", Table of arithmetic
  * permissions):
- *   MG_CONTRACT_STRICT_F32  every tensor f32; products on f32 matrix cores
- *                           with f32 accumulation (the paper's --strict mode).
+ *   MG_CONTRACT_STRICT_F32  every tensor f32; f32 products and f32
+ *                           accumulation (the paper's --strict mode).  Small
+ *                           problems multiply on f32 matrix cores; large ones
+ *                           and d = 128 take each f32 operand as the sum of
+ *                           three bf16 parts (24 significant bits) and six
+ *                           bf16 matrix products per f32 product, with no
+ *                           larger error against 64 bits.
  *   MG_CONTRACT_FAST_BF16   Q,K,V,O,dO,dQ,dK,dV are bf16; products run on
  *                           bf16 matrix cores with f32 accumulation, P and dS
  *                           are rounded to bf16 (nearest even) as operands;
@@ -123,9 +128,9 @@ size_t mg_attn_bwd_workspace_bytes(int B, int H, int L, int d, int causal,
  * Backward pass: dQ, dK, dV from Q, K, V, the forward outputs O and LSE, and
  * the upstream gradient dO (the paper's attention derivative node, Sec. 3.1,
  * lowered to a fused dK+dV kernel and a separate dQ kernel, Sec. 3.3 and
- * Sec. 8; for strict_f32 with d <= 64 the dK+dV kernel also emits per-tile
- * dQ partials that a reduction kernel sums, or, with a single key tile and
- * no query split, writes dQ itself).  P is recomputed from Q, K and
+ * Sec. 8; for small strict_f32 grids with d <= 64 the dK+dV kernel also emits
+ * per-tile dQ partials that a reduction kernel sums, or, with a single key
+ * tile and no query split, writes dQ itself).  P is recomputed from Q, K and
  * the saved LSE; nothing of size L x L is stored.  `workspace` is
  * caller-owned device memory of at least mg_attn_bwd_workspace_bytes(...)
  * bytes; its contents on entry are ignored

@@ -4,23 +4,22 @@
 // kernel and a fused dK+dV kernel (Sec. 3.3; Sec. 8 makes the fused dK+dV
 // kernel a compiler invariant; Sec. 7.3 profiles the backward pair).  Here:
 //
-//   attn_fwd_f32      query tile stationary, streams K/V tiles, online
-//                     softmax in base 2, writes O and LSE (natural log).
-//   attn_fwd_f32_ks2  the same for grids too small to spread evenly over
-//                     the CUs: 32-row query tiles, whose key tiles are split
-//                     between two halves of the workgroup; the halves merge
-//                     their (max, sum, O) states through LDS at the end.
+//   attn_fwd_f32_ks2  query tile of 32 rows stationary, streams K/V tiles,
+//                     online softmax in base 2, writes O and LSE (natural
+//                     log).  The key tiles are split between two halves of the
+//                     workgroup (four groups: _ks4), which merge their (max,
+//                     sum, O) states through LDS at the end: for grids too
+//                     small to spread evenly over the CUs.  Larger grids,
+//                     d = 128 and the separate dK/dV and dQ kernels run on
+//                     split bf16 operands (attn_f32x3_*.hip).
 //   attn_rowdot_f32   D_i = sum_k dO_ik O_ik (HBM-bound row reduction).
-//   attn_dkdv_f32     key tile stationary: recomputes P from LSE, then
-//                     dV += P^T dO, dP = dO V^T, dS = P(dP - D), dK += dS^T Q.
-//   attn_dkdvq_f32    attn_dkdv_f32 plus the dQ product of its key tile:
-//                     dQ_part = dS K_tile goes to the workspace, one partial
-//                     per (key tile, query row) (d <= 64).
+//   attn_dkdvq_f32    key tile stationary: recomputes P from LSE, then
+//                     dV += P^T dO, dP = dO V^T, dS = P(dP - D), dK += dS^T Q,
+//                     and the dQ product of its key tile, dQ_part = dS K_tile,
+//                     to the workspace, one partial per (key tile, query
+//                     row) (d <= 64).
 //   attn_dq_reduce_f32  dQ = scale * sum of a row's partials, in key-tile
 //                     order (fixed order: bitwise-reproducible, no atomics).
-//   attn_dq_f32       query tile stationary: recomputes P and dS, then
-//                     dQ += dS K (used when the partials do not fit: d = 128
-//                     or a workspace above 1 GiB).
 //
 // Every product runs on v_mfma_f32_16x16x4_f32 (f32 inputs, f32 accumulate),
 // which is what the strict contract permits (Sec. 4.2).  Each wave owns 16
@@ -28,9 +27,7 @@
 // is staged through LDS, 64 rows at a time, and shared by the waves of a
 // workgroup.  The forward kernel copies its K and V tiles with gfx950's
 // direct-to-LDS buffer loads (no staging registers) and fetches the next K
-// tile during P V and the next V tile during S = K Q^T.  The backward
-// kernels stage Q and dO through registers: the loads for the next tile are
-// issued before the current one is consumed and written to LDS after it.
+// tile during P V and the next V tile during S = K Q^T.
 //
 // Workgroup order: the 1-D grid is numbered rank-major over heads
 // (id = slot * B*H + head) with rank 0 the tile that has the most work under
@@ -52,7 +49,7 @@
 #include "device_common.h"
 #include "launch.h"
 #include "tiles_direct.h"
-#include "tiles_f32.h"
+#include "work_order.h"
 
 // Per-kernel launch configuration: waves per workgroup, minimum waves per
 // SIMD requested from the register allocator (0 = compiler default), and
@@ -61,17 +58,11 @@
 // the fastest of sweeps on MI355X at B8 H8 L1024 d64 and B16 H12 L512 d64
 // (double buffering lost there: it halves the workgroups an LDS-heavy CU can
 // hold); they can be overridden at build time.
-#ifndef MG_FWD_CFG
-#define MG_FWD_CFG 4, 3, false
-#endif
 #ifndef MG_DKDV_CFG
 #define MG_DKDV_CFG 4, 3, false
 #endif
 #ifndef MG_DKDVQ_CAUSAL_CFG
 #define MG_DKDVQ_CAUSAL_CFG 8, 4, false   // 128-key tiles: half the dQ partials
-#endif
-#ifndef MG_DQ_CFG
-#define MG_DQ_CFG 8, 0, false
 #endif
 #ifndef MG_DKDVQ_CAUSAL_NIB
 #define MG_DKDVQ_CAUSAL_NIB 2   // 16-row query blocks per step, 128-key fused kernel
@@ -83,18 +74,11 @@
 namespace mg {
 namespace {
 
-constexpr int kStream = 64;   // streamed rows per step
 #ifndef MG_FWD_SPLIT_CFG
 #define MG_FWD_SPLIT_CFG 2, 3, false
 #endif
 #ifndef MG_FWD_SPLIT_KS
 #define MG_FWD_SPLIT_KS 32
-#endif
-#ifndef MG_FWD_SPLIT_BELOW
-#define MG_FWD_SPLIT_BELOW 512   // forward grids below this split their key tiles in two
-#endif
-#ifndef MG_FWD_KS
-#define MG_FWD_KS 64
 #endif
 #ifndef MG_FWD_SPLIT4_UPTO
 #define MG_FWD_SPLIT4_UPTO 256     // 32-row grids up to this size split their keys four ways...
@@ -102,7 +86,6 @@ constexpr int kStream = 64;   // streamed rows per step
 #ifndef MG_FWD_SPLIT4_MIN_KEYS
 #define MG_FWD_SPLIT4_MIN_KEYS 256 // ...when each group still gets two or more 32-key tiles
 #endif
-constexpr int kFwdStream = MG_FWD_KS;   // keys per streamed forward tile
 
 template <int NW_, int OCC_, bool DB_>
 struct Cfg {
@@ -114,85 +97,9 @@ struct Cfg {
     template <int D> static constexpr int occ() { return D <= 64 ? OCC : 1; }
     static constexpr int NBUF = DB_ ? 2 : 1;   // LDS buffers for the streamed tile
 };
-using FwdCfg = Cfg<MG_FWD_CFG>;
 using FwdSplitCfg = Cfg<MG_FWD_SPLIT_CFG>;   // 32-row tiles, keys split in two
 using DkdvCfg = Cfg<MG_DKDV_CFG>;
 using DkdvqCausalCfg = Cfg<MG_DKDVQ_CAUSAL_CFG>;
-using DqCfg = Cfg<MG_DQ_CFG>;
-
-// ---------------------------------- work-first order for key-padded grids
-// In a non-causal problem with key padding, the key tiles at or past a
-// batch's key length have no query work (their workgroups only write zero
-// dK/dV rows).  Numbered in plain slot-major order such idle workgroups sit
-// between the working ones and leave CU slots empty while working tiles wait,
-// which measured 20-40 % slower than the same number of working tiles
-// dispatched back to back.  Here every XCD x takes the heads h = x (mod 8)
-// (workgroups are dealt to the eight XCDs round-robin, so block 8k + x runs
-// on XCD x and a head's tiles share one L2), and its k-th block takes the
-// k-th working (slot, head) of those heads in slot-major order, then the
-// idle ones.  Needs B*H a multiple of 8 and at most 64 heads per XCD; the
-// launcher checks both.  All lanes return the same slot and head.
-__device__ __forceinline__ int nth_set_bit(uint64_t mask, int n) {
-    for (int t = 0; t < n; ++t) mask &= mask - 1;   // drop the n lowest set bits
-    return __builtin_ctzll(mask);
-}
-
-__device__ __forceinline__ void work_first_tile(int id, int nslots, int nsplit, int key_rows,
-                                                int BH, int H, int Lk,
-                                                const int32_t *__restrict__ key_len, int &slot,
-                                                int &head) {
-    const int lane = threadIdx.x & 63;
-    const int x = id & 7, k = id >> 3;
-    const int G = BH >> 3;                // heads of this XCD's group
-    const bool valid = lane < G;
-    const int klen = valid ? key_limit(key_len, (x + 8 * lane) / H, Lk) : 0;
-    int before = 0;
-    for (int pass = 0; pass < 2; ++pass) {   // working tiles, then idle ones
-        for (int s = 0; s < nslots; ++s) {
-            const bool works = (s / nsplit) * key_rows < klen;
-            const uint64_t m = __ballot(valid && works == (pass == 0));
-            const int c = __popcll(m);
-            if (k < before + c) {
-                slot = s;
-                head = x + 8 * nth_set_bit(m, k - before);
-                return;
-            }
-            before += c;
-        }
-    }
-    slot = 0;   // not reached: the grid holds exactly nslots * B*H blocks
-    head = x;
-}
-
-// The forward's version: every query tile of a non-causal key-padded head
-// costs ceil(key length / key_rows) key tiles, so the k-th block of XCD x
-// takes its heads' (slot, head) pairs by decreasing cost (head by head within
-// one cost), and the short ones fill in at the end (a longest-first list
-// schedule per XCD).  Same requirements as work_first_tile.
-__device__ __forceinline__ void heavy_first_tile(int id, int nslots, int key_rows, int BH, int H,
-                                                 int Lk, const int32_t *__restrict__ key_len,
-                                                 int &slot, int &head) {
-    const int lane = threadIdx.x & 63;
-    const int x = id & 7, k = id >> 3;
-    const int G = BH >> 3;
-    const bool valid = lane < G;
-    const int klen = valid ? key_limit(key_len, (x + 8 * lane) / H, Lk) : 0;
-    const int cost = (klen + key_rows - 1) / key_rows;
-    int before = 0;
-    for (int v = (Lk + key_rows - 1) / key_rows; v >= 0; --v) {
-        const uint64_t m = __ballot(valid && cost == v);
-        const int c = __popcll(m) * nslots;
-        if (k < before + c) {
-            const int j = k - before;
-            head = x + 8 * nth_set_bit(m, j / nslots);
-            slot = j % nslots;
-            return;
-        }
-        before += c;
-    }
-    slot = 0;   // not reached
-    head = x;
-}
 
 // ---------------------------------------------------------------- forward --
 // Query tile of C::ROWS rows stationary (16 per wave); K and V tiles of KS
@@ -208,21 +115,20 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
                   const float *__restrict__ V, float *__restrict__ O, float *__restrict__ LSE,
                   const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
                   float scale_log2, int n_qtiles, int BH, int layer, int work_first) {
-    // keys per streamed tile (the split form streams shorter tiles, so that
-    // four of its workgroups fit in one CU's LDS)
-    constexpr int KS = (KSPLIT > 1) ? MG_FWD_SPLIT_KS : kFwdStream;
+    // keys per streamed tile (short, so that four workgroups fit in one CU's LDS)
+    constexpr int KS = MG_FWD_SPLIT_KS;
     constexpr int DQ = D / 4;    // contraction values per lane in one S chain
     constexpr int NC = D / 16;   // 16-column blocks of the head dimension
     constexpr int NJB = KS / 16; // 16-key blocks per streamed tile
     using Tile = DirectTile<KS, D, C::NW>;
     static_assert(Tile::kEven, "the vmcnt waits below count kPerWave loads per fetch");
     constexpr int NL = Tile::kPerWave;   // vector-memory operations per tile fetch
-    static_assert(KSPLIT == 1 || ((KSPLIT == 2 || KSPLIT == 4) && C::NW * NC * 256 <= KS * D),
+    static_assert((KSPLIT == 2 || KSPLIT == 4) && C::NW * NC * 256 <= KS * D,
                   "a key group's O must fit in its K tile");
     __shared__ __attribute__((aligned(16))) float Ks[KSPLIT][KS * D];
     __shared__ __attribute__((aligned(16))) float Vs[KSPLIT][KS * D];
-    // key split: m, l of groups 1 .. KSPLIT-1
-    __shared__ float xml[KSPLIT > 1 ? (KSPLIT - 1) * 2 * C::NW * 64 : 1];
+    // m, l of groups 1 .. KSPLIT-1
+    __shared__ float xml[(KSPLIT - 1) * 2 * C::NW * 64];
 
     int slot, head;
     if (work_first) {
@@ -242,8 +148,8 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = (KSPLIT > 1) ? wg / C::NW : 0;   // key group of this wave
-    const int w = (KSPLIT > 1) ? wg - hh * C::NW : wg;   // row wave within its half
+    const int hh = wg / C::NW;   // key group of this wave
+    const int w = wg - hh * C::NW;   // row wave within its half
     const int il = lane & 15;
     const int g = lane >> 4;
     const int q0 = qt * C::ROWS;
@@ -256,9 +162,9 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
     // Key split: group h takes key tiles [h*m, min(n, (h+1)*m)) with
     // m = ceil(n/KSPLIT); every group runs m iterations so that every barrier
     // is reached by all waves (a group's surplus iterations only wait).
-    const int iters = (KSPLIT > 1) ? (ntiles + KSPLIT - 1) / KSPLIT : ntiles;
+    const int iters = (ntiles + KSPLIT - 1) / KSPLIT;
     const int tbeg = hh * iters;
-    const int tend = (KSPLIT > 1) ? min(ntiles, tbeg + iters) : ntiles;
+    const int tend = min(ntiles, tbeg + iters);
     float *const Ksh = Ks[hh];
     float *const Vsh = Vs[hh];
 
@@ -299,7 +205,7 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
     __syncthreads();
     for (int it = 0; it < iters; ++it) {
         const int kt = tbeg + it;
-        const bool act = (KSPLIT == 1) || kt < tend;   // uniform over the half
+        const bool act = kt < tend;   // uniform over the half
         // 16-key blocks of this tile that hold an allowed key for some row
         // of this wave (a prefix: keys past the key length, or past the
         // wave's last row under a causal mask, are masked for every row).
@@ -404,41 +310,39 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
     }
 
     float l = sum_over_groups(l_run);
-    if constexpr (KSPLIT > 1) {
-        // Groups 1 .. KSPLIT-1 hand their (m, l, O) to group 0 through their
-        // own K tiles, which no wave reads any more; group 0 merges the
-        // online-softmax states in group order.
-        if (hh > 0) {
-            float *xo = Ks[hh];
-            float *xm = xml + (hh - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
+    // Groups 1 .. KSPLIT-1 hand their (m, l, O) to group 0 through their
+    // own K tiles, which no wave reads any more; group 0 merges the
+    // online-softmax states in group order.
+    if (hh > 0) {
+        float *xo = Ks[hh];
+        float *xm = xml + (hh - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
-                *reinterpret_cast<f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) = oacc[c];
-            xm[w * 64 + lane] = m_run;
-            xl[w * 64 + lane] = l;
-        }
-        __syncthreads();
-        if (hh > 0) return;
-        float mm = m_run;
-#pragma unroll
-        for (int h = 1; h < KSPLIT; ++h) mm = fmaxf(mm, xml[(h - 1) * 2 * C::NW * 64 + w * 64 + lane]);
-        const float mu = (mm == -INFINITY) ? 0.f : mm;
-        const float a0 = exp2_fast(m_run - mu);
-        l *= a0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) oacc[c] *= a0;
-#pragma unroll
-        for (int h = 1; h < KSPLIT; ++h) {
-            const float *xo = Ks[h];
-            const float *xm = xml + (h - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
-            const float ah = exp2_fast(xm[w * 64 + lane] - mu);
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                oacc[c] += *reinterpret_cast<const f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) * ah;
-            l += xl[w * 64 + lane] * ah;
-        }
-        m_run = mm;
+        for (int c = 0; c < NC; ++c)
+            *reinterpret_cast<f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) = oacc[c];
+        xm[w * 64 + lane] = m_run;
+        xl[w * 64 + lane] = l;
     }
+    __syncthreads();
+    if (hh > 0) return;
+    float mm = m_run;
+#pragma unroll
+    for (int h = 1; h < KSPLIT; ++h) mm = fmaxf(mm, xml[(h - 1) * 2 * C::NW * 64 + w * 64 + lane]);
+    const float mu = (mm == -INFINITY) ? 0.f : mm;
+    const float a0 = exp2_fast(m_run - mu);
+    l *= a0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) oacc[c] *= a0;
+#pragma unroll
+    for (int h = 1; h < KSPLIT; ++h) {
+        const float *xo = Ks[h];
+        const float *xm = xml + (h - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
+        const float ah = exp2_fast(xm[w * 64 + lane] - mu);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            oacc[c] += *reinterpret_cast<const f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) * ah;
+        l += xl[w * 64 + lane] * ah;
+    }
+    m_run = mm;
     if (qi < Lq) {
         const float inv = (l > 0.f) ? 1.f / l : 0.f;
         float *orow = O + ((size_t)head * Lq + qi) * D;
@@ -461,12 +365,6 @@ __device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const 
         float *__restrict__ O, float *__restrict__ LSE, const int32_t *__restrict__ key_len, \
         int H, int Lq, int Lk, int causal, float scale_log2, int n_qtiles, int BH, int layer, \
         int work_first
-template <int D, class C>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
-void attn_fwd_f32(MG_FWD_F32_ARGS) {
-    fwd_f32_body<D, C, 1>(Q, K, V, O, LSE, key_len, H, Lq, Lk, causal, scale_log2, n_qtiles, BH,
-                          layer, work_first);
-}
 template <int D, class C>
 __global__ __launch_bounds__(2 * C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
 void attn_fwd_f32_ks2(MG_FWD_F32_ARGS) {
@@ -498,185 +396,6 @@ __global__ __launch_bounds__(256) void attn_rowdot_f32(const float *__restrict__
 #pragma unroll
     for (int m = TPR / 2; m >= 1; m >>= 1) v += xor_lanes(v, m);
     if (row < rows && c4 == 0) Dws[row] = v;
-}
-
-// ------------------------------------------------------- backward: dK, dV
-// Key tile of C::ROWS keys stationary (16 per wave, one per lane column);
-// query tiles of NIB*16 rows stream through LDS.
-template <int D, int NIB, class C>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
-void attn_dkdv_f32(const float *__restrict__ Q, const float *__restrict__ K,
-                   const float *__restrict__ V, const float *__restrict__ dO,
-                   const float *__restrict__ LSE, const float *__restrict__ Dws,
-                   float *__restrict__ dK, float *__restrict__ dV,
-                   const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal, float scale,
-                   float scale_log2, int BH, int layer) {
-    constexpr int DQ = D / 4;
-    constexpr int NC = D / 16;
-    constexpr int BR = 16 * NIB;
-    using Stager = F32TileStager<BR, D, C::NT>;
-    constexpr int LD = Stager::kLd;
-    __shared__ __attribute__((aligned(16))) float Qs[C::NBUF][BR][LD];
-    __shared__ __attribute__((aligned(16))) float dOs[C::NBUF][BR][LD];
-    __shared__ __attribute__((aligned(16))) float lse2s[C::NBUF][BR];
-    __shared__ __attribute__((aligned(16))) float Ds[C::NBUF][BR];
-
-    const int slot = blockIdx.x / BH;
-    const int head = blockIdx.x - slot * BH;
-    // low key tiles see the most queries under a causal mask
-    const int kt = serpentine_rank(slot, (Lk + C::ROWS - 1) / C::ROWS, layer);
-    const int b = head / H;
-    const size_t qoff = (size_t)head * Lq * D, hoff = (size_t)head * Lk * D;
-    const float *Qh = Q + qoff;
-    const float *dOh = dO + qoff;
-    const int diag = Lk - Lq;   // causal: row i sees keys j <= i + diag
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int il = lane & 15;
-    const int g = lane >> 4;
-    const int k0 = kt * C::ROWS;
-    const int kj = k0 + 16 * (tid >> 6) + il;   // this lane's key
-
-    const int klen = key_limit(key_len, b, Lk);
-    const int nq = (Lq + BR - 1) / BR;
-    // first query tile holding a row that sees key k0
-    const int qstart = causal ? min(nq, max(0, k0 - diag) / BR) : 0;
-    const int qstop = (k0 < klen) ? nq : qstart;   // a fully padded key tile does no work
-
-    // B operands of S = Q K^T and dP = dO V^T: lane holds K[kj][g*DQ + s].
-    float kreg[DQ], vreg[DQ];
-#pragma unroll
-    for (int s4 = 0; s4 < DQ / 4; ++s4) {
-        const size_t off = hoff + (size_t)kj * D + g * DQ + 4 * s4;
-        const f32x4 kv = (kj < Lk) ? *reinterpret_cast<const f32x4 *>(K + off) : zero4();
-        const f32x4 vv = (kj < Lk) ? *reinterpret_cast<const f32x4 *>(V + off) : zero4();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            kreg[4 * s4 + e] = kv[e];
-            vreg[4 * s4 + e] = vv[e];
-        }
-    }
-
-    f32x4 dkacc[NC], dvacc[NC];   // dK^T[16c + 4g + r][kj], dV^T likewise
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        dkacc[c] = zero4();
-        dvacc[c] = zero4();
-    }
-
-    Stager qst, ost;
-    float lse_pre = 0.f, d_pre = 0.f;
-    auto load_rows = [&](int qt) {
-        qst.load(Qh, qt * BR, Lq, tid);
-        ost.load(dOh, qt * BR, Lq, tid);
-        if (tid < BR) {
-            const int row = qt * BR + tid;
-            // natural log; scaled to base 2 at the LDS store so that nothing waits
-            // for this load before the next tile's rows are consumed
-            lse_pre = (row < Lq) ? LSE[(size_t)head * Lq + row] : 0.f;
-            d_pre = (row < Lq) ? Dws[(size_t)head * Lq + row] : 0.f;
-        }
-    };
-    auto store_rows = [&](int buf) {
-        qst.store(Qs[buf], tid);
-        ost.store(dOs[buf], tid);
-        if (tid < BR) {
-            lse2s[buf][tid] = lse_pre * kLog2e;
-            Ds[buf][tid] = d_pre;
-        }
-    };
-    if (qstart < qstop) {
-        load_rows(qstart);
-        if (C::NBUF == 2) {
-            store_rows(0);
-            __syncthreads();
-        }
-    }
-
-    for (int qt = qstart; qt < qstop; ++qt) {
-        const int cur = (C::NBUF == 2) ? ((qt - qstart) & 1) : 0;
-        if (C::NBUF == 1) {
-            __syncthreads();
-            store_rows(0);
-            __syncthreads();
-        }
-        if (qt + 1 < qstop) load_rows(qt + 1);
-
-        // S[16ib + 4g + r][kj] and dP[..][kj]
-        f32x4 sacc[NIB], pacc[NIB];
-#pragma unroll
-        for (int ib = 0; ib < NIB; ++ib) {
-            sacc[ib] = zero4();
-            pacc[ib] = zero4();
-        }
-#pragma unroll
-        for (int s4 = 0; s4 < DQ / 4; ++s4) {
-            f32x4 aq[NIB], ao[NIB];
-#pragma unroll
-            for (int ib = 0; ib < NIB; ++ib) {
-                aq[ib] = *reinterpret_cast<const f32x4 *>(&Qs[cur][16 * ib + il][g * DQ + 4 * s4]);
-                ao[ib] = *reinterpret_cast<const f32x4 *>(&dOs[cur][16 * ib + il][g * DQ + 4 * s4]);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int ib = 0; ib < NIB; ++ib) {
-                    sacc[ib] = mfma16x16x4(aq[ib][e], kreg[4 * s4 + e], sacc[ib]);
-                    pacc[ib] = mfma16x16x4(ao[ib][e], vreg[4 * s4 + e], pacc[ib]);
-                }
-        }
-
-        // P = exp(S - LSE), dS = P (dP - D).  Under a causal mask element
-        // (ib, r) is query ibase + 16ib + r, allowed iff it is >= kj - diag.  Padded
-        // keys (kj >= key length) are not masked here: their rows of dK and dV
-        // are overwritten with zeros at the end.  Rows past Lq hold Q = dO = 0
-        // and LSE = D = 0, so they contribute exactly nothing.
-        const int ibase = qt * BR + 4 * g;
-        const int thr = causal ? kj - diag - ibase : INT_MIN;
-#pragma unroll
-        for (int ib = 0; ib < NIB; ++ib) {
-            const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lse2s[cur][16 * ib + 4 * g]);
-            const f32x4 dd = *reinterpret_cast<const f32x4 *>(&Ds[cur][16 * ib + 4 * g]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float p = exp2_fast(sacc[ib][r] * scale_log2 - l2[r]);
-                p = (16 * ib + r >= thr) ? p : 0.f;
-                sacc[ib][r] = p;
-                pacc[ib][r] = p * (pacc[ib][r] - dd[r]);
-            }
-        }
-
-        // dV^T[16c + 4g + r][kj] += sum_i dO[i][16c + il'] P[i][kj]
-        // dK^T[16c + 4g + r][kj] += sum_i  Q[i][16c + il'] dS[i][kj]
-#pragma unroll
-        for (int ib = 0; ib < NIB; ++ib)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    dvacc[c] = mfma16x16x4(dOs[cur][16 * ib + 4 * g + r][16 * c + il],
-                                           sacc[ib][r], dvacc[c]);
-                    dkacc[c] = mfma16x16x4(Qs[cur][16 * ib + 4 * g + r][16 * c + il],
-                                           pacc[ib][r], dkacc[c]);
-                }
-
-        if (C::NBUF == 2) {
-            if (qt + 1 < qstop) store_rows(cur ^ 1);
-            __syncthreads();
-        }
-    }
-
-    if (kj < Lk) {
-        const bool keep = kj < klen;   // padded keys get exact zeros
-        float *dkrow = dK + hoff + (size_t)kj * D;
-        float *dvrow = dV + hoff + (size_t)kj * D;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            *reinterpret_cast<f32x4 *>(dkrow + 16 * c + 4 * g) = keep ? dkacc[c] * scale : zero4();
-            *reinterpret_cast<f32x4 *>(dvrow + 16 * c + 4 * g) = keep ? dvacc[c] : zero4();
-        }
-    }
 }
 
 // ---------------------------------------- backward: dK, dV and dQ partials
@@ -1093,159 +812,7 @@ __global__ __launch_bounds__(256) void attn_bwd_reduce_f32(
                         Lq, Lk, causal, scale, BH, key_rows);
 }
 
-// ------------------------------------------------------------ backward: dQ
-// Query tile of C::ROWS rows stationary (16 per wave); key tiles stream.
-template <int D, class C>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
-void attn_dq_f32(const float *__restrict__ Q, const float *__restrict__ K,
-                 const float *__restrict__ V, const float *__restrict__ dO,
-                 const float *__restrict__ LSE, const float *__restrict__ Dws,
-                 float *__restrict__ dQ, const int32_t *__restrict__ key_len, int H, int Lq,
-                 int Lk, int causal, float scale, float scale_log2, int n_qtiles, int BH, int layer) {
-    constexpr int DQ = D / 4;
-    constexpr int NC = D / 16;
-    using Stager = F32TileStager<kStream, D, C::NT>;
-    constexpr int LD = Stager::kLd;
-    __shared__ __attribute__((aligned(16))) float Ks[C::NBUF][kStream][LD];
-    __shared__ __attribute__((aligned(16))) float Vs[C::NBUF][kStream][LD];
-
-    const int slot = blockIdx.x / BH;
-    const int head = blockIdx.x - slot * BH;
-    const int rank = serpentine_rank(slot, n_qtiles, layer);
-    const int qt = causal ? (n_qtiles - 1 - rank) : rank;
-    const int b = head / H;
-    const size_t qoff = (size_t)head * Lq * D, hoff = (size_t)head * Lk * D;
-    const float *Kh = K + hoff;
-    const float *Vh = V + hoff;
-    const int diag = Lk - Lq;   // causal: row i sees keys j <= i + diag
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int il = lane & 15;
-    const int g = lane >> 4;
-    const int q0 = qt * C::ROWS;
-    const int qi = q0 + 16 * (tid >> 6) + il;
-
-    const int klen = key_limit(key_len, b, Lk);
-    const int kend = causal ? min(klen, q0 + C::ROWS + diag) : klen;
-    const int ntiles = (kend + kStream - 1) / kStream;
-
-    float qreg[DQ], oreg[DQ];
-#pragma unroll
-    for (int s4 = 0; s4 < DQ / 4; ++s4) {
-        const size_t off = qoff + (size_t)qi * D + g * DQ + 4 * s4;
-        const f32x4 qv = (qi < Lq) ? *reinterpret_cast<const f32x4 *>(Q + off) : zero4();
-        const f32x4 ov = (qi < Lq) ? *reinterpret_cast<const f32x4 *>(dO + off) : zero4();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            qreg[4 * s4 + e] = qv[e];
-            oreg[4 * s4 + e] = ov[e];
-        }
-    }
-    const float lse2 = (qi < Lq) ? LSE[(size_t)head * Lq + qi] * kLog2e : 0.f;
-    const float Di = (qi < Lq) ? Dws[(size_t)head * Lq + qi] : 0.f;
-
-    f32x4 dqacc[NC];   // dQ^T[16c + 4g + r][qi]
-#pragma unroll
-    for (int c = 0; c < NC; ++c) dqacc[c] = zero4();
-
-    Stager kst, vst;
-    if (ntiles > 0) {
-        kst.load(Kh, 0, Lk, tid);
-        vst.load(Vh, 0, Lk, tid);
-        if (C::NBUF == 2) {
-            kst.store(Ks[0], tid);
-            vst.store(Vs[0], tid);
-            __syncthreads();
-        }
-    }
-    for (int kt = 0; kt < ntiles; ++kt) {
-        const int cur = (C::NBUF == 2) ? (kt & 1) : 0;
-        if (C::NBUF == 1) {
-            __syncthreads();
-            kst.store(Ks[0], tid);
-            vst.store(Vs[0], tid);
-            __syncthreads();
-        }
-        if (kt + 1 < ntiles) {
-            kst.load(Kh, (kt + 1) * kStream, Lk, tid);
-            vst.load(Vh, (kt + 1) * kStream, Lk, tid);
-        }
-
-        // S^T[j][qi] and dP^T[j][qi], j = 16jb + 4g + r
-        f32x4 sacc[4], pacc[4];
-#pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
-            sacc[jb] = zero4();
-            pacc[jb] = zero4();
-        }
-#pragma unroll
-        for (int s4 = 0; s4 < DQ / 4; ++s4) {
-            f32x4 ak[4], av[4];
-#pragma unroll
-            for (int jb = 0; jb < 4; ++jb) {
-                ak[jb] = *reinterpret_cast<const f32x4 *>(&Ks[cur][16 * jb + il][g * DQ + 4 * s4]);
-                av[jb] = *reinterpret_cast<const f32x4 *>(&Vs[cur][16 * jb + il][g * DQ + 4 * s4]);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int jb = 0; jb < 4; ++jb) {
-                    sacc[jb] = mfma16x16x4(ak[jb][e], qreg[4 * s4 + e], sacc[jb]);
-                    pacc[jb] = mfma16x16x4(av[jb][e], oreg[4 * s4 + e], pacc[jb]);
-                }
-        }
-
-        // Element (jb, r) holds key j0 + 16jb + r; same threshold as forward.
-        const int j0 = kt * kStream + 4 * g;
-        const int thr = causal ? min(klen - j0, qi + diag - j0 + 1) : klen - j0;
-#pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float p = exp2_fast(sacc[jb][r] * scale_log2 - lse2);
-                p = (16 * jb + r < thr) ? p : 0.f;
-                pacc[jb][r] = p * (pacc[jb][r] - Di);
-            }
-
-        // dQ^T[16c + 4g + r][qi] += sum_j K[j][16c + il'] dS^T[j][qi]
-#pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < NC; ++c)
-                    dqacc[c] = mfma16x16x4(Ks[cur][16 * jb + 4 * g + r][16 * c + il],
-                                           pacc[jb][r], dqacc[c]);
-
-        if (C::NBUF == 2) {
-            if (kt + 1 < ntiles) {
-                kst.store(Ks[cur ^ 1], tid);
-                vst.store(Vs[cur ^ 1], tid);
-            }
-            __syncthreads();
-        }
-    }
-
-    if (qi < Lq) {
-        float *dqrow = dQ + qoff + (size_t)qi * D;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            *reinterpret_cast<f32x4 *>(dqrow + 16 * c + 4 * g) = dqacc[c] * scale;
-    }
-}
-
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
-// Key-padded non-causal grids take the XCD-grouped work orders
-// (heavy_first_tile, work_first_tile) when the heads split evenly over the
-// eight XCDs, at most 64 per XCD, and the per-workgroup search (one ballot
-// per key tile) stays short: at most 1024 key tiles.
-inline int padded_work_order(const AttnProblem &p) {
-    const int BH = p.B * p.H;
-    return (p.key_len != nullptr && !p.causal && BH % 8 == 0 && BH <= 512 &&
-            p.Lk <= 1024 * 64) ? 1 : 0;
-}
 
 }  // namespace
 
@@ -1263,44 +830,26 @@ void launch_fwd_f32_as(Kern kern, int ksplit, const AttnProblem &p, const float 
 }
 }  // namespace
 
-hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K,
-                          const float *V, float *O, float *LSE, hipStream_t s) {
-    // Grids of fewer than MG_FWD_SPLIT_BELOW workgroups of 64 rows fall
-    // unevenly on the CUs (288 of them on 256 CUs put two on 32 CUs, which
-    // then set the kernel's time).  There the query tiles shrink to 32 rows
-    // and each workgroup splits its key tiles over two halves: four times
-    // the workgroups, each a quarter of the work (d <= 64, two or more key tiles).
-    // When even the 32-row grid leaves most CUs without a workgroup and the
-    // key side is long, the key tiles go to four groups instead of two.
-    const long grid = (long)cdiv(p.Lq, FwdCfg::ROWS) * p.B * p.H;
-    const bool split = p.d <= 64 && grid < MG_FWD_SPLIT_BELOW && p.Lk > kFwdStream;
-    const bool split4 = split && (long)cdiv(p.Lq, FwdSplitCfg::ROWS) * p.B * p.H <=
-                                     MG_FWD_SPLIT4_UPTO && p.Lk >= MG_FWD_SPLIT4_MIN_KEYS;
+// The key-split forms: 32-row query tiles, whose keys go to two or four groups
+// of waves, four when even the 32-row grid leaves most CUs without a
+// workgroup and the key side is long.  Taken for small d <= 64 grids (see
+// launch_fwd_f32 for where they end).
+hipError_t launch_fwd_f32_keysplit(const AttnProblem &p, const float *Q, const float *K,
+                                   const float *V, float *O, float *LSE, hipStream_t s) {
+    const bool split4 = (long)cdiv(p.Lq, FwdSplitCfg::ROWS) * p.B * p.H <= MG_FWD_SPLIT4_UPTO &&
+                        p.Lk >= MG_FWD_SPLIT4_MIN_KEYS;
+    auto go = [&](auto ks2, auto ks4) {
+        if (split4)
+            launch_fwd_f32_as<FwdSplitCfg>(ks4, 4, p, Q, K, V, O, LSE, s);
+        else
+            launch_fwd_f32_as<FwdSplitCfg>(ks2, 2, p, Q, K, V, O, LSE, s);
+        return hipGetLastError();
+    };
     switch (p.d) {
-    case 32:
-        if (split4)
-            launch_fwd_f32_as<FwdSplitCfg>(attn_fwd_f32_ks4<32, FwdSplitCfg>, 4, p, Q, K, V, O,
-                                           LSE, s);
-        else if (split)
-            launch_fwd_f32_as<FwdSplitCfg>(attn_fwd_f32_ks2<32, FwdSplitCfg>, 2, p, Q, K, V, O,
-                                           LSE, s);
-        else
-            launch_fwd_f32_as<FwdCfg>(attn_fwd_f32<32, FwdCfg>, 1, p, Q, K, V, O, LSE, s);
-        break;
-    case 64:
-        if (split4)
-            launch_fwd_f32_as<FwdSplitCfg>(attn_fwd_f32_ks4<64, FwdSplitCfg>, 4, p, Q, K, V, O,
-                                           LSE, s);
-        else if (split)
-            launch_fwd_f32_as<FwdSplitCfg>(attn_fwd_f32_ks2<64, FwdSplitCfg>, 2, p, Q, K, V, O,
-                                           LSE, s);
-        else
-            launch_fwd_f32_as<FwdCfg>(attn_fwd_f32<64, FwdCfg>, 1, p, Q, K, V, O, LSE, s);
-        break;
-    case 128: launch_fwd_f32_as<FwdCfg>(attn_fwd_f32<128, FwdCfg>, 1, p, Q, K, V, O, LSE, s); break;
+    case 32: return go(attn_fwd_f32_ks2<32, FwdSplitCfg>, attn_fwd_f32_ks4<32, FwdSplitCfg>);
+    case 64: return go(attn_fwd_f32_ks2<64, FwdSplitCfg>, attn_fwd_f32_ks4<64, FwdSplitCfg>);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const float *dO,
@@ -1311,27 +860,6 @@ hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const flo
     case 32: attn_rowdot_f32<32><<<dim3(cdiv(rows, 256 / 8)), block, 0, s>>>(O, dO, Dws, rows); break;
     case 64: attn_rowdot_f32<64><<<dim3(cdiv(rows, 256 / 16)), block, 0, s>>>(O, dO, Dws, rows); break;
     case 128: attn_rowdot_f32<128><<<dim3(cdiv(rows, 256 / 32)), block, 0, s>>>(O, dO, Dws, rows); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_dkdv_f32(const AttnProblem &p, const float *Q, const float *K,
-                               const float *V, const float *dO, const float *LSE,
-                               const float *Dws, float *dK, float *dV, hipStream_t s) {
-    using C = DkdvCfg;
-    const int BH = p.B * p.H;
-    const dim3 grid(cdiv(p.Lk, C::ROWS) * BH), block(C::NT);
-    const float sl2 = p.scale * kLog2e;
-    auto go = [&](auto kern) {
-        const int ly = causal_rank_layer((const void *)kern, C::NT, grid.x, BH, p.causal);
-        kern<<<grid, block, 0, s>>>(Q, K, V, dO, LSE, Dws, dK, dV, p.key_len, p.H, p.Lq, p.Lk,
-                                    p.causal, p.scale, sl2, BH, ly);
-    };
-    switch (p.d) {
-    case 32: go(attn_dkdv_f32<32, MG_DKDV_NIB, C>); break;
-    case 64: go(attn_dkdv_f32<64, MG_DKDV_NIB, C>); break;
-    case 128: go(attn_dkdv_f32<128, 2, C>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1458,28 +986,6 @@ hipError_t launch_bwd_dq_reduce_f32(const AttnProblem &p, const float *dQp, floa
     switch (p.d) {
     case 32: attn_dq_reduce_f32<32><<<grid, block, 0, s>>>(dQp, dQ, p.key_len, p.H, p.Lq, p.Lk, p.causal, p.scale, BH, kr); break;
     case 64: attn_dq_reduce_f32<64><<<grid, block, 0, s>>>(dQp, dQ, p.key_len, p.H, p.Lq, p.Lk, p.causal, p.scale, BH, kr); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_dq_f32(const AttnProblem &p, const float *Q, const float *K,
-                             const float *V, const float *dO, const float *LSE,
-                             const float *Dws, float *dQ, hipStream_t s) {
-    using C = DqCfg;
-    const int BH = p.B * p.H;
-    const int nqt = cdiv(p.Lq, C::ROWS);
-    const dim3 grid(nqt * BH), block(C::NT);
-    const float sl2 = p.scale * kLog2e;
-    auto go = [&](auto kern) {
-        const int ly = causal_rank_layer((const void *)kern, C::NT, grid.x, BH, p.causal);
-        kern<<<grid, block, 0, s>>>(Q, K, V, dO, LSE, Dws, dQ, p.key_len, p.H, p.Lq, p.Lk,
-                                    p.causal, p.scale, sl2, nqt, BH, ly);
-    };
-    switch (p.d) {
-    case 32: go(attn_dq_f32<32, C>); break;
-    case 64: go(attn_dq_f32<64, C>); break;
-    case 128: go(attn_dq_f32<128, C>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -1,0 +1,506 @@
+// attn_f32x3_bwd.hip -- strict-f32 attention backward on the bf16 matrix
+// cores: every product takes its f32 operands as three bf16 parts
+// (tiles_split.h).
+//
+// Two kernels, neither of which needs partial sums in memory: a
+// query-stationary dQ kernel, which also computes D_i = sum_k dO_ik O_ik for
+// its rows and writes it, and the key-stationary dK/dV kernel that reads D
+// after it.  Both recompute S and dP, 14 d instead of the 10 d operations per
+// pair of the fused kernel in attn_f32.hip, and drop that kernel's dQ partials
+// (written and read back, 151 MB at B8 H8 L1024 d64), their reduction and the
+// separate D launch.
+#include "device_common.h"
+#include "launch.h"
+#include "tiles_split.h"
+#include "work_order.h"
+
+namespace mg {
+namespace {
+
+// Wave-wide sum of a lane's products over the head dimension.
+template <int D>
+__device__ __forceinline__ float wave_dot(const float *a, const float *b, int lane) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < (D + 63) / 64; ++e)
+        if (64 * e + lane < D) s = fmaf(a[64 * e + lane], b[64 * e + lane], s);
+    for (int x = 32; x >= 1; x >>= 1) s += xor_lanes(s, x);
+    return s;
+}
+
+// Rows (dQ) or keys (dK, dV) whose fast result is not finite: plain f32
+// arithmetic, one at a time over the wave, keys outside the mask left out.
+template <int D>
+__device__ __noinline__ void dq_rows_plain(const float *Q, const float *K, const float *V,
+                                           const float *dO, const float *LSE, const float *Dw,
+                                           float *dQ, int row0, int nrows, int Lq, int kend,
+                                           int causal, int diag, float scale, float scale_log2,
+                                           int lane) {
+    constexpr int NE = (D + 63) / 64;
+    for (int i = row0; i < min(row0 + nrows, Lq); ++i) {
+        float acc[NE] = {};
+        const float lse2 = LSE[i] * kLog2e, Di = Dw[i];
+        const int n = causal ? min(kend, i + diag + 1) : kend;
+        for (int j = 0; j < n; ++j) {
+            const float s = wave_dot<D>(Q + (size_t)i * D, K + (size_t)j * D, lane);
+            const float dp = wave_dot<D>(dO + (size_t)i * D, V + (size_t)j * D, lane);
+            const float ds = exp2_fast(s * scale_log2 - lse2) * (dp - Di);
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+                if (64 * e + lane < D) acc[e] = fmaf(ds, K[(size_t)j * D + 64 * e + lane], acc[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (64 * e + lane < D) dQ[(size_t)i * D + 64 * e + lane] = acc[e] * scale;
+    }
+}
+
+template <int D>
+__device__ __noinline__ void dkdv_keys_plain(const float *Q, const float *K, const float *V,
+                                             const float *dO, const float *LSE, const float *Dw,
+                                             float *dK, float *dV, int key0, int nkeys, int klen,
+                                             int Lq, int causal, int diag, float scale,
+                                             float scale_log2, int lane) {
+    constexpr int NE = (D + 63) / 64;
+    for (int j = key0; j < min(key0 + nkeys, klen); ++j) {
+        float ak[NE] = {}, av[NE] = {};
+        for (int i = causal ? max(0, j - diag) : 0; i < Lq; ++i) {
+            const float s = wave_dot<D>(Q + (size_t)i * D, K + (size_t)j * D, lane);
+            const float dp = wave_dot<D>(dO + (size_t)i * D, V + (size_t)j * D, lane);
+            const float p = exp2_fast(s * scale_log2 - LSE[i] * kLog2e), ds = p * (dp - Dw[i]);
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+                if (64 * e + lane < D) {
+                    av[e] = fmaf(p, dO[(size_t)i * D + 64 * e + lane], av[e]);
+                    ak[e] = fmaf(ds, Q[(size_t)i * D + 64 * e + lane], ak[e]);
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (64 * e + lane < D) {
+                dK[(size_t)j * D + 64 * e + lane] = ak[e] * scale;
+                dV[(size_t)j * D + 64 * e + lane] = av[e];
+            }
+    }
+}
+
+// ------------------------------------------------------------------------ dQ --
+// QW waves of 16 QB query rows; key tiles of KT keys, double-buffered.
+template <int D, int QB, int QW, int KT>
+__global__ __launch_bounds__(64 * QW) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
+                   const float *__restrict__ V, const float *__restrict__ O,
+                   const float *__restrict__ dO, const float *__restrict__ LSE,
+                   float *__restrict__ Dws, float *__restrict__ dQ,
+                   const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
+                   float scale, float scale_log2, int n_qtiles, int BH, int layer,
+                   int padded_order) {
+    constexpr int NT = 64 * QW;
+    constexpr int NS = D / 32, NC = D / 16, NKB = KT / 16, WQ = 16 * QB;
+    using Tile = Bf16Tile<KT, D, 1, 32, 1, 3, 1>;
+    constexpr int BLK = Tile::kBlock, TS = 3 * Tile::kSize;
+    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][TS], Vs[2][TS];
+
+    int slot, head;
+    if (padded_order) {
+        heavy_first_tile(blockIdx.x, n_qtiles, KT, BH, H, Lk, key_len, slot, head);
+    } else {
+        slot = blockIdx.x / BH;
+        head = blockIdx.x - slot * BH;
+    }
+    const int rank = serpentine_rank(slot, n_qtiles, layer);
+    const int qt = causal ? (n_qtiles - 1 - rank) : rank;
+    const size_t qoff = (size_t)head * Lq * D, hoff = (size_t)head * Lk * D;
+    const float *Qh = Q + qoff, *dOh = dO + qoff, *Kh = K + hoff, *Vh = V + hoff;
+    const int diag = Lk - Lq;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int il = lane & 15, g = lane >> 4;
+    const int jr = il >> 2, jc = 4 * (il & 3);
+    const int q0 = qt * WQ * QW, qw0 = q0 + WQ * w, qi = qw0 + il;
+
+    const int klen = key_limit(key_len, head / H, Lk);
+    const int kend = causal ? min(klen, q0 + WQ * QW + diag) : klen;
+    const int ntiles = max((kend + KT - 1) / KT, 0);
+
+    SplitStager<Tile, KT, D, NT> sk, sv;
+    if (ntiles > 0) {
+        sk.load(Kh, 0, klen, tid);
+        sv.load(Vh, 0, klen, tid);
+    }
+    // parts of Q and dO [qi + 16qb][32s + 8g + e]; D from dO and O on the way
+    Split8 qreg[NS][QB], oreg[NS][QB];
+    float lse2[QB], Di[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int q = qi + 16 * qb;
+        lse2[qb] = (q < Lq) ? LSE[(size_t)head * Lq + q] * kLog2e : 0.f;
+        float dsum = 0.f;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            f32x4 a = zero4(), b = zero4(), x = zero4(), y = zero4();
+            if (q < Lq) {
+                const size_t off = qoff + (size_t)q * D + 32 * s + 8 * g;
+                a = *reinterpret_cast<const f32x4 *>(Q + off);
+                b = *reinterpret_cast<const f32x4 *>(Q + off + 4);
+                x = *reinterpret_cast<const f32x4 *>(dO + off);
+                y = *reinterpret_cast<const f32x4 *>(dO + off + 4);
+                const f32x4 u = *reinterpret_cast<const f32x4 *>(O + off);
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(O + off + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dsum = fmaf(x[e], u[e], fmaf(y[e], v[e], dsum));
+            }
+            qreg[s][qb] = split8(a, b);
+            oreg[s][qb] = split8(x, y);
+        }
+        Di[qb] = sum_over_groups(dsum);
+        if (q < Lq && g == 0) Dws[(size_t)head * Lq + q] = Di[qb];
+    }
+    const int ka = Tile::at(il, 8 * g);
+    const int kt_[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
+
+    f32x4 dqacc[NC][QB];   // dQ^T[16c + 4g + r][qi + 16qb]
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] = zero4();
+
+    if (ntiles > 0) {
+        sk.store(Ks[0], tid);
+        sv.store(Vs[0], tid);
+        sk.load(Kh, KT, klen, tid);
+        sv.load(Vh, KT, klen, tid);
+    }
+    __syncthreads();
+    for (int kt = 0; kt < ntiles; ++kt) {
+        const int cur = kt & 1;
+        if (kt + 1 < ntiles) {   // tile kt + 1 goes to the buffer the last barrier freed
+            sk.store(Ks[cur ^ 1], tid);
+            sv.store(Vs[cur ^ 1], tid);
+            sk.load(Kh, (kt + 2) * KT, klen, tid);
+            sv.load(Vh, (kt + 2) * KT, klen, tid);
+        }
+        const int jt = kt * KT;
+        if (!causal || jt <= qw0 + WQ - 1 + diag) {
+            const uint16_t *Kc = Ks[cur], *Vc = Vs[cur];
+            f32x4 sacc[NKB][QB], pacc[NKB][QB];   // S^T, dP^T[16kb + 4g + r][qi + 16qb]
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    sacc[kb][qb] = zero4();
+                    pacc[kb][qb] = zero4();
+                }
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) {
+                    const int o = ka + s * BLK + 32 * 16 * kb;
+                    mfma_split(load_split<Tile>(Kc, o), qreg[s], sacc[kb]);
+                    mfma_split(load_split<Tile>(Vc, o), oreg[s], pacc[kb]);
+                }
+            // two products' operand reads in flight (d = 128: 89 -> 82 us at B2 H8 L1024)
+            sched_reads_ahead<6 * NS * NKB, 12 * QB * NS * NKB, 6, 3, 6 * QB, 0>();
+            // dS^T = P^T (dP^T - D), P^T = exp2(S^T * scale*log2e - LSE*log2e)
+            const bool masked = jt + KT > klen || (causal && jt + KT - 1 > qw0 + diag);
+            const int j0 = jt + 4 * g;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int thr = causal ? min(klen - j0, qi + 16 * qb + diag - j0 + 1) : klen - j0;
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float p = exp2_fast(fmaf(sacc[kb][qb][r], scale_log2, -lse2[qb]));
+                        pacc[kb][qb][r] = p * (pacc[kb][qb][r] - Di[qb]);
+                    }
+                if (masked) {
+#pragma unroll
+                    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (16 * kb + r >= thr) pacc[kb][qb][r] = 0.f;
+                }
+            }
+            // dQ^T[16c + .][qi] += sum_j K^T[16c + il'][j] dS^T[j][qi], 32 keys per step
+#pragma unroll
+            for (int t = 0; t < NKB / 2; ++t) {
+                Split8 ds[QB];
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) ds[qb] = split8(pacc[2 * t][qb], pacc[2 * t + 1][qb]);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const int o = kt_[c & 1] + (c >> 1) * BLK + 32 * 32 * t;
+                    // a fresh sum per tile, added once: rounds at the size of dQ once
+                    // per 32 keys instead of six times (B4 H16 L2048 d64: dQ error
+                    // 9.6e-7 -> 6.8e-7, 3 % of the kernel's time)
+                    f32x4 part[QB];
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) part[qb] = zero4();
+                    mfma_split(load_split_tr<Tile>(Kc, o, o + 32 * 16), ds, part);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] += part[qb];
+                }
+            }
+            sched_reads_ahead<6 * NC * NKB / 2, 6 * QB * NC * NKB / 2, 6, 6, 6 * QB, 1>();
+        }
+        __syncthreads();   // tile kt + 1 visible; tile kt's buffers free
+    }
+
+    bool fine = true;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int q = qi + 16 * qb;
+        if (q < Lq) {
+            float chk = 0.f;
+            float *row = dQ + qoff + (size_t)q * D;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const f32x4 v = dqacc[c][qb] * scale;
+                *reinterpret_cast<f32x4 *>(row + 16 * c + 4 * g) = v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) chk = fmaf(v[e], 0.f, chk);   // NaN if not finite
+            }
+            fine = fine && finite_f32(chk);
+        }
+    }
+    if (!__all(fine)) {
+        __threadfence_block();   // this wave's D rows are in memory
+        dq_rows_plain<D>(Qh, Kh, Vh, dOh, LSE + (size_t)head * Lq, Dws + (size_t)head * Lq,
+                         dQ + qoff, qw0, WQ, Lq, klen, causal, diag, scale, scale_log2, lane);
+    }
+}
+
+// -------------------------------------------------------------------- dK, dV --
+// KW waves of 16 keys; query tiles of QT rows, double-buffered.
+template <int D, int KW, int QT>
+__global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
+                     const float *__restrict__ V, const float *__restrict__ dO,
+                     const float *__restrict__ LSE, const float *__restrict__ Dws,
+                     float *__restrict__ dK, float *__restrict__ dV,
+                     const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
+                     float scale, float scale_log2, int n_ktiles, int BH, int layer,
+                     int padded_order) {
+    constexpr int NT = 64 * KW;
+    constexpr int NS = D / 32, NC = D / 16, NIB = QT / 16, KR = 16 * KW;
+    using Tile = Bf16Tile<QT, D, 1, 32, 1, 3, 1>;
+    constexpr int BLK = Tile::kBlock, TS = 3 * Tile::kSize;
+    __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TS], Os[2][TS];
+    __shared__ __attribute__((aligned(16))) float lse2s[2][QT], Ds[2][QT];
+
+    int slot, head;
+    if (padded_order) {
+        work_first_tile(blockIdx.x, n_ktiles, 1, KR, BH, H, Lk, key_len, slot, head);
+    } else {
+        slot = blockIdx.x / BH;
+        head = blockIdx.x - slot * BH;
+    }
+    const int kt = serpentine_rank(slot, n_ktiles, layer);   // low key tiles see the most queries
+    const size_t qoff = (size_t)head * Lq * D, hoff = (size_t)head * Lk * D;
+    const float *Qh = Q + qoff, *dOh = dO + qoff;
+    const int diag = Lk - Lq;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int il = lane & 15, g = lane >> 4;
+    const int jr = il >> 2, jc = 4 * (il & 3);
+    const int k0 = kt * KR, wkey0 = k0 + 16 * w, kj = wkey0 + il;
+
+    const int klen = key_limit(key_len, head / H, Lk);
+    const int nq = (Lq + QT - 1) / QT;
+    const int qstart = causal ? min(nq, max(0, k0 - diag) / QT) : 0;
+    const int qstop = (k0 < klen) ? nq : qstart;
+
+    SplitStager<Tile, QT, D, NT> sq, so;
+    float lse_pre = 0.f, d_pre = 0.f;
+    auto load = [&](int qt) {
+        sq.load(Qh, qt * QT, Lq, tid);
+        so.load(dOh, qt * QT, Lq, tid);
+        if (tid < QT) {
+            const int row = qt * QT + tid;
+            lse_pre = (row < Lq) ? LSE[(size_t)head * Lq + row] : 0.f;
+            d_pre = (row < Lq) ? Dws[(size_t)head * Lq + row] : 0.f;
+        }
+    };
+    auto store = [&](int buf) {
+        sq.store(Qs[buf], tid);
+        so.store(Os[buf], tid);
+        if (tid < QT) {
+            lse2s[buf][tid] = lse_pre * kLog2e;
+            Ds[buf][tid] = d_pre;
+        }
+    };
+    if (qstart < qstop) load(qstart);
+
+    // B operands of S = Q K^T and dP = dO V^T: parts of K, V[kj][32s + 8g + e]
+    Split8 kreg[NS][1], vreg[NS][1];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        f32x4 a = zero4(), b = zero4(), x = zero4(), y = zero4();
+        if (kj < klen) {
+            const size_t off = hoff + (size_t)kj * D + 32 * s + 8 * g;
+            a = *reinterpret_cast<const f32x4 *>(K + off);
+            b = *reinterpret_cast<const f32x4 *>(K + off + 4);
+            x = *reinterpret_cast<const f32x4 *>(V + off);
+            y = *reinterpret_cast<const f32x4 *>(V + off + 4);
+        }
+        kreg[s][0] = split8(a, b);
+        vreg[s][0] = split8(x, y);
+    }
+    const int qa = Tile::at(il, 8 * g);
+    const int qb_[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
+
+    f32x4 dkacc[NC][1], dvacc[NC][1];   // dK^T, dV^T[16c + 4g + r][kj]
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        dkacc[c][0] = zero4();
+        dvacc[c][0] = zero4();
+    }
+    if (qstart < qstop) {
+        store(0);
+        if (qstart + 1 < qstop) load(qstart + 1);
+    }
+    __syncthreads();
+    for (int qt = qstart; qt < qstop; ++qt) {
+        const int cur = (qt - qstart) & 1;
+        if (qt + 1 < qstop) {
+            store(cur ^ 1);
+            if (qt + 2 < qstop) load(qt + 2);
+        }
+        if (wkey0 < klen && (!causal || wkey0 - diag <= qt * QT + QT - 1)) {
+            const uint16_t *Qc = Qs[cur], *Oc = Os[cur];
+            f32x4 sacc[NIB][1], pacc[NIB][1];   // S, dP[16ib + 4g + r][kj]
+#pragma unroll
+            for (int ib = 0; ib < NIB; ++ib) {
+                sacc[ib][0] = zero4();
+                pacc[ib][0] = zero4();
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int ib = 0; ib < NIB; ++ib) {
+                    const int o = qa + s * BLK + 32 * 16 * ib;
+                    mfma_split(load_split<Tile>(Qc, o), kreg[s], sacc[ib]);
+                    mfma_split(load_split<Tile>(Oc, o), vreg[s], pacc[ib]);
+                }
+            if constexpr (D == 128) sched_reads_ahead<6 * NS * NIB, 12 * NS * NIB, 6, 3, 6, 2>();
+            const bool masked = causal && qt * QT + diag < wkey0 + 15;
+            const int thr = kj - diag - (qt * QT + 4 * g);
+#pragma unroll
+            for (int ib = 0; ib < NIB; ++ib) {
+                const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lse2s[cur][16 * ib + 4 * g]);
+                const f32x4 dd = *reinterpret_cast<const f32x4 *>(&Ds[cur][16 * ib + 4 * g]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float p = exp2_fast(fmaf(sacc[ib][0][r], scale_log2, -l2[r]));
+                    if (masked && 16 * ib + r < thr) p = 0.f;
+                    sacc[ib][0][r] = p;
+                    pacc[ib][0][r] = p * (pacc[ib][0][r] - dd[r]);
+                }
+            }
+            // dV^T[16c + .][kj] += dO^T[16c + il'][i] P[i][kj]; dK^T likewise with Q, dS
+#pragma unroll
+            for (int t = 0; t < NIB / 2; ++t) {
+                const Split8 pb[1] = {split8(sacc[2 * t][0], sacc[2 * t + 1][0])};
+                const Split8 sb[1] = {split8(pacc[2 * t][0], pacc[2 * t + 1][0])};
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const int o = qb_[c & 1] + (c >> 1) * BLK + 32 * 32 * t;
+                    mfma_split(load_split_tr<Tile>(Oc, o, o + 32 * 16), pb, dvacc[c]);
+                    mfma_split(load_split_tr<Tile>(Qc, o, o + 32 * 16), sb, dkacc[c]);
+                }
+            }
+            if constexpr (D == 128) sched_reads_ahead<12 * NC * NIB / 2, 12 * NC * NIB / 2, 6, 6, 6, 3>();
+        }
+        __syncthreads();   // next tile visible; this tile's buffers free
+    }
+
+    bool fine = true;
+    if (kj < Lk) {
+        const bool keep = kj < klen;   // padded keys get exact zeros
+        float *dkrow = dK + hoff + (size_t)kj * D, *dvrow = dV + hoff + (size_t)kj * D;
+        float chk = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const f32x4 a = keep ? dkacc[c][0] * scale : zero4();
+            const f32x4 b = keep ? dvacc[c][0] : zero4();
+            *reinterpret_cast<f32x4 *>(dkrow + 16 * c + 4 * g) = a;
+            *reinterpret_cast<f32x4 *>(dvrow + 16 * c + 4 * g) = b;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) chk = fmaf(a[e], 0.f, fmaf(b[e], 0.f, chk));
+        }
+        fine = finite_f32(chk);
+    }
+    if (!__all(fine))
+        dkdv_keys_plain<D>(Qh, K + hoff, V + hoff, dOh, LSE + (size_t)head * Lq,
+                           Dws + (size_t)head * Lq, dK + hoff, dV + hoff, wkey0, 16, klen, Lq,
+                           causal, diag, scale, scale_log2, lane);
+}
+
+inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+}  // namespace
+
+// Grids that fill two workgroups per CU; the fused f32 kernel, which splits the
+// query tiles of a key tile over workgroups, keeps the smaller ones at d <= 64
+// (whole backward, us, that : this: B8 H8 L1024 causal 207 : 175, B4 H16 L2048
+// 1489 : 1100, d = 32 798 : 640; but B2 H6 L1500 186 : 228, B1 H4 L8192 causal
+// 918 : 1056, B4 H8 Lq1024 Lk77 37 : 82).  d = 128 always: 354 -> 205 at B2 H8
+// L1024 causal, 3907 -> 2006 at B4 H16 L2048, against separate f32 kernels.
+bool use_split_bwd(const AttnProblem &p) {
+    const long BH = (long)p.B * p.H;
+    return p.d == 128 || (cdiv(p.Lq, 128) * BH >= 512 && cdiv(p.Lk, 64) * BH >= 512);
+}
+
+// d = 128: eight waves share a tile's split once the grid fills the chip with
+// them (dQ at B4 H16 L1024 causal 198 -> 130 us, dK/dV 295 -> 170), four below
+// (B2 H8 L1024 causal: dQ 105 -> 82, dK/dV 144 -> 123).
+hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float *K,
+                               const float *V, const float *O, const float *dO, const float *LSE,
+                               float *Dws, float *dQ, hipStream_t s) {
+    const int BH = p.B * p.H;
+    auto go = [&](auto kern, int rows, int nt) {
+        const int nqt = cdiv(p.Lq, rows);
+        const dim3 grid(nqt * BH);
+        const int ly = causal_rank_layer((const void *)kern, nt, grid.x, BH, p.causal);
+        kern<<<grid, dim3(nt), 0, s>>>(Q, K, V, O, dO, LSE, Dws, dQ, p.key_len, p.H, p.Lq, p.Lk,
+                                       p.causal, p.scale, p.scale * kLog2e, nqt, BH, ly,
+                                       padded_work_order(p));
+        return hipGetLastError();
+    };
+    switch (p.d) {
+    case 32: return go(attn_dq_f32x3<32, 2, 4, 32>, 128, 256);
+    case 64: return go(attn_dq_f32x3<64, 2, 4, 32>, 128, 256);
+    case 128:
+        return (long)cdiv(p.Lq, 128) * BH >= 256 ? go(attn_dq_f32x3<128, 1, 8, 32>, 128, 512)
+                                                 : go(attn_dq_f32x3<128, 1, 4, 32>, 64, 256);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_bwd_dkdv_f32x3(const AttnProblem &p, const float *Q, const float *K,
+                                 const float *V, const float *dO, const float *LSE,
+                                 const float *Dws, float *dK, float *dV, hipStream_t s) {
+    const int BH = p.B * p.H;
+    auto go = [&](auto kern, int rows, int nt) {
+        const int nkt = cdiv(p.Lk, rows);
+        const dim3 grid(nkt * BH);
+        const int ly = causal_rank_layer((const void *)kern, nt, grid.x, BH, p.causal);
+        kern<<<grid, dim3(nt), 0, s>>>(Q, K, V, dO, LSE, Dws, dK, dV, p.key_len, p.H, p.Lq, p.Lk,
+                                       p.causal, p.scale, p.scale * kLog2e, nkt, BH, ly,
+                                       padded_work_order(p));
+        return hipGetLastError();
+    };
+    switch (p.d) {
+    case 32: return go(attn_dkdv_f32x3<32, 4, 32>, 64, 256);
+    case 64: return go(attn_dkdv_f32x3<64, 4, 32>, 64, 256);
+    case 128:
+        return (long)cdiv(p.Lk, 128) * BH >= 256 ? go(attn_dkdv_f32x3<128, 8, 32>, 128, 512)
+                                                 : go(attn_dkdv_f32x3<128, 4, 32>, 64, 256);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace mg

@@ -33,9 +33,13 @@ struct AttnProblem {
 // ones to whichever CU frees up first.  Non-causal grids get 0.
 int causal_rank_layer(const void *kernel, int block, long grid, int BH, int causal);
 
-// Forward, strict f32: O, LSE from Q, K, V.
+// Forward, strict f32: O, LSE from Q, K, V.  The first runs on the bf16 matrix
+// cores, operands split into three bf16 parts, and hands small grids to the
+// second (f32 matrix cores, d <= 64).
 hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K,
                           const float *V, float *O, float *LSE, hipStream_t s);
+hipError_t launch_fwd_f32_keysplit(const AttnProblem &p, const float *Q, const float *K,
+                                   const float *V, float *O, float *LSE, hipStream_t s);
 // Forward, bf16 inputs/outputs, f32 accumulation.
 hipError_t launch_fwd_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
                            const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s);
@@ -59,9 +63,6 @@ hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const flo
                                  float *Dws, hipStream_t s);
 
 // Backward step 2: dK, dV with the key tile stationary.
-hipError_t launch_bwd_dkdv_f32(const AttnProblem &p, const float *Q, const float *K,
-                               const float *V, const float *dO, const float *LSE,
-                               const float *Dws, float *dK, float *dV, hipStream_t s);
 hipError_t launch_bwd_dkdv_bf16(const AttnProblem &p, const uint16_t *Q,
                                 const uint16_t *K, const uint16_t *V, const uint16_t *dO,
                                 const float *LSE, const float *Dws, uint16_t *dK,
@@ -94,9 +95,16 @@ hipError_t launch_bwd_dq_reduce_f32(const AttnProblem &p, const float *dQp, floa
                                     hipStream_t s);
 
 // Backward step 3: dQ with the query tile stationary.
-hipError_t launch_bwd_dq_f32(const AttnProblem &p, const float *Q, const float *K,
-                             const float *V, const float *dO, const float *LSE,
-                             const float *Dws, float *dQ, hipStream_t s);
+// Strict backward on the bf16 matrix cores, operands split into three bf16
+// parts: the dQ kernel computes D and writes it to Dws; it runs first.
+// use_split_bwd: where it is taken although the fused kernel could be.
+bool use_split_bwd(const AttnProblem &p);
+hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float *K,
+                               const float *V, const float *O, const float *dO,
+                               const float *LSE, float *Dws, float *dQ, hipStream_t s);
+hipError_t launch_bwd_dkdv_f32x3(const AttnProblem &p, const float *Q, const float *K,
+                                 const float *V, const float *dO, const float *LSE,
+                                 const float *Dws, float *dK, float *dV, hipStream_t s);
 // bf16: the dQ kernel also computes D_i = sum_k dO_ik O_ik for its rows
 // and writes it to Dws; it runs first, and the dK/dV kernel reads D from
 // Dws after it.

@@ -1,0 +1,90 @@
+"""GPU parity of the strict-f32 kernels that run on split bf16 operands, on
+grids large enough to reach every form (d <= 64 backward: 512 or more 128-row
+query tiles and 64-key tiles), and their results for operands that the split
+cannot carry: infinities, NaN, and finite values that round to an infinite
+bf16."""
+import numpy as np
+import pytest
+
+from gpu_util import oracle_reference, run_gpu, say, to_host
+from workloads import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+# Relative 2-norm of the error: a product of split operands is within 2^-22 of
+# the f32 one, sums of up to 200 terms round to about sqrt(200) 2^-24 = 8e-7;
+# twice that for the chain of two products.
+REL = 2e-6
+
+# (B, H, Lq, Lk, mode): rows and keys off the 16-, 32-, 64- and 128-row tiles
+LARGE = [
+    (2, 260, 33, 33, "causal"), (2, 256, 130, 65, "causal"), (2, 256, 65, 193, "causal"),
+    (4, 128, 97, 70, "padded"), (2, 260, 64, 64, "full"),
+]
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,H,Lq,Lk,mode", LARGE)
+def test_large_grids(gpu_lib, B, H, Lq, Lk, mode, d):
+    say("split operands B=%d H=%d Lq=%d Lk=%d d=%d %s" % (B, H, Lq, Lk, d, mode))
+    kl = [1 + (b * Lk) // (B - 1) if b < B - 1 else Lk for b in range(B)] if mode == "padded" \
+        else None
+    x = make_inputs(B, H, Lq, d, causal=mode == "causal", seed=Lq + Lk + d, key_len=kl, Lk=Lk)
+    got, ref = run_gpu(x), oracle_reference(x)
+    for n in ("O", "LSE", "dQ", "dK", "dV"):
+        fin = np.isfinite(ref[n])
+        assert np.array_equal(got[n][~fin], ref[n][~fin]), n
+        rel = np.linalg.norm(got[n][fin] - ref[n][fin]) / np.linalg.norm(ref[n][fin])
+        assert rel <= REL, (n, rel)
+
+
+def plain(Q, K, V, dO, scale):
+    """The equations in f64 torch, infinities and NaN carried as they come."""
+    import torch
+    Q, K, V, dO = (t.double() for t in (Q, K, V, dO))
+    S = scale * torch.matmul(Q, K.transpose(-1, -2).contiguous())
+    P = torch.softmax(S, dim=-1)
+    O = torch.matmul(P, V)
+    dP = torch.matmul(dO, V.transpose(-1, -2).contiguous())
+    dS = P * (dP - (dO * O).sum(-1, keepdim=True))
+    return {"O": O, "LSE": torch.logsumexp(S, -1), "dQ": scale * torch.matmul(dS, K),
+            "dK": scale * torch.matmul(dS.transpose(-1, -2).contiguous(), Q),
+            "dV": torch.matmul(P.transpose(-1, -2).contiguous(), dO)}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what,value", [("V", np.inf), ("V", -np.inf), ("V", np.nan),
+                                        ("dO", np.inf), ("dO", 3.4e38), ("V", 3.4e38),
+                                        ("Q", np.nan), ("K", np.nan)])
+def test_values_the_split_cannot_carry(gpu_lib, what, value, d):
+    """One such value in one head: entries are finite, infinite or NaN where
+    f32 arithmetic has them so, and the finite ones are right."""
+    import torch
+    import paper_2608_01563_amd as mg
+    say("split operands %s = %s d=%d" % (what, value, d))
+    H, L = 520, 70
+    x = make_inputs(1, H, L, d, causal=False, seed=d, qkv_std=0.3)
+    t = {n: torch.from_numpy(getattr(x, n).copy()) for n in ("Q", "K", "V", "dO")}
+    t[what][0, 1, 37, 5] = value
+    Q, K, V, dO = (t[n].cuda() for n in ("Q", "K", "V", "dO"))
+    O, LSE = mg.attention_forward(Q, K, V, causal=False, scale=x.scale)
+    dQ, dK, dV = mg.attention_backward(Q, K, V, O, LSE, dO, causal=False, scale=x.scale)
+    got = {n: to_host(v)[0, :3] for n, v in (("O", O), ("LSE", LSE), ("dQ", dQ), ("dK", dK),
+                                             ("dV", dV))}
+    ref = plain(*(t[n][:, :3] for n in ("Q", "K", "V", "dO")), x.scale)
+    for n, g in got.items():
+        r = ref[n][0].numpy()
+        with np.errstate(over="ignore"):
+            r = r.astype(np.float32).astype(np.float64)   # overflows as f32 results do
+        if what == "Q" or what == "K":
+            if n == "LSE":
+                continue   # a NaN row's LSE is reported as -inf
+        if np.isnan(value) or np.isinf(value) or n == "O" or n == "dV":
+            assert np.array_equal(np.isfinite(g), np.isfinite(r)), n
+        # heads 0 and 2 hold ordinary values
+        for h in (0, 2):
+            rel = np.linalg.norm(g[h] - r[h]) / np.linalg.norm(r[h])
+            assert rel <= REL, (n, h, rel)
+        fin = np.isfinite(g[1]) & np.isfinite(r[1])
+        if fin.any() and np.abs(value) != 3.4e38:
+            assert np.max(np.abs(g[1][fin] - r[1][fin])) <= 1e-4 * max(1.0, np.max(np.abs(r[1][fin]))), n
