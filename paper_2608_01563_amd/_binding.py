@@ -98,6 +98,8 @@ def _declare(lib):
 def load_library(path=LIB_PATH):
     """Load libmg.so (after torch, so both share one HIP runtime)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             import torch  # noqa: F401  (brings in the HIP runtime the library binds to)
@@ -123,8 +125,10 @@ def _contract_id(contract):
 def _stream_handle(stream):
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        # the current stream's handle without building a Stream object
+        # (0.4 against 3.1 us per call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _alloc_stream(stream):
@@ -148,7 +152,7 @@ def _empty_bytes(nbytes, device, stream):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check_tensors(contract, shape, named):
@@ -157,6 +161,8 @@ def _check_tensors(contract, shape, named):
     import torch
     want = torch.bfloat16 if contract == FAST_BF16 else torch.float32
     for name, t in named:
+        if t.is_cuda and t.dtype is want and t.shape == shape and t.is_contiguous():
+            continue
         if not t.is_cuda:
             raise ValueError("%s must be a GPU tensor" % name)
         if t.dtype != want:
@@ -173,14 +179,15 @@ def _cross_shapes(Q, K):
     if Q.dim() != 4 or K.dim() != 4:
         raise ValueError("Q must be [B,H,Lq,d] and K [B,H,Lk,d]")
     B, H, Lq, d = Q.shape
-    if tuple(K.shape) != (B, H, K.shape[2], d):
+    kb, kh, Lk, kd = K.shape
+    if (kb, kh, kd) != (B, H, d):
         raise ValueError("K has shape %s, expected [%d,%d,Lk,%d]" % (tuple(K.shape), B, H, d))
-    return B, H, Lq, K.shape[2], d
+    return B, H, Lq, Lk, d
 
 
 def _check_lse(LSE, shape):
     import torch
-    if not LSE.is_cuda or LSE.dtype != torch.float32 or tuple(LSE.shape) != tuple(shape[:3]) \
+    if not LSE.is_cuda or LSE.dtype != torch.float32 or LSE.shape != shape[:3] \
             or not LSE.is_contiguous():
         raise ValueError("LSE must be a contiguous float32 GPU tensor of shape %s"
                          % (tuple(shape[:3]),))
@@ -190,7 +197,7 @@ def _check_key_len(key_len, B):
     import torch
     if key_len is None:
         return
-    if not key_len.is_cuda or key_len.dtype != torch.int32 or tuple(key_len.shape) != (B,) \
+    if not key_len.is_cuda or key_len.dtype != torch.int32 or key_len.shape != (B,) \
             or not key_len.is_contiguous():
         raise ValueError("key_len must be a contiguous int32 GPU tensor of shape [%d]" % B)
 
@@ -230,9 +237,9 @@ def mg_attn_bwd(Q, K, V, O, LSE, dO, dQ, dK, dV, key_len=None, *, causal, scale,
                                 ("dQ", dQ), ("dK", dK), ("dV", dV)))
     _check_lse(LSE, Q.shape)
     _check_key_len(key_len, B)
-    need = mg_attn_bwd_workspace_bytes(B, H, L, d, causal, c)
     if workspace is None:
-        workspace = _empty_bytes(need, Q.device, stream)
+        workspace = _empty_bytes(mg_attn_bwd_workspace_bytes(B, H, L, d, causal, c), Q.device,
+                                 stream)
     nbytes = workspace.numel() * workspace.element_size()
     _check(lib.mg_attn_bwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO), _ptr(dQ),
                            _ptr(dK), _ptr(dV), _ptr(key_len), B, H, L, d, int(bool(causal)),
@@ -273,9 +280,9 @@ def mg_attn_bwd_cross(Q, K, V, O, LSE, dO, dQ, dK, dV, key_len=None, *, causal, 
     _check_tensors(c, K.shape, (("K", K), ("V", V), ("dK", dK), ("dV", dV)))
     _check_lse(LSE, Q.shape)
     _check_key_len(key_len, B)
-    need = mg_attn_bwd_cross_workspace_bytes(B, H, Lq, Lk, d, causal, c)
     if workspace is None:
-        workspace = _empty_bytes(need, Q.device, stream)
+        workspace = _empty_bytes(mg_attn_bwd_cross_workspace_bytes(B, H, Lq, Lk, d, causal, c),
+                                 Q.device, stream)
     nbytes = workspace.numel() * workspace.element_size()
     _check(lib.mg_attn_bwd_cross(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO),
                                  _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(key_len), B, H, Lq, Lk, d,
@@ -320,7 +327,7 @@ def _check_f32(named):
     for name, t, want in named:
         if not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous():
             raise ValueError("%s must be a contiguous float32 GPU tensor" % name)
-        if tuple(t.shape) != tuple(want):
+        if t.shape != tuple(want):
             raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(want)))
 
 
@@ -341,9 +348,10 @@ def mg_conv2d_bwd_data(dY, W, dX, *, stride=(1, 1), pad=(0, 0), contract=STRICT_
     P, Q = conv_out_hw(shape)
     _check_f32((("dY", dY, (shape.N, P, Q, shape.K)), ("W", W, tuple(W.shape)),
                 ("dX", dX, tuple(dX.shape))))
-    need = mg_conv2d_bwd_data_workspace_bytes(dX.shape, W.shape, stride, pad, contract)
-    if workspace is None and need > 0:
-        workspace = _empty_bytes(need, dX.device, stream)
+    if workspace is None:
+        need = mg_conv2d_bwd_data_workspace_bytes(dX.shape, W.shape, stride, pad, contract)
+        if need > 0:
+            workspace = _empty_bytes(need, dX.device, stream)
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.mg_conv2d_bwd_data(_ptr(dY), _ptr(W), _ptr(dX), ctypes.byref(shape),
                                   _contract_id(contract), _ptr(workspace), nbytes,
@@ -366,9 +374,10 @@ def mg_conv2d_bwd_filter(X, dY, dW, *, stride=(1, 1), pad=(0, 0), contract=STRIC
     P, Q = conv_out_hw(shape)
     _check_f32((("X", X, tuple(X.shape)), ("dY", dY, (shape.N, P, Q, shape.K)),
                 ("dW", dW, tuple(dW.shape))))
-    need = mg_conv2d_bwd_filter_workspace_bytes(X.shape, dW.shape, stride, pad, contract)
-    if workspace is None and need > 0:
-        workspace = _empty_bytes(need, X.device, stream)
+    if workspace is None:
+        need = mg_conv2d_bwd_filter_workspace_bytes(X.shape, dW.shape, stride, pad, contract)
+        if need > 0:
+            workspace = _empty_bytes(need, X.device, stream)
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.mg_conv2d_bwd_filter(_ptr(X), _ptr(dY), _ptr(dW), ctypes.byref(shape),
                                     _contract_id(contract), _ptr(workspace), nbytes,
@@ -391,9 +400,10 @@ def mg_conv2d_bwd(X, W, dY, dX, dW, *, stride=(1, 1), pad=(0, 0), contract=STRIC
     _check_f32((("X", X, tuple(X.shape)), ("W", W, tuple(W.shape)),
                 ("dY", dY, (shape.N, P, Q, shape.K)), ("dX", dX, tuple(X.shape)),
                 ("dW", dW, tuple(W.shape))))
-    need = mg_conv2d_bwd_workspace_bytes(X.shape, W.shape, stride, pad, contract)
-    if workspace is None and need > 0:
-        workspace = _empty_bytes(need, X.device, stream)
+    if workspace is None:
+        need = mg_conv2d_bwd_workspace_bytes(X.shape, W.shape, stride, pad, contract)
+        if need > 0:
+            workspace = _empty_bytes(need, X.device, stream)
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.mg_conv2d_bwd(_ptr(X), _ptr(W), _ptr(dY), _ptr(dX), _ptr(dW),
                              ctypes.byref(shape), _contract_id(contract), _ptr(workspace),
