@@ -17,8 +17,8 @@
 // rows it holds the rows of the accumulator registers it already owns, so
 // P and dS become the B operand without leaving registers, and the LDS
 // operand (a column of the row-major tile) comes from transpose reads.
-//   16x16x32 (dK/dV): rows 32t + 16*(e/4) + 4g + e%4, g = lane/16
-//   32x32x16 (forward, dQ): rows 16t + 8*(e/4) + 4h + e%4, h = lane/32
+//   16x16x32 (dK/dV, dQ): rows 32t + 16*(e/4) + 4g + e%4, g = lane/16
+//   32x32x16 (forward): rows 16t + 8*(e/4) + 4h + e%4, h = lane/32
 #include <type_traits>
 
 #include "device_common.h"
@@ -638,8 +638,14 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
 }
 
 // ------------------------------------------------------------ backward: dQ
-// Query-stationary, 32 queries per wave on 32x32x16 products (as the forward):
-// S^T = K Q^T and dP^T = V dO^T from row-major K and V tiles, then
+// Query-stationary, 32 queries per wave in two 16-query blocks on 16x16x32
+// products (each K, V or K^T fragment read from LDS feeds both): on random
+// data the chip clocks down under its power limit, and this shape sustains
+// 2.03 PFLOP/s of bf16 where 32x32x16 sustains 1.81.  Against the 32x32x16 form
+// of the same loop: 199 -> 184 us at B2 H16 L4096 d128 causal, 183 -> 169 at
+// B4 H16 L2048 d128, 105 -> 98 at d64, 65 -> 61 at d32.  (The d = 128 forward
+// gained 3 % on the largest grid and lost 9 % on small ones, so it keeps
+// 32x32x16.)  S^T = K Q^T and dP^T = V dO^T from row-major K and V tiles, then
 // dQ^T += K^T dS^T with dS^T straight from registers and K^T from transpose
 // reads of the row-major K tile.  KS keys per streamed tile; K and V tiles
 // are double-buffered in LDS and arrive by direct-to-LDS row loads, so the
@@ -655,12 +661,12 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
                   float *__restrict__ Dws, uint16_t *__restrict__ dQ,
                   const int32_t *__restrict__ key_len, int H, int Lq, int Lk,
                   int causal, float scale, float scale_log2, int n_qtiles, int BH, int layer) {
-    constexpr int NS = D / 16;
-    constexpr int NCB = D / 32;
-    constexpr int NKB = KS / 32;
+    constexpr int QB = 2;
+    constexpr int NS = D / 32;
+    constexpr int NC = D / 16;
     // K and V tiles are double-buffered and arrive by 16-byte direct-to-LDS
     // loads: the next tile is fetched during the whole current iteration.
-    using Tile = Bf16Tile<KS, D, kWaves, 32, 2, 3, 1>;
+    using Tile = Bf16Tile<KS, D, kWaves, 32, 1, 3, 1>;
     constexpr int BLK = Tile::kBlock;
     __shared__ __attribute__((aligned(16))) uint16_t Kr0[Tile::kSize], Kr1[Tile::kSize];
     __shared__ __attribute__((aligned(16))) uint16_t Vr0[Tile::kSize], Vr1[Tile::kSize];
@@ -676,53 +682,55 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 31;
-    const int h = lane >> 5;
-    const int jr = (lane & 15) >> 2, jc = 4 * (lane & 3);
+    const int il = lane & 15;
+    const int g = lane >> 4;
+    const int jr = il >> 2, jc = 4 * (il & 3);
     const int q0 = qt * kFwdRows;
-    const int qi = q0 + 32 * w + c;
+    const int qi = q0 + 32 * w + il;   // query of block 0; block qb: + 16 qb
 
     const int klen = key_limit(key_len, b, Lk);
     const int kend = causal ? min(klen, q0 + kFwdRows + diag) : klen;
     const int ntiles = (kend + KS - 1) / KS;
 
-    bf16x8 qreg[NS], oreg[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const size_t off = qoff + (size_t)qi * D + 16 * s + 8 * h;
-        qreg[s] = (qi < Lq) ? load_bf16x8(Q + off) : __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-        oreg[s] = (qi < Lq) ? load_bf16x8(dO + off) : __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-    }
     // Rows past Lq: Q = dO = 0 and LSE = D = 0, so their dS is exactly 0.
-    const float lse2 = (qi < Lq) ? LSE[(size_t)head * Lq + qi] * kLog2e : 0.f;
     // D_i = sum_d dO[i][d] O[i][d], in f32 from the bf16 values: this lane
-    // holds the d values of oreg, its partner (lane ^ 32) the other half of
-    // the row.  The row's D goes to the workspace for the dK/dV kernel,
-    // which runs after this one.
-    float Di = 0.f;
-    if (qi < Lq) {
+    // holds the d values of oreg, the other lane groups the rest of the row.
+    // The row's D goes to the workspace for the dK/dV kernel, which runs
+    // after this one.
+    bf16x8 qreg[NS][QB], oreg[NS][QB];
+    float lse2[QB], Di[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int q = qi + 16 * qb;
+        lse2[qb] = (q < Lq) ? LSE[(size_t)head * Lq + q] * kLog2e : 0.f;
+        float dsum = 0.f;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const bf16x8 o8 = load_bf16x8(O + qoff + (size_t)qi * D + 16 * s + 8 * h);
+            const size_t off = qoff + (size_t)q * D + 32 * s + 8 * g;
+            qreg[s][qb] = (q < Lq) ? load_bf16x8(Q + off) : __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+            oreg[s][qb] = (q < Lq) ? load_bf16x8(dO + off) : __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+            if (q < Lq) {
+                const bf16x8 o8 = load_bf16x8(O + off);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) Di = fmaf((float)o8[e], (float)oreg[s][e], Di);
+                for (int e = 0; e < 8; ++e) dsum = fmaf((float)o8[e], (float)oreg[s][qb][e], dsum);
+            }
         }
+        Di[qb] = sum_over_groups(dsum);
+        if (q < Lq && g == 0) Dws[(size_t)head * Lq + q] = Di[qb];
     }
-    Di += xor_lanes(Di, 32);
-    if (qi < Lq && h == 0) Dws[(size_t)head * Lq + qi] = Di;
 
-    f32x16 dqacc[NCB];   // dQ^T[32cb + 8a + 4h + r][qi]
+    f32x4 dqacc[NC][QB];   // dQ^T[16c + 4g + r][qi + 16qb]
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) dqacc[cb] = zero16();
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] = zero4();
 
     Tile tile;
     tile.init(lane);
-    // Lane bases of the tile reads.  K, V rows: row 32kb + c, chunk
-    // 2(s%2) + h of block s/2 (kc[s%2]); K^T: rows 32kb + 16t + 4h + jr (+8)
-    // of column 32cb + 16(c/16) + jc (klo, khi).
-    const int kc[2] = {Tile::at(c, 8 * h), Tile::at(c, 16 + 8 * h)};
-    const int klo = Tile::at(4 * h + jr, 16 * (c >> 4) + jc);
-    const int khi = Tile::at(4 * h + jr + 8, 16 * (c >> 4) + jc);
+    // Lane bases of the tile reads.  K, V rows: row 16kb + il, columns
+    // 32s + 8g; K^T: rows 32t + 4g + jr (+16) of columns 16c + jc.
+    const int ka = Tile::at(il, 8 * g);
+    const int ta[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
     using Buf = uint16_t[Tile::kSize];
     auto fetch = [&](int t, Buf &Kn, Buf &Vn) {
         tile.issue(Kn, K + hoff, t * KS, Lk, w);
@@ -733,48 +741,64 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
         if (kt + 1 < ntiles) fetch(kt + 1, Kn, Vn);   // freed by the last barrier
         const bool full = (kt + 1) * KS <= klen &&
                           (!causal || (kt + 1) * KS - 1 <= q0 + diag);
-        const int j0 = kt * KS + 4 * h;
-        const int thr = causal ? min(klen - j0, qi + diag - j0 + 1) : klen - j0;
+        const int j0 = kt * KS + 4 * g;
 
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
+        for (int t = 0; t < KS / 32; ++t) {   // 32 keys at a time
             // S^T = K Q^T; dP^T - D = V dO^T accumulated onto -D
-            f32x16 sacc = zero16(), pacc;
+            f32x4 sacc[2][QB], pacc[2][QB];   // [16-key block][query block]
 #pragma unroll
-            for (int v = 0; v < 16; ++v) pacc[v] = -Di;
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int o = kc[s & 1] + (s >> 1) * BLK + 32 * 32 * kb;
-                sacc = mfma32x32x16bf16(load_bf16x8(Kc + o), qreg[s], sacc);
-                pacc = mfma32x32x16bf16(load_bf16x8(Vc + o), oreg[s], pacc);
-            }
-            // eight operand reads ahead of the products (d = 128: dQ 205-207 -> 203 us)
-            if constexpr (D == 128) sched_reads_ahead<2 * NS, 2 * NS, 8, 2, 2, 2>();
+                for (int qb = 0; qb < QB; ++qb) {
+                    sacc[kb][qb] = zero4();
+                    pacc[kb][qb] = f32x4{-Di[qb], -Di[qb], -Di[qb], -Di[qb]};
+                }
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    const int o = ka + s * BLK + 32 * (32 * t + 16 * kb);
+                    const bf16x8 k8 = load_bf16x8(Kc + o), v8 = load_bf16x8(Vc + o);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) {
+                        sacc[kb][qb] = mfma16x16x32bf16(k8, qreg[s][qb], sacc[kb][qb]);
+                        pacc[kb][qb] = mfma16x16x32bf16(v8, oreg[s][qb], pacc[kb][qb]);
+                    }
+                }
+            // eight operand reads ahead of the products
+            if constexpr (D == 128) sched_reads_ahead<4 * NS, 8 * NS, 8, 2, 4, 2>();
             // dS^T = P^T (dP^T - D), P^T = exp2(S^T * scale*log2e - LSE*log2e);
             // the mask only in tiles that cross the diagonal or the key length
             auto softmax = [&](auto masked) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float p = exp2_fast(fmaf(sacc[v], scale_log2, -lse2));
-                    if (masked && 32 * kb + 8 * (v >> 2) + (v & 3) >= thr) p = 0.f;
-                    pacc[v] *= p;
+                for (int qb = 0; qb < QB; ++qb) {
+                    const int thr = causal ? min(klen - j0, qi + 16 * qb + diag - j0 + 1) : klen - j0;
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            float p = exp2_fast(fmaf(sacc[kb][qb][r], scale_log2, -lse2[qb]));
+                            if (masked && 32 * t + 16 * kb + r >= thr) p = 0.f;
+                            pacc[kb][qb][r] *= p;
+                        }
                 }
             };
             if (full)
                 softmax(std::false_type{});
             else
                 softmax(std::true_type{});
+            bf16x8 sb[QB];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const bf16x8 sb = pack_bf16_half(pacc, t);
-                const int r0 = 32 * (32 * kb + 16 * t);
+            for (int qb = 0; qb < QB; ++qb) sb[qb] = pack_bf16(pacc[0][qb], pacc[1][qb]);
 #pragma unroll
-                for (int cb2 = 0; cb2 < NCB; ++cb2)
-                    dqacc[cb2] = mfma32x32x16bf16(
-                        load_tr_pair_at(Kc + klo + cb2 * BLK + r0, Kc + khi + cb2 * BLK + r0),
-                        sb, dqacc[cb2]);
+            for (int c = 0; c < NC; ++c) {
+                const int o = ta[c & 1] + (c >> 1) * BLK + 32 * 32 * t;
+                const bf16x8 a = load_tr_pair_at(Kc + o, Kc + o + 32 * 16);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] = mfma16x16x32bf16(a, sb[qb], dqacc[c][qb]);
             }
-            if constexpr (D == 128) sched_reads_ahead<4 * NCB, 2 * NCB, 8, 2, 1, 3>();
+            if constexpr (D == 128) sched_reads_ahead<2 * NC, 2 * NC, 8, 2, 2, 3>();
         }
         wait_vmcnt<0>();   // next K/V tile landed
         __syncthreads();   // it is visible; buffers (Kc, Vc) are free
@@ -787,15 +811,14 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
         if (kt + 1 < ntiles) step(kt + 1, Kr1, Vr1, Kr0, Vr0);
     }
 
-    if (qi < Lq) {
-        uint16_t *dqrow = dQ + qoff + (size_t)qi * D;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
+    for (int qb = 0; qb < QB; ++qb) {
+        const int q = qi + 16 * qb;
+        if (q < Lq) {
+            uint16_t *dqrow = dQ + qoff + (size_t)q * D;
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-                store_bf16x4(dqrow + 32 * cb + 8 * a + 4 * h,
-                             f32x4{dqacc[cb][4 * a], dqacc[cb][4 * a + 1], dqacc[cb][4 * a + 2],
-                                   dqacc[cb][4 * a + 3]} * scale);
+            for (int c = 0; c < NC; ++c) store_bf16x4(dqrow + 16 * c + 4 * g, dqacc[c][qb] * scale);
+        }
     }
 }
 
