@@ -1,5 +1,6 @@
 // conv_f32.hip -- data and filter gradients of a 2-D convolution as
-// implicit GEMMs on the f32 matrix cores (v_mfma_f32_16x16x4_f32).
+// implicit GEMMs, their f32 operands split into three bf16 parts
+// (tiles_split.h) for v_mfma_f32_16x16x32_bf16.
 //
 // Neither derivative materialises an unfolded (im2col) matrix: each
 // workgroup gathers the operand rows it needs straight from the
@@ -14,11 +15,16 @@
 //       fastest, W[j][c] = W[k][r][s][c], dYg[m][j] = dY at the output
 //       position the tap reads, 0 outside dY.
 //
-// Both run 64x64 output tiles on 256 threads: each of the four waves owns a
-// 32x32 quarter as 2x2 blocks of 16x16 accumulators, and the reduction
-// advances BK (16) at a time through double-buffered LDS tiles (one barrier
-// per step; the global loads of steps t+1 and t+2 are in flight, in two
-// register sets, during the products of step t).  Operands reach LDS
+// Both run 64x64 output tiles on 512 threads: each of the eight waves owns a
+// 32x16 part as two blocks of 16x16 accumulators, and the reduction advances
+// BK (32) at a time through double-buffered LDS tiles (one barrier per step;
+// the global loads of steps t+1 and t+2 are in flight, in two register sets,
+// during the products of step t; more sets gained nothing).  A step of the
+// small grids is a chain of staging, barrier, LDS reads and products with one
+// workgroup per CU, so eight waves with a quarter of the f32 form's work per
+// step each beat four (N4 14x14 1024 -> 256 1x1, data gradient: f32 matrix
+// cores 13.1 us, split 11.7 with four waves, 9.9 with eight; N32 28x28
+// 512 3x3: 1113, 973, 895 us, both derivatives 2562 -> 2000).  Operands reach LDS
 // through raw buffer loads whose offset is pushed past the end of the buffer
 // for a padded or out-of-range element, which reads as zero: the padding of
 // the convolution and the tails of every dimension become zeros without a
@@ -28,28 +34,16 @@
 #include <vector>
 
 #include "../device_common.h"
+#include "../tiles_split.h"
 #include "conv_launch.h"
 
 namespace mg {
 namespace {
 
-#ifndef MG_CONV_BK
-#define MG_CONV_BK 16
-#endif
-constexpr int BM = 64;          // output rows per workgroup (columns: 64 or 128, TN)
-constexpr int BK = MG_CONV_BK;  // reduction step (16 or 32)
-constexpr int NSUB = BK / 16;   // staged rows per thread and operand in one step
-constexpr int NT = 256;         // four waves
-constexpr int LDR = 64 + 16;    // reduction-major 64-wide tiles: rows 80 floats (16 banks)
-                                // apart; 128-wide ones use 144 (also 16 banks)
-constexpr int LDM = BK + 4;     // the data gradient's pixel-major A tile: 20 (or 36)
-                                // floats per row, conflict-free for the operand reads
-static_assert(BK == 16 || BK == 32, "reduction step");
-// Waves per SIMD the register allocator must allow (measured best of 4, 6
-// and 8 at a 16-deep step; 4 also fits 40 KB workgroups at a 32-deep one).
-#ifndef MG_CONV_OCC
-#define MG_CONV_OCC 4
-#endif
+constexpr int BM = 64, BN = 64; // output tile of a workgroup
+constexpr int BK = 32;          // reduction step
+constexpr int NP = 2;           // register sets: steps of loads in flight
+constexpr int NT = 512;         // eight waves, each a 32 x 16 part of the tile
 constexpr int kOOB = 0x7ffffff0;   // byte offset past every buffer: reads as zero
 
 __device__ __forceinline__ int fdiv(int n, FastDiv f) {
@@ -76,52 +70,59 @@ __device__ __forceinline__ f32x4 load_vec(__amdgpu_buffer_rsrc_t r, const int (&
     return v;
 }
 
-// 2 x NJ blocks of v_mfma_f32_16x16x4_f32 over one reduction step.
-// a(kk, i) and b(kk, jb) return this lane's operand: A[row 16i + l%16][red 4kk + l/16]
-// and B[red 4kk + l/16][col 16jb + l%16] of the wave's 32 x 16NJ part of the tile.
-template <int NJ, typename FA, typename FB>
-__device__ __forceinline__ void mma_step(f32x4 (&acc)[2][NJ], FA &&a, FB &&b) {
+// Staged B columns of one thread: with 16-byte chunks (VB == 4), one chunk at
+// columns 4*col; with 4-byte loads (VB == 1), four floats at columns
+// col + 16e.
+template <int VB>
+struct BCols {
+    static constexpr int NE = VB == 4 ? 1 : 4;   // separately addressed elements
+    __device__ static int col(int c, int e) { return VB == 4 ? 4 * c : c + 16 * e; }
+};
+
+// LDS tiles: three bf16 planes each.  RedTile is reduction-major ([32
+// reduction rows][64 columns]) and read by 4-row transpose reads, so a lane
+// group g holds reduction rows 4g..4g+3 and 16+4g..+3; PixTile is the data
+// gradient's pixel-major A ([64 pixels][32]), whose reduction columns are
+// stored in that order (column 16u + 4g + x at 8g + 4u + x) for 16-byte reads.
+using RedTile = Bf16Tile<BK, BN, 1, 32, 1, 3, 1>;
+using PixTile = Bf16Tile<BM, BK, 1, 32, 1, 3, 1>;
+static_assert(RedTile::kSize == PixTile::kSize, "one plane size");
+constexpr int kTile = 3 * RedTile::kSize;
+struct ConvLds {
+    uint16_t A[2][kTile], B[2][kTile];   // double-buffered operands
+};
+
+// Four f32 into the three planes at u16 offset o (8-byte stores), or at four
+// separate offsets.
+__device__ __forceinline__ void store_split4(uint16_t *t, int o, f32x4 v) {
+    const float x[4] = {v[0], v[1], v[2], v[3]};
+    uint32_t p[3][2];
+    split_pairs<2>(x, p);
 #pragma unroll
-    for (int kk = 0; kk < BK / 4; ++kk) {
-        const float a0 = a(kk, 0), a1 = a(kk, 1);
-        float bj[NJ];
+    for (int k = 0; k < 3; ++k)
+        *reinterpret_cast<uint64_t *>(t + k * RedTile::kSize + o) =
+            (uint64_t)p[k][0] | ((uint64_t)p[k][1] << 32);
+}
+__device__ __forceinline__ void store_split4(uint16_t *t, const int (&o)[4], f32x4 v) {
+    const float x[4] = {v[0], v[1], v[2], v[3]};
+    uint32_t p[3][2];
+    split_pairs<2>(x, p);
 #pragma unroll
-        for (int jb = 0; jb < NJ; ++jb) bj[jb] = b(kk, jb);
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int jb = 0; jb < NJ; ++jb) {
-            acc[0][jb] = mfma16x16x4(a0, bj[jb], acc[0][jb]);
-            acc[1][jb] = mfma16x16x4(a1, bj[jb], acc[1][jb]);
-        }
-    }
+        for (int e = 0; e < 4; ++e)
+            t[k * RedTile::kSize + o[e]] = (uint16_t)(p[k][e >> 1] >> (16 * (e & 1)));
 }
 
-// Staged B columns of one thread: with 16-byte chunks (VB == 4), TN/64
-// chunks at columns 4*col + 64v; with 4-byte loads (VB == 1, TN == 64), four
-// floats at columns col + 16e.
-template <int VB, int TN>
-struct BCols {
-    static_assert(TN == 64 || (TN == 128 && VB == 4), "tile width");
-    static constexpr int NV = VB == 4 ? TN / 64 : 1;   // f32x4 registers per row
-    static constexpr int NE = VB == 4 ? TN / 64 : 4;   // separately addressed elements
-    __device__ static int col(int c, int e) { return VB == 4 ? 4 * c + 64 * e : c + 16 * e; }
-};
-
-// LDS of one workgroup: the two derivatives' double-buffered tiles share it.
-template <int TN>
-struct WgradLds {
-    float As[2][BK][LDR];      // dY tile, [m][k]
-    float Bs[2][BK][TN + 16];  // X gather, [m][j]
-};
-template <int TN>
-struct DgradLds {
-    float As[2][BM][LDM];      // dY gather, [m][j]
-    float Bs[2][BK][TN + 16];  // W rows, [j][c]
-};
-template <int TN>
-union __attribute__((aligned(16))) ConvLds {
-    WgradLds<TN> w;
-    DgradLds<TN> d;
-};
+// acc[i] += A[16i + .][:] B[:][.] over one 32-deep step, six
+// products of bf16 parts each.
+__device__ __forceinline__ void mma_step(f32x4 (&acc)[2], const Split8 (&a)[2], const Split8 &b) {
+    constexpr int I[6] = {2, 1, 1, 0, 0, 0}, J[6] = {0, 1, 0, 2, 1, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] = mfma16x16x32bf16(a[i].p[I[t]], b.p[J[t]], acc[i]);
+}
 
 // Work of one filter-gradient launch: grid (k tile, j tile, split), split fastest.
 struct WgradJob {
@@ -150,16 +151,30 @@ struct DgradJobs {
     int n;
 };
 
+// An output whose split sum is not finite: the same terms in plain f32.
+__device__ __forceinline__ float wgrad_plain(const WgradJob &job, const ConvProblem &p,
+                                          const ConvDivs &dv, int k, int j, int m0, int m1) {
+    const int rs = fdiv(j, dv.C), c = j - rs * p.C;
+    const int r = fdiv(rs, dv.S), s = rs - r * p.S;
+    float sum = 0.f;
+    for (int m = m0; m < m1; ++m) {
+        const int n = fdiv(m, dv.PQ), pq = m - n * p.P * p.Q;
+        const int pp = fdiv(pq, dv.Q), qq = pq - pp * p.Q;
+        const int h = pp * p.sh - p.ph + r, w = qq * p.sw - p.pw + s;
+        if ((unsigned)h >= (unsigned)p.H || (unsigned)w >= (unsigned)p.W) continue;   // padding
+        sum = fmaf(job.dY[(size_t)m * p.K + k],
+                   job.X[(((size_t)n * p.H + h) * p.W + w) * p.C + c], sum);
+    }
+    return sum;
+}
+
 // ------------------------------------------------------- filter gradient --
 // Block `bid` of the job: split `split` of `nsplit` sums the reduction steps
 // [st0, st1) of the N*P*Q positions for one 64x64 tile of dW.
-template <int VA, int VB, int TN>
-__device__ __forceinline__ void wgrad_tile(int bid, WgradLds<TN> &L, const WgradJob &job,
+template <int VA, int VB>
+__device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &job,
                                            const ConvProblem &p, const ConvDivs &dv) {
-    using BC = BCols<VB, TN>;
-    constexpr int NJ = TN / 32;   // 16-column blocks per wave
-    auto &As = L.As;
-    auto &Bs = L.Bs;
+    using BC = BCols<VB>;
     const float *__restrict__ X = job.X;
     const float *__restrict__ dY = job.dY;
     float *__restrict__ out = job.out;
@@ -171,7 +186,7 @@ __device__ __forceinline__ void wgrad_tile(int bid, WgradLds<TN> &L, const Wgrad
     const int split = bid % nsplit;
     bid /= nsplit;
     const int k0 = (bid / tiles_j) * BM;
-    const int j0 = (bid % tiles_j) * TN;
+    const int j0 = (bid % tiles_j) * BN;
     const int st0 = (int)((long)nsteps * split / nsplit);
     const int st1 = (int)((long)nsteps * (split + 1) / nsplit);
 
@@ -206,107 +221,109 @@ __device__ __forceinline__ void wgrad_tile(int bid, WgradLds<TN> &L, const Wgrad
         bok[e] = j < RSC;
     }
 
-    // Step st stages reduction rows st*BK + lrow + 16u, u < NSUB.
-    using Regs = f32x4[NSUB][1 + BC::NV];   // [u][0]: A (dY), [u][1 + v]: B (X)
+    // Step st stages reduction row st*BK + lrow.
+    using Regs = f32x4[2];   // A (dY), B (X)
     auto load = [&](int st, Regs &rg) {
+        const int m = st * BK + lrow;
+        const bool mok = m < M;
+        const int n = fdiv(m, dv.PQ), pq = m - n * PQ;
+        const int pp = fdiv(pq, dv.Q), qq = pq - pp * p.Q;
+        const int hb = pp * p.sh - p.ph, wb = qq * p.sw - p.pw;
+        const int xbase = ((n * p.H + hb) * p.W + wb) * p.C;
+        int oa[4], ob[BC::NE];
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-            const int m = st * BK + lrow + 16 * u;
-            const bool mok = m < M;
-            const int n = fdiv(m, dv.PQ), pq = m - n * PQ;
-            const int pp = fdiv(pq, dv.Q), qq = pq - pp * p.Q;
-            const int hb = pp * p.sh - p.ph, wb = qq * p.sw - p.pw;
-            const int xbase = ((n * p.H + hb) * p.W + wb) * p.C;
-            int oa[4], ob[BC::NE];
+        for (int e = 0; e < 4; ++e) {
+            oa[e] = (mok && kok[e]) ? m * (4 * p.K) + ka4[e] : kOOB;
+            if (VA == 4) break;
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                oa[e] = (mok && kok[e]) ? m * (4 * p.K) + ka4[e] : kOOB;
-                if (VA == 4) break;
-            }
+        for (int e = 0; e < BC::NE; ++e) {
+            const int h = hb + br[e], wi = wb + bsx[e];
+            const bool ok = mok && bok[e] && (unsigned)h < (unsigned)p.H &&
+                            (unsigned)wi < (unsigned)p.W;
+            ob[e] = ok ? xbase * 4 + boff[e] : kOOB;
+        }
+        rg[0] = load_vec<VA>(rdy, oa);
+        if (VB == 4) {
+            rg[1] = buffer_load_f32x4(rx, ob[0]);
+        } else {
 #pragma unroll
-            for (int e = 0; e < BC::NE; ++e) {
-                const int h = hb + br[e], wi = wb + bsx[e];
-                const bool ok = mok && bok[e] && (unsigned)h < (unsigned)p.H &&
-                                (unsigned)wi < (unsigned)p.W;
-                ob[e] = ok ? xbase * 4 + boff[e] : kOOB;
-            }
-            rg[u][0] = load_vec<VA>(rdy, oa);
-            if (VB == 4) {
-#pragma unroll
-                for (int v = 0; v < BC::NV; ++v) rg[u][1 + v] = buffer_load_f32x4(rx, ob[v]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rg[u][1][e] = buffer_load_f32(rx, ob[e]);
-            }
+            for (int e = 0; e < 4; ++e) rg[1][e] = buffer_load_f32(rx, ob[e]);
         }
     };
     auto store = [&](int buf, const Regs &rg) {
+        int o[4];
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-            const int row = lrow + 16 * u;
-            if (VA == 4) {
-                *reinterpret_cast<f32x4 *>(&As[buf][row][4 * lcol]) = rg[u][0];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) As[buf][row][lcol + 16 * e] = rg[u][0][e];
-            }
-            if (VB == 4) {
-#pragma unroll
-                for (int v = 0; v < BC::NV; ++v)
-                    *reinterpret_cast<f32x4 *>(&Bs[buf][row][BC::col(lcol, v)]) = rg[u][1 + v];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Bs[buf][row][BC::col(lcol, e)] = rg[u][1][e];
-            }
-        }
+        for (int e = 0; e < 4; ++e) o[e] = RedTile::at(lrow, lcol + 16 * e);
+        if (VA == 4)
+            store_split4(L.A[buf], RedTile::at(lrow, 4 * lcol), rg[0]);
+        else
+            store_split4(L.A[buf], o, rg[0]);
+        if (VB == 4)
+            store_split4(L.B[buf], RedTile::at(lrow, 4 * lcol), rg[1]);
+        else
+            store_split4(L.B[buf], o, rg[1]);
     };
 
-    f32x4 acc[2][NJ];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int jb = 0; jb < NJ; ++jb) acc[i][jb] = zero4();
+    f32x4 acc[2] = {zero4(), zero4()};
 
+    // Lane bases of the transpose reads: reduction rows 4g + jr (+16), columns
+    // 32wm + 16i + jc of A, 16wn + jc of B.
+    const int jr = il >> 2, jc = 4 * (il & 3);
+    const int ta[2] = {RedTile::at(4 * g + jr, 32 * wm + jc),
+                       RedTile::at(4 * g + jr, 32 * wm + 16 + jc)};
+    const int tb = RedTile::at(4 * g + jr, 16 * wn + jc);
     // Two register sets keep the loads of the next two steps in flight while
     // the current step, already in LDS, is multiplied.
-    Regs r0, r1;
-    if (st0 < st1) load(st0, r0);
-    if (st0 + 1 < st1) load(st0 + 1, r1);
-    if (st0 < st1) store(0, r0);
+    Regs rg[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+        if (st0 + u < st1) load(st0 + u, rg[u]);
+    if (st0 < st1) store(0, rg[0]);
     __syncthreads();
     // step st: `nx` holds step st+1 (in flight), `fr` is free
     auto body = [&](int st, Regs &nx, Regs &fr) {
         const int cur = (st - st0) & 1;
-        if (st + 2 < st1) load(st + 2, fr);
-        mma_step<NJ>(acc,
-                     [&](int kk, int i) { return As[cur][4 * kk + g][32 * wm + 16 * i + il]; },
-                     [&](int kk, int jb) { return Bs[cur][4 * kk + g][(TN / 2) * wn + 16 * jb + il]; });
+        if (st + NP < st1) load(st + NP, fr);
+        const Split8 a[2] = {load_split_tr<RedTile>(L.A[cur], ta[0], ta[0] + 32 * 16),
+                             load_split_tr<RedTile>(L.A[cur], ta[1], ta[1] + 32 * 16)};
+        mma_step(acc, a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16));
         if (st + 1 < st1) store(cur ^ 1, nx);
         __syncthreads();
     };
-    for (int st = st0; st < st1; st += 2) {
-        body(st, r1, r0);
-        if (st + 1 < st1) body(st + 1, r0, r1);
+    for (int st = st0; st < st1; st += NP) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (st + u < st1) body(st + u, rg[(u + 1) % NP], rg[u]);
     }
 
     float *dst = out + (size_t)split * p.K * RSC;   // split 0 of 1 is dW itself
+    float chk = 0.f;
+    const int j = j0 + 16 * wn + il;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int jb = 0; jb < NJ; ++jb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = k0 + 32 * wm + 16 * i + 4 * g + r;
-                const int j = j0 + (TN / 2) * wn + 16 * jb + il;
-                if (k < p.K && j < RSC) dst[(size_t)k * RSC + j] = acc[i][jb][r];
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int k = k0 + 32 * wm + 16 * i + 4 * g + r;
+            if (k < p.K && j < RSC) dst[(size_t)k * RSC + j] = acc[i][r];
+            chk = fmaf(acc[i][r], 0.f, chk);   // NaN if not finite
+        }
+    if (!__all(finite_f32(chk))) {
+#pragma unroll 1
+        for (int x = 0; x < 8; ++x) {
+            const int k = k0 + 32 * wm + 16 * (x >> 2) + 4 * g + (x & 3);
+            if (k < p.K && j < RSC && !finite_f32(dst[(size_t)k * RSC + j]))
+                dst[(size_t)k * RSC + j] =
+                    wgrad_plain(job, p, dv, k, j, st0 * BK, min(st1 * BK, M));
+        }
+    }
 }
 
-template <int VA, int VB, int TN>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MG_CONV_OCC, 8)))
+template <int VA, int VB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void conv_wgrad_f32(WgradJob job, ConvProblem p, ConvDivs dv) {
-    __shared__ ConvLds<TN> lds;
-    wgrad_tile<VA, VB, TN>(blockIdx.x, lds.w, job, p, dv);
+    __shared__ __attribute__((aligned(16))) ConvLds lds;
+    wgrad_tile<VA, VB>(blockIdx.x, lds, job, p, dv);
 }
 
 // out[i] = sum over splits of part[split][i].  A group of G consecutive lanes
@@ -357,17 +374,29 @@ __global__ __launch_bounds__(256) void conv_split_reduce_f32(ReduceJob a, Reduce
         split_reduce(blockIdx.x - a.blocks, b);
 }
 
+__device__ __forceinline__ float dgrad_plain(const DgradJob &job, const ConvProblem &p,
+                                          const ConvDivs &dv, int n, int i, int j, int c, int j0,
+                                          int j1) {
+    float sum = 0.f;
+    for (int x = j0; x < j1; ++x) {
+        const int t = fdiv(x, dv.K), k = x - t * p.K;
+        const int tr = fdiv(t, job.Sc_), ts = t - tr * job.Sc;
+        const int pp = i + job.da - tr, qq = j + job.db - ts;
+        if ((unsigned)pp >= (unsigned)p.P || (unsigned)qq >= (unsigned)p.Q) continue;
+        const size_t w = (((size_t)k * p.R + job.r0 + p.sh * tr) * p.S + job.s0 + p.sw * ts) * p.C;
+        sum = fmaf(job.dY[(((size_t)n * p.P + pp) * p.Q + qq) * p.K + k], job.Wt[w + c], sum);
+    }
+    return sum;
+}
+
 // --------------------------------------------------------- data gradient --
 // Block `bid` of a class job: split `split` of `nsplit` sums the reduction
 // steps [st0, st1) of the class's (tr, ts, k) for one 64x64 tile of its
 // pixels x channels.
-template <int VA, int VB, int TN>
-__device__ __forceinline__ void dgrad_tile(int bid, DgradLds<TN> &L, const DgradJob &job,
+template <int VA, int VB>
+__device__ __forceinline__ void dgrad_tile(int bid, ConvLds &L, const DgradJob &job,
                                            const ConvProblem &p, const ConvDivs &dv) {
-    using BC = BCols<VB, TN>;
-    constexpr int NJ = TN / 32;   // 16-column blocks per wave
-    auto &As = L.As;
-    auto &Bs = L.Bs;
+    using BC = BCols<VB>;
     const float *__restrict__ dY = job.dY;
     const float *__restrict__ Wt = job.Wt;
     float *__restrict__ out = job.out;
@@ -380,7 +409,7 @@ __device__ __forceinline__ void dgrad_tile(int bid, DgradLds<TN> &L, const Dgrad
     const int split = bid % nsplit;
     bid /= nsplit;
     const int m0 = (bid / tiles_c) * BM;
-    const int c0 = (bid % tiles_c) * TN;
+    const int c0 = (bid % tiles_c) * BN;
     const int st0 = (int)((long)nsteps * split / nsplit);
     const int st1 = (int)((long)nsteps * (split + 1) / nsplit);
 
@@ -393,9 +422,9 @@ __device__ __forceinline__ void dgrad_tile(int bid, DgradLds<TN> &L, const Dgrad
     const auto rdy = buffer_rsrc(dY, p.N * p.P * p.Q * p.K * 4);
     const auto rw = buffer_rsrc(Wt, p.K * p.R * p.S * p.C * 4);
 
-    // A staging: class pixel row ar (fixed), reduction columns 4*jq + 16u ..
-    // +3 of a step; B staging: reduction rows jr + 16u of a step, channel columns.
-    const int ar = tid >> 2, jq = tid & 3;
+    // A staging: class pixel row ar (fixed), reduction columns aj .. aj + 3 of
+    // a step; B staging: reduction row jr of a step, channel columns.
+    const int ar = tid >> 3, aj = 4 * (tid & 7);
     const int m = m0 + ar;
     const bool mok = m < Mc;
     const int n = fdiv(m, job.HWc), ij = m - n * HWc;
@@ -422,104 +451,93 @@ __device__ __forceinline__ void dgrad_tile(int bid, DgradLds<TN> &L, const Dgrad
         return ((k * p.R + job.r0 + p.sh * tr) * p.S + job.s0 + p.sw * ts) * p.C;
     };
 
-    using Regs = f32x4[NSUB][1 + BC::NV];   // [u][0]: A (dY), [u][1 + v]: B (W)
+    using Regs = f32x4[2];   // A (dY), B (W)
     auto load = [&](int st, Regs &rg) {
         const int j0 = st * BK;
-        int kb = 0, tr0 = 0, ts0 = 0;
+        int oa[4], ob[BC::NE];
         if (tap_uniform) {
             const int t0 = fdiv(j0, dv.K);
-            kb = j0 - t0 * p.K;
-            tr0 = fdiv(t0, job.Sc_);
-            ts0 = t0 - tr0 * job.Sc;
-        }
+            const int kb = j0 - t0 * p.K;
+            const int tr = fdiv(t0, job.Sc_);
+            const int ts = t0 - tr * job.Sc;
+            oa[0] = dy_offset(tr, ts, kb + aj);   // K % BK == 0: VA == 4
+            // W[k][r][s][c] for reduction row k = kb + jr of the tap
+            const int row = w_row(kb + jr, tr, ts);
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-            int oa[4], ob[BC::NE];
-            if (tap_uniform) {
+            for (int e = 0; e < BC::NE; ++e) ob[e] = cb[e] < p.C ? (row + cb[e]) * 4 : kOOB;
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int dk = 16 * u + 4 * jq + e;
-                    oa[e] = j0 + dk < RSKc ? dy_offset(tr0, ts0, kb + dk) : kOOB;
-                    if (VA == 4) break;
-                }
-                // W[k][r][s][c] for reduction row k = kb + 16u + jr of the tap
-                const int row = w_row(kb + 16 * u + jr, tr0, ts0);
-#pragma unroll
-                for (int e = 0; e < BC::NE; ++e)
-                    ob[e] = (j0 + 16 * u + jr < RSKc && cb[e] < p.C) ? (row + cb[e]) * 4 : kOOB;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    // a 16-byte chunk (VA == 4, K % 4 == 0) never straddles two taps
-                    const int j = j0 + 16 * u + 4 * jq + e;
-                    const int t = fdiv(j, dv.K), k = j - t * p.K;
-                    const int tr = fdiv(t, job.Sc_), ts = t - tr * job.Sc;
-                    oa[e] = j < RSKc ? dy_offset(tr, ts, k) : kOOB;
-                    if (VA == 4) break;
-                }
-                const int j = j0 + 16 * u + jr;
+            for (int e = 0; e < 4; ++e) {
+                // a 16-byte chunk (VA == 4, K % 4 == 0) never straddles two taps
+                const int j = j0 + aj + e;
                 const int t = fdiv(j, dv.K), k = j - t * p.K;
                 const int tr = fdiv(t, job.Sc_), ts = t - tr * job.Sc;
-                const int row = w_row(k, tr, ts);
-#pragma unroll
-                for (int e = 0; e < BC::NE; ++e)
-                    ob[e] = (j < RSKc && cb[e] < p.C) ? (row + cb[e]) * 4 : kOOB;
+                oa[e] = j < RSKc ? dy_offset(tr, ts, k) : kOOB;
+                if (VA == 4) break;
             }
-            rg[u][0] = load_vec<VA>(rdy, oa);
-            if (VB == 4) {
+            const int j = j0 + jr;
+            const int t = fdiv(j, dv.K), k = j - t * p.K;
+            const int tr = fdiv(t, job.Sc_), ts = t - tr * job.Sc;
+            const int row = w_row(k, tr, ts);
 #pragma unroll
-                for (int v = 0; v < BC::NV; ++v) rg[u][1 + v] = buffer_load_f32x4(rw, ob[v]);
-            } else {
+            for (int e = 0; e < BC::NE; ++e)
+                ob[e] = (j < RSKc && cb[e] < p.C) ? (row + cb[e]) * 4 : kOOB;
+        }
+        rg[0] = load_vec<VA>(rdy, oa);
+        if (VB == 4) {
+            rg[1] = buffer_load_f32x4(rw, ob[0]);
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) rg[u][1][e] = buffer_load_f32(rw, ob[e]);
-            }
+            for (int e = 0; e < 4; ++e) rg[1][e] = buffer_load_f32(rw, ob[e]);
         }
     };
     auto store = [&](int buf, const Regs &rg) {
+        store_split4(L.A[buf], PixTile::at(ar, 2 * (aj & 15) + 4 * (aj >> 4)), rg[0]);
+        if (VB == 4) {
+            store_split4(L.B[buf], RedTile::at(jr, 4 * cc), rg[1]);
+        } else {
+            int o[4];
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-            *reinterpret_cast<f32x4 *>(&As[buf][ar][16 * u + 4 * jq]) = rg[u][0];
-            if (VB == 4) {
-#pragma unroll
-                for (int v = 0; v < BC::NV; ++v)
-                    *reinterpret_cast<f32x4 *>(&Bs[buf][jr + 16 * u][BC::col(cc, v)]) = rg[u][1 + v];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Bs[buf][jr + 16 * u][BC::col(cc, e)] = rg[u][1][e];
-            }
+            for (int e = 0; e < 4; ++e) o[e] = RedTile::at(jr, cc + 16 * e);
+            store_split4(L.B[buf], o, rg[1]);
         }
     };
 
-    f32x4 acc[2][NJ];
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int jb = 0; jb < NJ; ++jb) acc[ii][jb] = zero4();
+    f32x4 acc[2] = {zero4(), zero4()};
 
+    // Lane bases of the reads: pixels 32wm + 16ii + il, reduction set of group
+    // g of A; reduction rows 4g + br (+16), columns 16wn + bc of B.
+    const int br = il >> 2, bc = 4 * (il & 3);
+    const int ta[2] = {PixTile::at(32 * wm + il, 8 * g), PixTile::at(32 * wm + 16 + il, 8 * g)};
+    const int tb = RedTile::at(4 * g + br, 16 * wn + bc);
     // Two register sets keep the loads of the next two steps in flight while
     // the current step, already in LDS, is multiplied.
-    Regs r0, r1;
-    if (st0 < st1) load(st0, r0);
-    if (st0 + 1 < st1) load(st0 + 1, r1);
-    if (st0 < st1) store(0, r0);
+    Regs rg[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+        if (st0 + u < st1) load(st0 + u, rg[u]);
+    if (st0 < st1) store(0, rg[0]);
     __syncthreads();
     // step st: `nx` holds step st+1 (in flight), `fr` is free
     auto body = [&](int st, Regs &nx, Regs &fr) {
         const int cur = (st - st0) & 1;
-        if (st + 2 < st1) load(st + 2, fr);
-        mma_step<NJ>(acc,
-                     [&](int kk, int ii) { return As[cur][32 * wm + 16 * ii + il][4 * kk + g]; },
-                     [&](int kk, int jb) { return Bs[cur][4 * kk + g][(TN / 2) * wn + 16 * jb + il]; });
+        if (st + NP < st1) load(st + NP, fr);
+        const Split8 a[2] = {load_split<PixTile>(L.A[cur], ta[0]),
+                             load_split<PixTile>(L.A[cur], ta[1])};
+        mma_step(acc, a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16));
         if (st + 1 < st1) store(cur ^ 1, nx);
         __syncthreads();
     };
-    for (int st = st0; st < st1; st += 2) {
-        body(st, r1, r0);
-        if (st + 1 < st1) body(st + 1, r0, r1);
+    for (int st = st0; st < st1; st += NP) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (st + u < st1) body(st + u, rg[(u + 1) % NP], rg[u]);
     }
 
     // rows of this lane's accumulators back to dX pixels (n, a + sh*i, b + sw*j)
     float *dst = out + (size_t)split * p.N * p.H * p.W * p.C;   // split 0 of 1 is dX
+    float chk = 0.f;
+    const int c = c0 + 16 * wn + il;
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -529,12 +547,22 @@ __device__ __forceinline__ void dgrad_tile(int bid, DgradLds<TN> &L, const Dgrad
             const int on = fdiv(mo, job.HWc), oij = mo - on * HWc;
             const int oi = fdiv(oij, job.Wc_), oj = oij - oi * job.Wc;
             const size_t pix = ((size_t)on * p.H + job.a + p.sh * oi) * p.W + job.b + p.sw * oj;
-#pragma unroll
-            for (int jb = 0; jb < NJ; ++jb) {
-                const int c = c0 + (TN / 2) * wn + 16 * jb + il;
-                if (c < p.C) dst[pix * p.C + c] = acc[ii][jb][r];
-            }
+            if (c < p.C) dst[pix * p.C + c] = acc[ii][r];
+            chk = fmaf(acc[ii][r], 0.f, chk);   // NaN if not finite
         }
+    if (!__all(finite_f32(chk))) {
+#pragma unroll 1
+        for (int x = 0; x < 8; ++x) {
+            const int mo = m0 + 32 * wm + 16 * (x >> 2) + 4 * g + (x & 3);
+            if (mo >= Mc || c >= p.C) continue;
+            const int on = fdiv(mo, job.HWc), oij = mo - on * HWc;
+            const int oi = fdiv(oij, job.Wc_), oj = oij - oi * job.Wc;
+            const size_t pix = ((size_t)on * p.H + job.a + p.sh * oi) * p.W + job.b + p.sw * oj;
+            if (!finite_f32(dst[pix * p.C + c]))
+                dst[pix * p.C + c] =
+                    dgrad_plain(job, p, dv, on, oi, oj, c, st0 * BK, min(st1 * BK, RSKc));
+        }
+    }
 }
 
 // Which class job a block belongs to (job counts and sizes are uniform).
@@ -547,27 +575,27 @@ __device__ __forceinline__ int find_class(const DgradJobs &jobs, int &bid) {
     return c;
 }
 
-template <int VA, int VB, int TN>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MG_CONV_OCC, 8)))
+template <int VA, int VB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void conv_dgrad_f32(DgradJobs jobs, ConvProblem p, ConvDivs dv) {
-    __shared__ ConvLds<TN> lds;
+    __shared__ __attribute__((aligned(16))) ConvLds lds;
     int bid = blockIdx.x;
     const int c = find_class(jobs, bid);
-    dgrad_tile<VA, VB, TN>(bid, lds.d, jobs.c[c], p, dv);
+    dgrad_tile<VA, VB>(bid, lds, jobs.c[c], p, dv);
 }
 
 // Both derivatives of one convolution in one launch: the first `dblocks`
 // workgroups run the data gradient's class jobs, the rest the filter gradient.
-template <int VA, int VB, int TN>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MG_CONV_OCC, 8)))
+template <int VA, int VB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void conv_bwd_f32(DgradJobs d, int dblocks, WgradJob w, ConvProblem p, ConvDivs dv) {
-    __shared__ ConvLds<TN> lds;
+    __shared__ __attribute__((aligned(16))) ConvLds lds;
     int bid = blockIdx.x;
     if (bid < dblocks) {
         const int c = find_class(d, bid);
-        dgrad_tile<VA, VB, TN>(bid, lds.d, d.c[c], p, dv);
+        dgrad_tile<VA, VB>(bid, lds, d.c[c], p, dv);
     } else {
-        wgrad_tile<VA, VB, TN>(bid - dblocks, lds.w, w, p, dv);
+        wgrad_tile<VA, VB>(bid - dblocks, lds, w, p, dv);
     }
 }
 
@@ -599,29 +627,18 @@ FastDiv make_fastdiv(unsigned d) {
 #ifndef MG_CONV_SPLIT_TERMS
 #define MG_CONV_SPLIT_TERMS 256
 #endif
+constexpr int kStepTerms = 16;   // terms counted as one step
 static int splits_for(long tiles, long steps) {
     if (tiles >= MG_CONV_SPLIT_BELOW) return 1;
     const long by_grid = (MG_CONV_SPLIT_TARGET + tiles - 1) / tiles;
-    const long by_steps = steps / (MG_CONV_SPLIT_TERMS / BK);
+    const long by_steps = steps / (MG_CONV_SPLIT_TERMS / kStepTerms);
     const long s = by_grid < by_steps ? by_grid : by_steps;
     return s < 1 ? 1 : (int)s;
 }
 
-// Output tile width: 64 columns.  A build option (MG_CONV_WIDE=1) selects
-// 128 columns, with half the operand loads per product, when the channel
-// vectors allow 16-byte loads and there are that many channels; on the
-// ResNet-50 step it measured 6 % slower (fewer tiles, more splits, five
-// waves per SIMD instead of seven).
-#ifndef MG_CONV_WIDE
-#define MG_CONV_WIDE 0
-#endif
-int conv_tile_n(const ConvProblem &p) {
-    return (MG_CONV_WIDE && p.C % 4 == 0 && p.C >= 128) ? 128 : 64;
-}
-
 int conv_wgrad_splits(const ConvProblem &p) {
-    return splits_for((long)cdiv(p.K, BM) * cdiv(p.R * p.S * p.C, conv_tile_n(p)),
-                      cdiv(p.N * p.P * p.Q, BK));
+    return splits_for((long)cdiv(p.K, BM) * cdiv(p.R * p.S * p.C, BN),
+                      cdiv(p.N * p.P * p.Q, kStepTerms));
 }
 
 namespace {
@@ -647,7 +664,7 @@ std::vector<DgradJob> dgrad_classes(const ConvProblem &p) {
             j.HWc = make_fastdiv(j.Hc * j.Wc);
             j.Wc_ = make_fastdiv(j.Wc);
             j.Sc_ = make_fastdiv(j.Sc > 0 ? j.Sc : 1);
-            j.tiles_c = cdiv(p.C, conv_tile_n(p));
+            j.tiles_c = cdiv(p.C, BN);
             cls.push_back(j);
         }
     return cls;
@@ -661,7 +678,7 @@ int conv_dgrad_splits(const ConvProblem &p) {
     long tiles = 0, steps = 0;
     for (const DgradJob &j : dgrad_classes(p)) {
         tiles += (long)cdiv(p.N * j.Hc * j.Wc, BM) * j.tiles_c;
-        steps = std::max<long>(steps, cdiv(j.Rc * j.Sc * p.K, BK));
+        steps = std::max<long>(steps, cdiv(j.Rc * j.Sc * p.K, kStepTerms));
     }
     return splits_for(tiles, steps);
 }
@@ -671,7 +688,7 @@ namespace {
 WgradJob wgrad_job(const ConvProblem &p, const float *X, const float *dY, float *dW,
                    float *partials) {
     const int ns = conv_wgrad_splits(p);
-    const int tiles_j = cdiv(p.R * p.S * p.C, conv_tile_n(p));
+    const int tiles_j = cdiv(p.R * p.S * p.C, BN);
     return WgradJob{X, dY, ns > 1 ? partials : dW, tiles_j, ns, cdiv(p.N * p.P * p.Q, BK),
                     cdiv(p.K, BM) * tiles_j * ns};
 }
@@ -712,43 +729,37 @@ ReduceJob reduce_job(const float *partials, int nsplit, int total, float *out) {
 // The kernel instance for the operands' vector widths (16-byte loads along
 // k when K % 4 == 0 and along c when C % 4 == 0, else 4-byte loads) and the
 // output tile width.
-template <template <int, int, int> class Launch, typename... Args>
+template <template <int, int> class Launch, typename... Args>
 hipError_t by_widths(const ConvProblem &p, Args &&...args) {
     const bool va = p.K % 4 == 0, vb = p.C % 4 == 0;
-#if MG_CONV_WIDE
-    if (conv_tile_n(p) == 128) {
-        if (va) return Launch<4, 4, 128>::run(args...);
-        return Launch<1, 4, 128>::run(args...);
-    }
-#endif
-    if (va && vb) return Launch<4, 4, 64>::run(args...);
-    if (va) return Launch<4, 1, 64>::run(args...);
-    if (vb) return Launch<1, 4, 64>::run(args...);
-    return Launch<1, 1, 64>::run(args...);
+    if (va && vb) return Launch<4, 4>::run(args...);
+    if (va) return Launch<4, 1>::run(args...);
+    if (vb) return Launch<1, 4>::run(args...);
+    return Launch<1, 1>::run(args...);
 }
 
-template <int VA, int VB, int TN>
+template <int VA, int VB>
 struct LaunchW {
     static hipError_t run(const WgradJob &j, const ConvProblem &p, const ConvDivs &dv,
                           hipStream_t s) {
-        conv_wgrad_f32<VA, VB, TN><<<dim3(j.blocks), dim3(NT), 0, s>>>(j, p, dv);
+        conv_wgrad_f32<VA, VB><<<dim3(j.blocks), dim3(NT), 0, s>>>(j, p, dv);
         return hipGetLastError();
     }
 };
-template <int VA, int VB, int TN>
+template <int VA, int VB>
 struct LaunchD {
     static hipError_t run(const DgradJobs &j, const ConvProblem &p, const ConvDivs &dv,
                           hipStream_t s) {
-        conv_dgrad_f32<VA, VB, TN><<<dim3(total_blocks(j)), dim3(NT), 0, s>>>(j, p, dv);
+        conv_dgrad_f32<VA, VB><<<dim3(total_blocks(j)), dim3(NT), 0, s>>>(j, p, dv);
         return hipGetLastError();
     }
 };
-template <int VA, int VB, int TN>
+template <int VA, int VB>
 struct LaunchDW {
     static hipError_t run(const DgradJobs &d, const WgradJob &w, const ConvProblem &p,
                           const ConvDivs &dv, hipStream_t s) {
         const int db = total_blocks(d);
-        conv_bwd_f32<VA, VB, TN><<<dim3(db + w.blocks), dim3(NT), 0, s>>>(d, db, w, p, dv);
+        conv_bwd_f32<VA, VB><<<dim3(db + w.blocks), dim3(NT), 0, s>>>(d, db, w, p, dv);
         return hipGetLastError();
     }
 };

@@ -49,14 +49,14 @@ __device__ __forceinline__ float minus_bf16(float x, uint32_t u, uint32_t select
                                            __builtin_bit_cast(bf16x2, select), x, false);
 }
 
-// Written on packed pairs: three pair conversions and four exact remainders
-// for two values.
-__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+// N pairs of f32 into their parts, as packed pairs: three pair conversions and
+// four exact remainders for two values.
+template <int N>
+__device__ __forceinline__ void split_pairs(const float (&x)[2 * N], uint32_t (&p)[3][N]) {
     uint32_t lo = 0x0000bf80u, hi = 0xbf800000u;
     asm("" : "+s"(lo), "+s"(hi));
-    u32x4 p[3];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
         float a = x[2 * i], b = x[2 * i + 1];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -68,9 +68,15 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
             }
         }
     }
+}
+
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+    uint32_t p[3][4];
+    split_pairs<4>(x, p);
     Split8 s;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) s.p[k] = __builtin_bit_cast(bf16x8, p[k]);
+    for (int k = 0; k < 3; ++k)
+        s.p[k] = __builtin_bit_cast(bf16x8, u32x4{p[k][0], p[k][1], p[k][2], p[k][3]});
     return s;
 }
 

@@ -88,3 +88,34 @@ def test_values_the_split_cannot_carry(gpu_lib, what, value, d):
         fin = np.isfinite(g[1]) & np.isfinite(r[1])
         if fin.any() and np.abs(value) != 3.4e38:
             assert np.max(np.abs(g[1][fin] - r[1][fin])) <= 1e-4 * max(1.0, np.max(np.abs(r[1][fin]))), n
+
+
+@pytest.mark.parametrize("which", ["X", "W", "dY"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_convolution_carries_infinities(gpu_lib, which, value):
+    """A value that the split cannot carry changes the outputs it reaches in
+    the equations and no others (3x3, stride 1, padding 1; channels 20 and 36
+    so that tiles end inside)."""
+    import torch
+    import paper_2608_01563_amd as mg
+    say("split operands convolution %s = %s" % (which, value))
+    g = torch.Generator().manual_seed(3)
+    X, W = torch.randn(2, 9, 9, 20, generator=g), torch.randn(36, 3, 3, 20, generator=g)
+    dY = torch.randn(2, 9, 9, 36, generator=g)
+    clean = mg.conv2d_backward(X.cuda(), W.cuda(), dY.cuda(), pad=(1, 1))
+    t = {"X": X, "W": W, "dY": dY}[which]
+    t[(1, 4, 5, 3) if which != "W" else (5, 1, 2, 3)] = value
+    dX, dW = mg.conv2d_backward(X.cuda(), W.cuda(), dY.cuda(), pad=(1, 1))
+    hit = {"dX": torch.zeros(dX.shape, dtype=torch.bool), "dW": torch.zeros(dW.shape, dtype=torch.bool)}
+    if which == "X":       # dW[:, r, s, 3] through dY[1, 5 - r, 6 - s]
+        hit["dW"][:, :, :, 3] = True
+    elif which == "W":     # dX[n, h, w, 3] where output (h, w - 1) exists
+        hit["dX"][:, :, 1:, 3] = True
+    else:                  # dX[1, 3:6, 4:7], dW[3]
+        hit["dX"][1, 3:6, 4:7] = True
+        hit["dW"][3] = True
+    for n, got, ref in (("dX", dX.cpu(), clean[0].cpu()), ("dW", dW.cpu(), clean[1].cpu())):
+        assert not torch.isfinite(got[hit[n]]).any(), n
+        rest = ~hit[n]
+        assert torch.isfinite(got[rest]).all(), n
+        assert torch.allclose(got[rest], ref[rest], rtol=1e-5, atol=1e-4), n
