@@ -78,7 +78,7 @@ void attn_fwd_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ 
     constexpr int VW = (D >= 64) ? 64 : 32;
     using TileV = std::conditional_t<VW == 64, Bf16Tile<kStream, D, kWaves, 64, 1, 1, 4>, Tile>;
     constexpr int NL = Tile::kPerWave;   // loads per wave per tile (the vmcnt waits below)
-    static_assert(TileV::kPerWave == NL, "K and V loads per wave");
+    static_assert(TileV::kPerWave == NL && Tile::kEven && TileV::kEven, "K and V loads per wave");
     constexpr int BLK = Tile::kBlock, BLKV = TileV::kBlock;
     __shared__ __attribute__((aligned(16))) uint16_t Kr[Tile::kSize];
     __shared__ __attribute__((aligned(16))) uint16_t Vr[TileV::kSize];
@@ -444,9 +444,11 @@ void attn_fwd_bf16_pipe(const uint16_t *__restrict__ Q, const uint16_t *__restri
 // compiler can then tell the next tile's direct-to-LDS loads apart from the
 // current tile's operand reads and does not wait for the loads before the
 // reads (with one array indexed by a run-time buffer number it must assume
-// they may overlap, and the prefetch would stall every iteration).
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// they may overlap, and the prefetch would stall every iteration).  G = 2: two
+// groups of four waves hold the same keys and take half of every query tile
+// each; the second hands its sums over at the end.
+template <int D, int G>
+__global__ __launch_bounds__(kThreads * G) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                     const uint16_t *__restrict__ V, const uint16_t *__restrict__ dO,
                     const float *__restrict__ LSE, const float *__restrict__ Dws,
@@ -461,7 +463,8 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
     // loads: the next tile is fetched during the whole current iteration,
     // and one barrier per iteration suffices.
     constexpr int TW = 32;   // column block width of the tiles
-    using Tile = Bf16Tile<QR, D, kWaves, TW, 1, 3, 1>;
+    using Tile = Bf16Tile<QR, D, kWaves * G, TW, 1, 3, 1>;
+    constexpr int GB = QB / G;       // 16-row blocks per row group
     constexpr int BLK = Tile::kBlock;
     __shared__ __attribute__((aligned(16))) uint16_t Qr0[Tile::kSize], Qr1[Tile::kSize];
     __shared__ __attribute__((aligned(16))) uint16_t Or0[Tile::kSize], Or1[Tile::kSize];
@@ -477,7 +480,9 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gr = (G == 1) ? 0 : wg / kWaves;   // row group: blocks GB*gr .. of each tile
+    const int w = wg - gr * kWaves;
     const int il = lane & 15;
     const int g = lane >> 4;
     const int jr = il >> 2, jc = 4 * (il & 3);   // transpose-read block offsets
@@ -522,21 +527,21 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
     static_assert(QR == 64, "one statistic per lane");
     __shared__ __attribute__((aligned(16))) float raw[2][QR];   // LSE, D in flight
     auto fetch = [&](int qt, Buf &Qn, Buf &On) {
-        tile.issue(Qn, Q + qoff, qt * QR, Lq, w);
-        tile.issue(On, dO + qoff, qt * QR, Lq, w);
-        if (w == 0 || w == kWaves - 1) {
+        tile.issue(Qn, Q + qoff, qt * QR, Lq, wg);
+        tile.issue(On, dO + qoff, qt * QR, Lq, wg);
+        if (wg == 0 || wg == kWaves * G - 1) {
             const int row0 = qt * QR;
             const int rows = min(max(Lq - row0, 0), QR);
-            const float *src = (w == 0 ? LSE : Dws) + (size_t)head * Lq + row0;
+            const float *src = (wg == 0 ? LSE : Dws) + (size_t)head * Lq + row0;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 buffer_rsrc(src, rows * 4),
-                (__attribute__((address_space(3))) void *)&raw[w == 0 ? 0 : 1][0], 4, lane * 4, 0,
+                (__attribute__((address_space(3))) void *)&raw[wg == 0 ? 0 : 1][0], 4, lane * 4, 0,
                 0, 0);
         }
     };
     auto publish = [&](float (&ln)[QR], float (&dn)[QR]) {
-        if (w == 0) ln[lane] = raw[0][lane] * kLog2e;
-        if (w == kWaves - 1) dn[lane] = -raw[1][lane];
+        if (wg == 0) ln[lane] = raw[0][lane] * kLog2e;
+        if (wg == kWaves * G - 1) dn[lane] = -raw[1][lane];
     };
 
     // One query tile from buffers (Qc, Oc, lc, dc) while tile qt + 1 loads
@@ -545,35 +550,36 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
                     Buf &On, float (&ln)[QR], float (&dn)[QR]) {
         if (qt + 1 < qstop) fetch(qt + 1, Qn, On);   // freed by the last barrier
 
+        const int row0 = 16 * GB * gr;   // this group's rows of the tile
         // S = Q K^T; dP - D = dO V^T accumulated onto -D (rows 16ib + 4g + r)
-        f32x4 sacc[QB], pacc[QB];
+        f32x4 sacc[GB], pacc[GB];
 #pragma unroll
-        for (int ib = 0; ib < QB; ++ib) {
+        for (int ib = 0; ib < GB; ++ib) {
             sacc[ib] = zero4();
-            pacc[ib] = *reinterpret_cast<const f32x4 *>(&dc[16 * ib + 4 * g]);
+            pacc[ib] = *reinterpret_cast<const f32x4 *>(&dc[row0 + 16 * ib + 4 * g]);
         }
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
-            for (int ib = 0; ib < QB; ++ib) {
-                const int o = qa[s % NA] + (s / NA) * BLK + 16 * TW * ib;
+            for (int ib = 0; ib < GB; ++ib) {
+                const int o = qa[s % NA] + (s / NA) * BLK + TW * (row0 + 16 * ib);
                 sacc[ib] = mfma16x16x32bf16(load_bf16x8(Qc + o), kreg[s], sacc[ib]);
                 pacc[ib] = mfma16x16x32bf16(load_bf16x8(Oc + o), vreg[s], pacc[ib]);
             }
 
-        // 2*NS*QB operand reads and as many products: eight reads ahead
+        // 2*NS*GB operand reads and as many products: eight reads ahead
         // (d = 128: 279-282 -> 268-273 us at B2 H16 L4096; at d = 64 and 32,
         // where a wave has half or a quarter of the reads, 1-3 % slower)
-        if constexpr (D == 128) sched_reads_ahead<2 * NS * QB, 2 * NS * QB, 8, 2, 2, 0>();
+        if constexpr (D == 128) sched_reads_ahead<2 * NS * GB, 2 * NS * GB, 8, 2, 2, 0>();
 
         // P = exp2(S * scale*log2e - LSE*log2e), dS = P (dP - D); the mask (row
         // qt*QR + 16ib + 4g + r sees key kj iff 16ib + r >= thr) only in tiles
         // that cross the wave's causal boundary.
         auto softmax = [&](auto masked) {
-            const int thr = kj - diag - (qt * QR + 4 * g);
+            const int thr = kj - diag - (qt * QR + row0 + 4 * g);
 #pragma unroll
-            for (int ib = 0; ib < QB; ++ib) {
-                const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lc[16 * ib + 4 * g]);
+            for (int ib = 0; ib < GB; ++ib) {
+                const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lc[row0 + 16 * ib + 4 * g]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float p = exp2_fast(fmaf(sacc[ib][r], scale_log2, -l2[r]));
@@ -583,17 +589,17 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
                 }
             }
         };
-        if (!causal || qt * QR + diag >= k0 + 16 * w + 15)
+        if (!causal || qt * QR + row0 + diag >= k0 + 16 * w + 15)
             softmax(std::false_type{});
         else
             softmax(std::true_type{});
 
         // dV^T[16c + .][kj] += dO^T[16c + il'][i] P[i][kj]; dK^T likewise with Q, dS
 #pragma unroll
-        for (int t = 0; t < QB / 2; ++t) {
+        for (int t = 0; t < GB / 2; ++t) {
             const bf16x8 pb = pack_bf16(sacc[2 * t], sacc[2 * t + 1]);
             const bf16x8 sb = pack_bf16(pacc[2 * t], pacc[2 * t + 1]);
-            const int r0 = 32 * TW * t;
+            const int r0 = TW * (row0 + 32 * t);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const int o = qb[c % NB] + (c / NB) * BLK + r0;
@@ -604,8 +610,8 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
             }
         }
 
-        // 2*QB*NC transpose reads for QB*NC products, eight ahead (d = 128)
-        if constexpr (D == 128) sched_reads_ahead<2 * QB * NC, QB * NC, 8, 2, 1, 1>();
+        // 2*GB*NC transpose reads for GB*NC products, eight ahead (d = 128)
+        if constexpr (D == 128) sched_reads_ahead<2 * GB * NC, GB * NC, 8, 2, 1, 1>();
 
         if (qt + 1 < qstop) {
             wait_vmcnt<0>();   // next tile and its LSE, D landed
@@ -625,6 +631,27 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
         if (qt + 1 < qstop) step(qt + 1, Qr1, Or1, lse1, Ds1, Qr0, Or0, lse0, Ds0);
     }
 
+    if constexpr (G == 2) {
+        // the second row group's sums reach the first through the tile
+        // buffers, which no wave reads any more
+        static_assert(sizeof(Buf) == 2 * NC * 64 * sizeof(f32x4), "a wave's sums fill one buffer");
+        uint16_t *const mine = w == 0 ? Qr0 : w == 1 ? Qr1 : w == 2 ? Or0 : Or1;
+        f32x4 *x = reinterpret_cast<f32x4 *>(mine) + lane;
+        if (gr == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                x[64 * 2 * c] = dkacc[c];
+                x[64 * (2 * c + 1)] = dvacc[c];
+            }
+        }
+        __syncthreads();
+        if (gr == 1) return;   // no barrier follows
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            dkacc[c] += x[64 * 2 * c];
+            dvacc[c] += x[64 * (2 * c + 1)];
+        }
+    }
     if (kj < Lk) {
         const bool keep = kj < klen;   // padded keys get exact zeros
         uint16_t *dkrow = dK + hoff + (size_t)kj * D;
@@ -652,9 +679,10 @@ void attn_dkdv_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__
 // next tile is fetched during the whole current iteration.  As in the dK/dV
 // kernel, the two buffers are separate arrays and the tile loop is unrolled
 // by two, so that the current tile's reads need not wait for the next
-// tile's loads.
-template <int D, int KS>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// tile's loads.  G = 2: two groups of four waves hold the same queries and take
+// half of every key tile each; the second hands its sums over at the end.
+template <int D, int KS, int G>
+__global__ __launch_bounds__(kThreads * G) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                   const uint16_t *__restrict__ V, const uint16_t *__restrict__ O,
                   const uint16_t *__restrict__ dO, const float *__restrict__ LSE,
@@ -666,7 +694,7 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
     constexpr int NC = D / 16;
     // K and V tiles are double-buffered and arrive by 16-byte direct-to-LDS
     // loads: the next tile is fetched during the whole current iteration.
-    using Tile = Bf16Tile<KS, D, kWaves, 32, 1, 3, 1>;
+    using Tile = Bf16Tile<KS, D, kWaves * G, 32, 1, 3, 1>;
     constexpr int BLK = Tile::kBlock;
     __shared__ __attribute__((aligned(16))) uint16_t Kr0[Tile::kSize], Kr1[Tile::kSize];
     __shared__ __attribute__((aligned(16))) uint16_t Vr0[Tile::kSize], Vr1[Tile::kSize];
@@ -681,7 +709,9 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gr = (G == 1) ? 0 : wg / kWaves;   // key group: the gr-th part of each tile
+    const int w = wg - gr * kWaves;
     const int il = lane & 15;
     const int g = lane >> 4;
     const int jr = il >> 2, jc = 4 * (il & 3);
@@ -716,7 +746,7 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
             }
         }
         Di[qb] = sum_over_groups(dsum);
-        if (q < Lq && g == 0) Dws[(size_t)head * Lq + q] = Di[qb];
+        if (q < Lq && g == 0 && gr == 0) Dws[(size_t)head * Lq + q] = Di[qb];
     }
 
     f32x4 dqacc[NC][QB];   // dQ^T[16c + 4g + r][qi + 16qb]
@@ -733,18 +763,19 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
     const int ta[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
     using Buf = uint16_t[Tile::kSize];
     auto fetch = [&](int t, Buf &Kn, Buf &Vn) {
-        tile.issue(Kn, K + hoff, t * KS, Lk, w);
-        tile.issue(Vn, V + hoff, t * KS, Lk, w);
+        tile.issue(Kn, K + hoff, t * KS, Lk, wg);
+        tile.issue(Vn, V + hoff, t * KS, Lk, wg);
     };
     // key tile kt from (Kc, Vc) while tile kt + 1 loads into (Kn, Vn)
     auto step = [&](int kt, Buf &Kc, Buf &Vc, Buf &Kn, Buf &Vn) {
         if (kt + 1 < ntiles) fetch(kt + 1, Kn, Vn);   // freed by the last barrier
         const bool full = (kt + 1) * KS <= klen &&
                           (!causal || (kt + 1) * KS - 1 <= q0 + diag);
-        const int j0 = kt * KS + 4 * g;
+        const int key0 = (KS / G) * gr;   // this group's keys of the tile
+        const int j0 = kt * KS + key0 + 4 * g;
 
 #pragma unroll
-        for (int t = 0; t < KS / 32; ++t) {   // 32 keys at a time
+        for (int t = 0; t < KS / (32 * G); ++t) {   // 32 keys at a time
             // S^T = K Q^T; dP^T - D = V dO^T accumulated onto -D
             f32x4 sacc[2][QB], pacc[2][QB];   // [16-key block][query block]
 #pragma unroll
@@ -758,7 +789,7 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
             for (int s = 0; s < NS; ++s)
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
-                    const int o = ka + s * BLK + 32 * (32 * t + 16 * kb);
+                    const int o = ka + s * BLK + 32 * (key0 + 32 * t + 16 * kb);
                     const bf16x8 k8 = load_bf16x8(Kc + o), v8 = load_bf16x8(Vc + o);
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb) {
@@ -793,7 +824,7 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
             for (int qb = 0; qb < QB; ++qb) sb[qb] = pack_bf16(pacc[0][qb], pacc[1][qb]);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const int o = ta[c & 1] + (c >> 1) * BLK + 32 * 32 * t;
+                const int o = ta[c & 1] + (c >> 1) * BLK + 32 * (key0 + 32 * t);
                 const bf16x8 a = load_tr_pair_at(Kc + o, Kc + o + 32 * 16);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] = mfma16x16x32bf16(a, sb[qb], dqacc[c][qb]);
@@ -811,6 +842,24 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
         if (kt + 1 < ntiles) step(kt + 1, Kr1, Vr1, Kr0, Vr0);
     }
 
+    if constexpr (G == 2) {
+        // the second key group's sums reach the first through the tile buffers
+        static_assert(sizeof(Buf) == QB * NC * 64 * sizeof(f32x4), "a wave's sums fill one buffer");
+        uint16_t *const mine = w == 0 ? Kr0 : w == 1 ? Kr1 : w == 2 ? Vr0 : Vr1;
+        f32x4 *x = reinterpret_cast<f32x4 *>(mine) + lane;
+        if (gr == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) x[64 * (QB * c + qb)] = dqacc[c][qb];
+        }
+        __syncthreads();
+        if (gr == 1) return;   // no barrier follows
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] += x[64 * (QB * c + qb)];
+    }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int q = qi + 16 * qb;
@@ -823,6 +872,15 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// The backward's two-group forms (eight waves, each group half of every streamed
+// tile) where one round of workgroups leaves the time to the chain of tiles:
+// at most one workgroup per CU and 768 or more streamed rows.  One against two
+// groups, us: B1 H4 L2500 d64 dQ 40.8 : 34.5, dK/dV 40.6 : 33.9; B2 H6 L1200
+// causal 22.7 : 20.7, 22.8 : 20.2; B1 H12 L900 d128 causal 28.8 : 26.1, 27.0 :
+// 26.4; but B4 H6 L300 11.6 : 12.2, B4 H12 L700 d128 (288 and 528 workgroups)
+// 33.3 : 41.2, 45.0 : 54.8.
+inline bool two_groups(long grid, int streamed) { return grid <= 256 && streamed >= 768; }
 
 }  // namespace
 
@@ -855,16 +913,19 @@ hipError_t launch_bwd_dkdv_bf16(const AttnProblem &p, const uint16_t *Q, const u
                                 const float *Dws, uint16_t *dK, uint16_t *dV, hipStream_t s) {
     const int BH = p.B * p.H;
     const float sl2 = p.scale * kLog2e;
-    const dim3 grid(cdiv(p.Lk, kStatRows) * BH), block(kThreads);
-    auto go = [&](auto kern) {
-        const int ly = causal_rank_layer((const void *)kern, kThreads, grid.x, BH, p.causal);
+    const dim3 grid(cdiv(p.Lk, kStatRows) * BH);
+    const bool two = two_groups(grid.x, p.Lq);
+    auto go = [&](auto one, auto pair) {
+        auto kern = two ? pair : one;
+        const dim3 block(two ? 2 * kThreads : kThreads);
+        const int ly = causal_rank_layer((const void *)kern, block.x, grid.x, BH, p.causal);
         kern<<<grid, block, 0, s>>>(Q, K, V, dO, LSE, Dws, dK, dV, p.key_len, p.H, p.Lq, p.Lk,
                                     p.causal, p.scale, sl2, BH, ly);
     };
     switch (p.d) {
-    case 32: go(attn_dkdv_bf16<32>); break;
-    case 64: go(attn_dkdv_bf16<64>); break;
-    case 128: go(attn_dkdv_bf16<128>); break;
+    case 32: go(attn_dkdv_bf16<32, 1>, attn_dkdv_bf16<32, 2>); break;
+    case 64: go(attn_dkdv_bf16<64, 1>, attn_dkdv_bf16<64, 2>); break;
+    case 128: go(attn_dkdv_bf16<128, 1>, attn_dkdv_bf16<128, 2>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -875,17 +936,20 @@ hipError_t launch_bwd_dq_bf16(const AttnProblem &p, const uint16_t *Q, const uin
                               const float *LSE, float *Dws, uint16_t *dQ, hipStream_t s) {
     const int BH = p.B * p.H;
     const int nqt = cdiv(p.Lq, kFwdRows);
-    const dim3 grid(nqt * BH), block(kThreads);
+    const dim3 grid(nqt * BH);
     const float sl2 = p.scale * kLog2e;
-    auto go = [&](auto kern) {
-        const int ly = causal_rank_layer((const void *)kern, kThreads, grid.x, BH, p.causal);
+    const bool two = two_groups(grid.x, p.Lk);
+    auto go = [&](auto one, auto pair) {
+        auto kern = two ? pair : one;
+        const dim3 block(two ? 2 * kThreads : kThreads);
+        const int ly = causal_rank_layer((const void *)kern, block.x, grid.x, BH, p.causal);
         kern<<<grid, block, 0, s>>>(Q, K, V, O, dO, LSE, Dws, dQ, p.key_len, p.H, p.Lq, p.Lk,
                                     p.causal, p.scale, sl2, nqt, BH, ly);
     };
     switch (p.d) {
-    case 32: go(attn_dq_bf16<32, 64>); break;
-    case 64: go(attn_dq_bf16<64, 64>); break;
-    case 128: go(attn_dq_bf16<128, 64>); break;
+    case 32: go(attn_dq_bf16<32, 64, 1>, attn_dq_bf16<32, 64, 2>); break;
+    case 64: go(attn_dq_bf16<64, 64, 1>, attn_dq_bf16<64, 64, 2>); break;
+    case 128: go(attn_dq_bf16<128, 64, 1>, attn_dq_bf16<128, 64, 2>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

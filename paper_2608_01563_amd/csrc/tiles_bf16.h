@@ -70,8 +70,8 @@ struct Bf16Tile {
     static constexpr int kBlock = ROWS * W;     // u16 per column block
     static constexpr int kSize = ROWS * D;      // u16 per tile
     static constexpr int kLoads = kSize / 512;  // 1 KB loads per tile
-    static constexpr int kPerWave = kLoads / NW;
-    static_assert(kLoads % NW == 0, "every wave issues the same number of loads");
+    static constexpr int kPerWave = (kLoads + NW - 1) / NW;
+    static constexpr bool kEven = kLoads % NW == 0;   // else the last waves issue fewer
 
     __host__ __device__ static constexpr int swz(int r) { return ((r >> SS) & SM) * SK; }
     // u16 offset of element (r, e) in the tile
@@ -89,8 +89,8 @@ struct Bf16Tile {
     }
 
     // This wave's share of rows [row0, row0 + ROWS) of src (row-major, D
-    // bf16 per row) into dst (kSize u16 of LDS); kPerWave loads, tracked by
-    // the wave's vmcnt.  A load's row and block offset goes into the vector
+    // bf16 per row) into dst (kSize u16 of LDS); kPerWave loads when kEven
+    // (else at most that many), tracked by the wave's vmcnt.  A load's row and block offset goes into the vector
     // offset, the one the buffer's range check sees.
     __device__ __forceinline__ void issue(uint16_t *dst, const uint16_t *__restrict__ src,
                                           int row0, int L, int w) const {
@@ -99,6 +99,7 @@ struct Bf16Tile {
 #pragma unroll
         for (int uu = 0; uu < kPerWave; ++uu) {
             const int u = uu * NW + w;
+            if (!kEven && u >= kLoads) break;
             const int r0 = (kRowsPerLoad * u) % ROWS, blk = (kRowsPerLoad * u) / ROWS;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rsrc, (__attribute__((address_space(3))) void *)(dst + 512 * u), 16,

@@ -74,3 +74,17 @@ def test_many_rows(gpu_lib, Lq, Lk, causal, d, contract):
     x = make_inputs(1, H, Lq, d, causal=causal, contract=contract, seed=Lq + Lk + d, Lk=Lk,
                     key_len=None if causal else [Lk - 3])
     check_forward(x, contract)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("Lq,Lk,mode", [(800, 800, "causal"), (769, 801, "padded"),
+                                        (830, 790, "causal")])
+def test_bf16_two_group_backward(gpu_lib, Lq, Lk, mode, d):
+    """Long chains on a small grid: the bf16 backward's two wave groups per
+    workgroup, tiles whose second half is masked or past the end among them."""
+    from gpu_util import compare, oracle_reference, run_gpu
+    say("bf16 two groups Lq=%d Lk=%d d=%d %s" % (Lq, Lk, d, mode))
+    x = make_inputs(2, 2, Lq, d, causal=mode == "causal", contract="fast_bf16", seed=Lq + d, Lk=Lk,
+                    key_len=[Lk - 33, 65] if mode == "padded" else None)
+    errs = compare(run_gpu(x), oracle_reference(x), "fast_bf16")
+    assert max(errs.values()) <= TOL["fast_bf16"], errs
