@@ -9,6 +9,8 @@
 // pair of the fused kernel in attn_f32.hip, and drop that kernel's dQ partials
 // (written and read back, 151 MB at B8 H8 L1024 d64), their reduction and the
 // separate D launch.
+#include <algorithm>
+
 #include "device_common.h"
 #include "launch.h"
 #include "tiles_split.h"
@@ -85,9 +87,11 @@ __device__ __noinline__ void dkdv_keys_plain(const float *Q, const float *K, con
 }
 
 // ------------------------------------------------------------------------ dQ --
-// QW waves of 16 QB query rows; key tiles of KT keys, double-buffered.
-template <int D, int QB, int QW, int KT>
-__global__ __launch_bounds__(64 * QW) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// QW waves of 16 QB query rows; key tiles of KT keys, double-buffered.  G = 2: two
+// groups of QW waves hold the same rows and take half of every key tile each,
+// through one buffer; the second hands its sums over at the end.
+template <int D, int QB, int QW, int KT, int G>
+__global__ __launch_bounds__(64 * QW * G) __attribute__((amdgpu_waves_per_eu(G == 2 && D <= 64 ? 4 : 2, 8)))
 void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                    const float *__restrict__ V, const float *__restrict__ O,
                    const float *__restrict__ dO, const float *__restrict__ LSE,
@@ -95,11 +99,12 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                    const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
                    float scale, float scale_log2, int n_qtiles, int BH, int layer,
                    int padded_order) {
-    constexpr int NT = 64 * QW;
-    constexpr int NS = D / 32, NC = D / 16, NKB = KT / 16, WQ = 16 * QB;
+    constexpr int NT = 64 * QW * G;
+    constexpr int NS = D / 32, NC = D / 16, NKB = KT / (16 * G), WQ = 16 * QB;
     using Tile = Bf16Tile<KT, D, 1, 32, 1, 3, 1>;
     constexpr int BLK = Tile::kBlock, TS = 3 * Tile::kSize;
-    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][TS], Vs[2][TS];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[(G == 1 ? 4 : 2) * TS];
+    uint16_t *const Ks = smem, *const Vs = smem + TS;   // next buffers 2 TS further
 
     int slot, head;
     if (padded_order) {
@@ -115,7 +120,9 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     const int diag = Lk - Lq;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gr = (G == 1) ? 0 : wg / QW;   // key group: the gr-th part of each tile
+    const int w = wg - gr * QW;
     const int il = lane & 15, g = lane >> 4;
     const int jr = il >> 2, jc = 4 * (il & 3);
     const int q0 = qt * WQ * QW, qw0 = q0 + WQ * w, qi = qw0 + il;
@@ -155,10 +162,12 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             oreg[s][qb] = split8(x, y);
         }
         Di[qb] = sum_over_groups(dsum);
-        if (q < Lq && g == 0) Dws[(size_t)head * Lq + q] = Di[qb];
+        if (q < Lq && g == 0 && gr == 0) Dws[(size_t)head * Lq + q] = Di[qb];
     }
-    const int ka = Tile::at(il, 8 * g);
-    const int kt_[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
+    const int key0 = 16 * NKB * gr;   // this group's keys of a tile
+    const int ka = Tile::at(il, 8 * g) + 32 * key0;
+    const int kt_[2] = {Tile::at(4 * g + jr, jc) + 32 * key0,
+                        Tile::at(4 * g + jr, 16 + jc) + 32 * key0};
 
     f32x4 dqacc[NC][QB];   // dQ^T[16c + 4g + r][qi + 16qb]
 #pragma unroll
@@ -167,23 +176,23 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] = zero4();
 
     if (ntiles > 0) {
-        sk.store(Ks[0], tid);
-        sv.store(Vs[0], tid);
+        sk.store(Ks, tid);
+        sv.store(Vs, tid);
         sk.load(Kh, KT, klen, tid);
         sv.load(Vh, KT, klen, tid);
     }
     __syncthreads();
     for (int kt = 0; kt < ntiles; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < ntiles) {   // tile kt + 1 goes to the buffer the last barrier freed
-            sk.store(Ks[cur ^ 1], tid);
-            sv.store(Vs[cur ^ 1], tid);
+        const int cur = (G == 1 && (kt & 1)) ? 2 * TS : 0, nxt = 2 * TS - cur;
+        if (G == 1 && kt + 1 < ntiles) {   // tile kt + 1 goes to the buffer the last barrier freed
+            sk.store(Ks + nxt, tid);
+            sv.store(Vs + nxt, tid);
             sk.load(Kh, (kt + 2) * KT, klen, tid);
             sv.load(Vh, (kt + 2) * KT, klen, tid);
         }
-        const int jt = kt * KT;
-        if (!causal || jt <= qw0 + WQ - 1 + diag) {
-            const uint16_t *Kc = Ks[cur], *Vc = Vs[cur];
+        const int jt = kt * KT + key0;
+        if (jt < klen && (!causal || jt <= qw0 + WQ - 1 + diag)) {
+            const uint16_t *Kc = Ks + cur, *Vc = Vs + cur;
             f32x4 sacc[NKB][QB], pacc[NKB][QB];   // S^T, dP^T[16kb + 4g + r][qi + 16qb]
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
@@ -203,7 +212,7 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             // two products' operand reads in flight (d = 128: 89 -> 82 us at B2 H8 L1024)
             sched_reads_ahead<6 * NS * NKB, 12 * QB * NS * NKB, 6, 3, 6 * QB, 0>();
             // dS^T = P^T (dP^T - D), P^T = exp2(S^T * scale*log2e - LSE*log2e)
-            const bool masked = jt + KT > klen || (causal && jt + KT - 1 > qw0 + diag);
+            const bool masked = jt + 16 * NKB > klen || (causal && jt + 16 * NKB - 1 > qw0 + diag);
             const int j0 = jt + 4 * g;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
@@ -246,6 +255,30 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             sched_reads_ahead<6 * NC * NKB / 2, 6 * QB * NC * NKB / 2, 6, 6, 6 * QB, 1>();
         }
         __syncthreads();   // tile kt + 1 visible; tile kt's buffers free
+        if (G > 1 && kt + 1 < ntiles) {
+            sk.store(Ks, tid);
+            sv.store(Vs, tid);
+            sk.load(Kh, (kt + 2) * KT, klen, tid);
+            sv.load(Vh, (kt + 2) * KT, klen, tid);
+            __syncthreads();
+        }
+    }
+    if constexpr (G == 2) {
+        // the second group's sums reach the first through the tile buffers
+        static_assert(sizeof(smem) >= (size_t)QW * NC * QB * 64 * sizeof(f32x4), "sums fit");
+        f32x4 *x = reinterpret_cast<f32x4 *>(smem) + w * NC * QB * 64 + lane;
+        if (gr == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) x[64 * (QB * c + qb)] = dqacc[c][qb];
+        }
+        __syncthreads();
+        if (gr == 1) return;   // no barrier follows
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) dqacc[c][qb] += x[64 * (QB * c + qb)];
     }
 
     bool fine = true;
@@ -273,9 +306,10 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
 }
 
 // -------------------------------------------------------------------- dK, dV --
-// KW waves of 16 keys; query tiles of QT rows, double-buffered.
-template <int D, int KW, int QT>
-__global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// KW waves of 16 keys; query tiles of QT rows, double-buffered (G = 2: as above,
+// half of every query tile per group, through one buffer).
+template <int D, int KW, int QT, int G>
+__global__ __launch_bounds__(64 * KW * G) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                      const float *__restrict__ V, const float *__restrict__ dO,
                      const float *__restrict__ LSE, const float *__restrict__ Dws,
@@ -283,11 +317,12 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                      const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
                      float scale, float scale_log2, int n_ktiles, int BH, int layer,
                      int padded_order) {
-    constexpr int NT = 64 * KW;
-    constexpr int NS = D / 32, NC = D / 16, NIB = QT / 16, KR = 16 * KW;
+    constexpr int NT = 64 * KW * G;
+    constexpr int NS = D / 32, NC = D / 16, NIB = QT / (16 * G), KR = 16 * KW;
     using Tile = Bf16Tile<QT, D, 1, 32, 1, 3, 1>;
     constexpr int BLK = Tile::kBlock, TS = 3 * Tile::kSize;
-    __shared__ __attribute__((aligned(16))) uint16_t Qs[2][TS], Os[2][TS];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[(G == 1 ? 4 : 2) * TS];
+    uint16_t *const Qs = smem, *const Os = smem + TS;   // next buffers 2 TS further
     __shared__ __attribute__((aligned(16))) float lse2s[2][QT], Ds[2][QT];
 
     int slot, head;
@@ -303,7 +338,9 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     const int diag = Lk - Lq;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gr = (G == 1) ? 0 : wg / KW;   // row group: the gr-th part of each tile
+    const int w = wg - gr * KW;
     const int il = lane & 15, g = lane >> 4;
     const int jr = il >> 2, jc = 4 * (il & 3);
     const int k0 = kt * KR, wkey0 = k0 + 16 * w, kj = wkey0 + il;
@@ -325,8 +362,8 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         }
     };
     auto store = [&](int buf) {
-        sq.store(Qs[buf], tid);
-        so.store(Os[buf], tid);
+        sq.store(Qs + buf * 2 * TS, tid);
+        so.store(Os + buf * 2 * TS, tid);
         if (tid < QT) {
             lse2s[buf][tid] = lse_pre * kLog2e;
             Ds[buf][tid] = d_pre;
@@ -349,8 +386,10 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         kreg[s][0] = split8(a, b);
         vreg[s][0] = split8(x, y);
     }
-    const int qa = Tile::at(il, 8 * g);
-    const int qb_[2] = {Tile::at(4 * g + jr, jc), Tile::at(4 * g + jr, 16 + jc)};
+    const int row0 = 16 * NIB * gr;   // this group's rows of a tile
+    const int qa = Tile::at(il, 8 * g) + 32 * row0;
+    const int qb_[2] = {Tile::at(4 * g + jr, jc) + 32 * row0,
+                        Tile::at(4 * g + jr, 16 + jc) + 32 * row0};
 
     f32x4 dkacc[NC][1], dvacc[NC][1];   // dK^T, dV^T[16c + 4g + r][kj]
 #pragma unroll
@@ -364,13 +403,14 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     }
     __syncthreads();
     for (int qt = qstart; qt < qstop; ++qt) {
-        const int cur = (qt - qstart) & 1;
-        if (qt + 1 < qstop) {
+        const int cur = (G == 1) ? (qt - qstart) & 1 : 0;
+        if (G == 1 && qt + 1 < qstop) {
             store(cur ^ 1);
             if (qt + 2 < qstop) load(qt + 2);
         }
-        if (wkey0 < klen && (!causal || wkey0 - diag <= qt * QT + QT - 1)) {
-            const uint16_t *Qc = Qs[cur], *Oc = Os[cur];
+        const int rt = qt * QT + row0;
+        if (wkey0 < klen && (!causal || wkey0 - diag <= rt + 16 * NIB - 1)) {
+            const uint16_t *Qc = Qs + cur * 2 * TS, *Oc = Os + cur * 2 * TS;
             f32x4 sacc[NIB][1], pacc[NIB][1];   // S, dP[16ib + 4g + r][kj]
 #pragma unroll
             for (int ib = 0; ib < NIB; ++ib) {
@@ -386,12 +426,12 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                     mfma_split(load_split<Tile>(Oc, o), vreg[s], pacc[ib]);
                 }
             if constexpr (D == 128) sched_reads_ahead<6 * NS * NIB, 12 * NS * NIB, 6, 3, 6, 2>();
-            const bool masked = causal && qt * QT + diag < wkey0 + 15;
-            const int thr = kj - diag - (qt * QT + 4 * g);
+            const bool masked = causal && rt + diag < wkey0 + 15;
+            const int thr = kj - diag - (rt + 4 * g);
 #pragma unroll
             for (int ib = 0; ib < NIB; ++ib) {
-                const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lse2s[cur][16 * ib + 4 * g]);
-                const f32x4 dd = *reinterpret_cast<const f32x4 *>(&Ds[cur][16 * ib + 4 * g]);
+                const f32x4 l2 = *reinterpret_cast<const f32x4 *>(&lse2s[cur][row0 + 16 * ib + 4 * g]);
+                const f32x4 dd = *reinterpret_cast<const f32x4 *>(&Ds[cur][row0 + 16 * ib + 4 * g]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float p = exp2_fast(fmaf(sacc[ib][0][r], scale_log2, -l2[r]));
@@ -415,6 +455,30 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             if constexpr (D == 128) sched_reads_ahead<12 * NC * NIB / 2, 12 * NC * NIB / 2, 6, 6, 6, 3>();
         }
         __syncthreads();   // next tile visible; this tile's buffers free
+        if (G > 1 && qt + 1 < qstop) {
+            store(0);
+            if (qt + 2 < qstop) load(qt + 2);
+            __syncthreads();
+        }
+    }
+    if constexpr (G == 2) {
+        // the second group's sums reach the first through the tile buffers
+        static_assert(sizeof(smem) >= (size_t)KW * 2 * NC * 64 * sizeof(f32x4), "sums fit");
+        f32x4 *x = reinterpret_cast<f32x4 *>(smem) + w * 2 * NC * 64 + lane;
+        if (gr == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                x[64 * 2 * c] = dkacc[c][0];
+                x[64 * (2 * c + 1)] = dvacc[c][0];
+            }
+        }
+        __syncthreads();
+        if (gr == 1) return;   // no barrier follows
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            dkacc[c][0] += x[64 * 2 * c];
+            dvacc[c][0] += x[64 * (2 * c + 1)];
+        }
     }
 
     bool fine = true;
@@ -443,20 +507,33 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-// Grids that fill two workgroups per CU; the fused f32 kernel, which splits the
-// query tiles of a key tile over workgroups, keeps the smaller ones at d <= 64
-// (whole backward, us, that : this: B8 H8 L1024 causal 207 : 175, B4 H16 L2048
-// 1489 : 1100, d = 32 798 : 640; but B2 H6 L1500 186 : 228, B1 H4 L8192 causal
-// 918 : 1056, B4 H8 Lq1024 Lk77 37 : 82).  d = 128 always: 354 -> 205 at B2 H8
-// L1024 causal, 3907 -> 2006 at B4 H16 L2048, against separate f32 kernels.
-bool use_split_bwd(const AttnProblem &p) {
+// Forms.  kWide: four waves of 32 query rows or 16 keys, for grids of two
+// workgroups per CU.  kPair: eight waves in two groups that share a 64-row tile
+// and take half of each streamed 64-row tile, for grids that leave the time to
+// the chain of tiles.  kEight (d = 128): eight waves that share a tile's split.
+//
+// d <= 64, where the alternative is the fused f32 kernel, which splits the query
+// tiles of a key tile over workgroups (whole backward, GPU us, that : this).
+// Wide: B8 H8 L1024 causal 207 : 173, B4 H16 L2048 1489 : 1100, d = 32 798 : 640.
+// Pair, from 448 64-key tiles or with short query sides: B4 H8 L1024 200 : 169,
+// B4 H16 L512 causal 75 : 66, B3 H6 Lq814 Lk1850 221 : 192, B8 H8 L256 causal
+// 42.7 : 32.6; not B2 H6 L1500 (288 tiles) 186 : 224, B1 H4 L2500 179 : 209, B2
+// H6 L1200 causal 86 : 105.
+// d = 128, against separate f32 kernels: pair up to 128 128-row tiles (B2 H8
+// L1024 causal 354 -> 157, four-wave workgroups 198), then eight (B4 H8 L1024
+// 270, pair 316; B4 H16 L2048 3907 -> 2006).
+enum class Form { kNone, kWide, kPair, kEight };
+static Form split_form(const AttnProblem &p) {
     const long BH = (long)p.B * p.H;
-    return p.d == 128 || (cdiv(p.Lq, 128) * BH >= 512 && cdiv(p.Lk, 64) * BH >= 512);
+    if (p.d == 128)
+        return std::max(cdiv(p.Lq, 128), cdiv(p.Lk, 128)) * BH > 128 ? Form::kEight : Form::kPair;
+    const long q64 = cdiv(p.Lq, 64) * BH, k64 = cdiv(p.Lk, 64) * BH;
+    if (cdiv(p.Lq, 128) * BH >= 512 && k64 >= 512) return Form::kWide;
+    if (q64 >= 224 && (k64 >= 448 || (k64 >= 224 && p.Lq <= 512))) return Form::kPair;
+    return Form::kNone;
 }
+bool use_split_bwd(const AttnProblem &p) { return split_form(p) != Form::kNone; }
 
-// d = 128: eight waves share a tile's split once the grid fills the chip with
-// them (dQ at B4 H16 L1024 causal 198 -> 130 us, dK/dV 295 -> 170), four below
-// (B2 H8 L1024 causal: dQ 105 -> 82, dK/dV 144 -> 123).
 hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float *K,
                                const float *V, const float *O, const float *dO, const float *LSE,
                                float *Dws, float *dQ, hipStream_t s) {
@@ -470,12 +547,18 @@ hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float
                                        padded_work_order(p));
         return hipGetLastError();
     };
+    // (none: the caller has no room for the fused kernel's partials)
+    const bool pair = split_form(p) == Form::kPair;
     switch (p.d) {
-    case 32: return go(attn_dq_f32x3<32, 2, 4, 32>, 128, 256);
-    case 64: return go(attn_dq_f32x3<64, 2, 4, 32>, 128, 256);
+    case 32:
+        return pair ? go(attn_dq_f32x3<32, 1, 4, 64, 2>, 64, 512)
+                    : go(attn_dq_f32x3<32, 2, 4, 32, 1>, 128, 256);
+    case 64:
+        return pair ? go(attn_dq_f32x3<64, 1, 4, 64, 2>, 64, 512)
+                    : go(attn_dq_f32x3<64, 2, 4, 32, 1>, 128, 256);
     case 128:
-        return (long)cdiv(p.Lq, 128) * BH >= 256 ? go(attn_dq_f32x3<128, 1, 8, 32>, 128, 512)
-                                                 : go(attn_dq_f32x3<128, 1, 4, 32>, 64, 256);
+        return pair ? go(attn_dq_f32x3<128, 1, 4, 64, 2>, 64, 512)
+                    : go(attn_dq_f32x3<128, 1, 8, 32, 1>, 128, 512);
     default: return hipErrorInvalidValue;
     }
 }
@@ -493,12 +576,17 @@ hipError_t launch_bwd_dkdv_f32x3(const AttnProblem &p, const float *Q, const flo
                                        padded_work_order(p));
         return hipGetLastError();
     };
+    const bool pair = split_form(p) == Form::kPair;
     switch (p.d) {
-    case 32: return go(attn_dkdv_f32x3<32, 4, 32>, 64, 256);
-    case 64: return go(attn_dkdv_f32x3<64, 4, 32>, 64, 256);
+    case 32:
+        return pair ? go(attn_dkdv_f32x3<32, 4, 64, 2>, 64, 512)
+                    : go(attn_dkdv_f32x3<32, 4, 32, 1>, 64, 256);
+    case 64:
+        return pair ? go(attn_dkdv_f32x3<64, 4, 64, 2>, 64, 512)
+                    : go(attn_dkdv_f32x3<64, 4, 32, 1>, 64, 256);
     case 128:
-        return (long)cdiv(p.Lk, 128) * BH >= 256 ? go(attn_dkdv_f32x3<128, 8, 32>, 128, 512)
-                                                 : go(attn_dkdv_f32x3<128, 4, 32>, 64, 256);
+        return pair ? go(attn_dkdv_f32x3<128, 4, 64, 2>, 64, 512)
+                    : go(attn_dkdv_f32x3<128, 8, 32, 1>, 128, 512);
     default: return hipErrorInvalidValue;
     }
 }

@@ -20,6 +20,9 @@ REL = 2e-6
 LARGE = [
     (2, 260, 33, 33, "causal"), (2, 256, 130, 65, "causal"), (2, 256, 65, 193, "causal"),
     (4, 128, 97, 70, "padded"), (2, 260, 64, 64, "full"),
+    # two wave groups: 224 or more 64-row tiles of either side
+    (1, 230, 50, 64, "causal"), (2, 115, 65, 33, "full"), (4, 60, 193, 100, "padded"),
+    (1, 113, 130, 257, "causal"),
 ]
 
 
