@@ -2,16 +2,10 @@
 //
 // The paper's attention archetype is three kernels: a tiled forward, a dQ
 // kernel and a fused dK+dV kernel (Sec. 3.3; Sec. 8 makes the fused dK+dV
-// kernel a compiler invariant; Sec. 7.3 profiles the backward pair).  Here:
+// kernel a compiler invariant; Sec. 7.3 profiles the backward pair).  The
+// forward and the separate dK/dV and dQ kernels run on split bf16 operands
+// (attn_f32x3_*.hip); here:
 //
-//   attn_fwd_f32_ks2  query tile of 32 rows stationary, streams K/V tiles,
-//                     online softmax in base 2, writes O and LSE (natural
-//                     log).  The key tiles are split between two halves of the
-//                     workgroup (four groups: _ks4), which merge their (max,
-//                     sum, O) states through LDS at the end: for grids too
-//                     small to spread evenly over the CUs.  Larger grids,
-//                     d = 128 and the separate dK/dV and dQ kernels run on
-//                     split bf16 operands (attn_f32x3_*.hip).
 //   attn_rowdot_f32   D_i = sum_k dO_ik O_ik (HBM-bound row reduction).
 //   attn_dkdvq_f32    key tile stationary: recomputes P from LSE, then
 //                     dV += P^T dO, dP = dO V^T, dS = P(dP - D), dK += dS^T Q,
@@ -25,9 +19,7 @@
 // which is what the strict contract permits (Sec. 4.2).  Each wave owns 16
 // rows of the stationary tile (one per lane column l%16); the other operand
 // is staged through LDS, 64 rows at a time, and shared by the waves of a
-// workgroup.  The forward kernel copies its K and V tiles with gfx950's
-// direct-to-LDS buffer loads (no staging registers) and fetches the next K
-// tile during P V and the next V tile during S = K Q^T.
+// workgroup.
 //
 // Workgroup order: the 1-D grid is numbered rank-major over heads
 // (id = slot * B*H + head) with rank 0 the tile that has the most work under
@@ -40,8 +32,7 @@
 // XCDs round-robin), so a head's K/V or Q/dO stay in one L2.
 //
 // Masking: an element's offset inside its tile is compared against one
-// per-lane threshold (key length, causal diagonal); the forward kernel skips
-// the comparison on tiles that hold no masked element.
+// per-lane threshold (key length, causal diagonal).
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -53,8 +44,7 @@
 
 // Per-kernel launch configuration: waves per workgroup, minimum waves per
 // SIMD requested from the register allocator (0 = compiler default), and
-// double-buffered LDS for the streamed tile of the backward kernels (the
-// forward kernel always alternates its K and V fetches).  The defaults are
+// double-buffered LDS for the streamed tile.  The defaults are
 // the fastest of sweeps on MI355X at B8 H8 L1024 d64 and B16 H12 L512 d64
 // (double buffering lost there: it halves the workgroups an LDS-heavy CU can
 // hold); they can be overridden at build time.
@@ -74,19 +64,6 @@
 namespace mg {
 namespace {
 
-#ifndef MG_FWD_SPLIT_CFG
-#define MG_FWD_SPLIT_CFG 2, 3, false
-#endif
-#ifndef MG_FWD_SPLIT_KS
-#define MG_FWD_SPLIT_KS 32
-#endif
-#ifndef MG_FWD_SPLIT4_UPTO
-#define MG_FWD_SPLIT4_UPTO 256     // 32-row grids up to this size split their keys four ways...
-#endif
-#ifndef MG_FWD_SPLIT4_MIN_KEYS
-#define MG_FWD_SPLIT4_MIN_KEYS 256 // ...when each group still gets two or more 32-key tiles
-#endif
-
 template <int NW_, int OCC_, bool DB_>
 struct Cfg {
     static constexpr int NW = NW_;             // waves per workgroup
@@ -97,287 +74,8 @@ struct Cfg {
     template <int D> static constexpr int occ() { return D <= 64 ? OCC : 1; }
     static constexpr int NBUF = DB_ ? 2 : 1;   // LDS buffers for the streamed tile
 };
-using FwdSplitCfg = Cfg<MG_FWD_SPLIT_CFG>;   // 32-row tiles, keys split in two
 using DkdvCfg = Cfg<MG_DKDV_CFG>;
 using DkdvqCausalCfg = Cfg<MG_DKDVQ_CAUSAL_CFG>;
-
-// ---------------------------------------------------------------- forward --
-// Query tile of C::ROWS rows stationary (16 per wave); K and V tiles of KS
-// keys (64; 32 in the key-split form, one pair per half) stream through LDS
-// by direct-to-LDS loads.  The next K tile is fetched
-// while the softmax and P V of the current tile run, the next V tile while
-// the next S = K Q^T runs, so each iteration has two barriers and no staging
-// registers:
-//   S(kt) from K | wait V(kt), barrier | fetch K(kt+1) | softmax, P V(kt)
-//   | wait K(kt+1), barrier | fetch V(kt+1)
-template <int D, class C, int KSPLIT>
-__device__ __forceinline__ void fwd_f32_body(const float *__restrict__ Q, const float *__restrict__ K,
-                  const float *__restrict__ V, float *__restrict__ O, float *__restrict__ LSE,
-                  const int32_t *__restrict__ key_len, int H, int Lq, int Lk, int causal,
-                  float scale_log2, int n_qtiles, int BH, int layer, int work_first) {
-    // keys per streamed tile (short, so that four workgroups fit in one CU's LDS)
-    constexpr int KS = MG_FWD_SPLIT_KS;
-    constexpr int DQ = D / 4;    // contraction values per lane in one S chain
-    constexpr int NC = D / 16;   // 16-column blocks of the head dimension
-    constexpr int NJB = KS / 16; // 16-key blocks per streamed tile
-    using Tile = DirectTile<KS, D, C::NW>;
-    static_assert(Tile::kEven, "the vmcnt waits below count kPerWave loads per fetch");
-    constexpr int NL = Tile::kPerWave;   // vector-memory operations per tile fetch
-    static_assert((KSPLIT == 2 || KSPLIT == 4) && C::NW * NC * 256 <= KS * D,
-                  "a key group's O must fit in its K tile");
-    __shared__ __attribute__((aligned(16))) float Ks[KSPLIT][KS * D];
-    __shared__ __attribute__((aligned(16))) float Vs[KSPLIT][KS * D];
-    // m, l of groups 1 .. KSPLIT-1
-    __shared__ float xml[(KSPLIT - 1) * 2 * C::NW * 64];
-
-    int slot, head;
-    if (work_first) {
-        heavy_first_tile(blockIdx.x, n_qtiles, KS, BH, H, Lk, key_len, slot, head);
-    } else {
-        slot = blockIdx.x / BH;
-        head = blockIdx.x - slot * BH;
-    }
-    const int rank = serpentine_rank(slot, n_qtiles, layer);
-    const int qt = causal ? (n_qtiles - 1 - rank) : rank;
-    const int b = head / H;
-    const float *Qh = Q + (size_t)head * Lq * D;
-    const float *Kh = K + (size_t)head * Lk * D;
-    const float *Vh = V + (size_t)head * Lk * D;
-    const int diag = Lk - Lq;   // causal: row i sees keys j <= i + diag
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = wg / C::NW;   // key group of this wave
-    const int w = wg - hh * C::NW;   // row wave within its half
-    const int il = lane & 15;
-    const int g = lane >> 4;
-    const int q0 = qt * C::ROWS;
-    const int qw0 = q0 + 16 * w;   // first query row of this wave
-    const int qi = qw0 + il;
-
-    const int klen = key_limit(key_len, b, Lk);
-    const int kend = causal ? min(klen, q0 + C::ROWS + diag) : klen;
-    const int ntiles = (kend + KS - 1) / KS;
-    // Key split: group h takes key tiles [h*m, min(n, (h+1)*m)) with
-    // m = ceil(n/KSPLIT); every group runs m iterations so that every barrier
-    // is reached by all waves (a group's surplus iterations only wait).
-    const int iters = (ntiles + KSPLIT - 1) / KSPLIT;
-    const int tbeg = hh * iters;
-    const int tend = min(ntiles, tbeg + iters);
-    float *const Ksh = Ks[hh];
-    float *const Vsh = Vs[hh];
-
-    Tile tile;
-    tile.init(w, lane);
-    // LDS float offsets of this lane's operands in key block jb = 0; block jb
-    // adds 16*jb*D (the chunk permutation repeats every 16 rows).
-    int koff[DQ / 4], voffs[4][NC];
-#pragma unroll
-    for (int s4 = 0; s4 < DQ / 4; ++s4) koff[s4] = Tile::at(il, g * DQ + 4 * s4);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) voffs[r][c] = Tile::at(4 * g + r, 16 * c + il);
-    if (tbeg < tend) {
-        tile.issue(Ksh, Kh, tbeg * KS, Lk, w);
-        tile.issue(Vsh, Vh, tbeg * KS, Lk, w);
-    }
-
-    // B operand of S^T = K Q^T: lane holds Q[qi][g*DQ + s] times
-    // scale*log2(e), so that the product is the exponent in base 2.
-    float qreg[DQ];
-#pragma unroll
-    for (int s4 = 0; s4 < DQ / 4; ++s4) {
-        f32x4 v = (qi < Lq) ? *reinterpret_cast<const f32x4 *>(Qh + (size_t)qi * D + g * DQ + 4 * s4)
-                           : zero4();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) qreg[4 * s4 + e] = v[e] * scale_log2;
-    }
-
-    float m_run = -INFINITY;   // running max of this lane's row, base-2 units
-    float l_run = 0.f;         // this lane's share of the row sum
-    f32x4 oacc[NC];            // O^T[16c + 4g + r][qi]
-#pragma unroll
-    for (int c = 0; c < NC; ++c) oacc[c] = zero4();
-
-    wait_vmcnt<NL>();   // K(0) landed (V(0) may still be in flight)
-    __syncthreads();
-    for (int it = 0; it < iters; ++it) {
-        const int kt = tbeg + it;
-        const bool act = kt < tend;   // uniform over the half
-        // 16-key blocks of this tile that hold an allowed key for some row
-        // of this wave (a prefix: keys past the key length, or past the
-        // wave's last row under a causal mask, are masked for every row).
-        // The products of the other blocks are skipped; their scores are
-        // masked below and their probabilities are exactly zero.
-        const int jt = kt * KS;
-        const int kcut = causal ? min(klen, qw0 + 16 + diag) : klen;
-        const int nlive = act ? min(NJB, (kcut - jt + 15) / 16) : 0;
-
-        // S^T[16jb + 4g + r][qi] = sum_k K[j][k] Q[qi][k]
-        f32x4 sacc[NJB];
-#pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) sacc[jb] = zero4();
-        if (nlive == NJB) {
-#pragma unroll
-            for (int s4 = 0; s4 < DQ / 4; ++s4) {
-                f32x4 a[NJB];
-#pragma unroll
-                for (int jb = 0; jb < NJB; ++jb)
-                    a[jb] = *reinterpret_cast<const f32x4 *>(&Ksh[koff[s4] + 16 * jb * D]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int jb = 0; jb < NJB; ++jb)
-                        sacc[jb] = mfma16x16x4(a[jb][e], qreg[4 * s4 + e], sacc[jb]);
-            }
-        } else {
-#pragma unroll
-            for (int jb = 0; jb < NJB; ++jb) {
-                if (jb >= nlive) break;
-#pragma unroll
-                for (int s4 = 0; s4 < DQ / 4; ++s4) {
-                    const f32x4 a =
-                        *reinterpret_cast<const f32x4 *>(&Ksh[koff[s4] + 16 * jb * D]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        sacc[jb] = mfma16x16x4(a[e], qreg[4 * s4 + e], sacc[jb]);
-                }
-            }
-        }
-        wait_vmcnt<0>();   // V(kt) landed
-        __syncthreads();   // every wave is done with K(kt) and sees V(kt)
-        if (kt + 1 < tend) tile.issue(Ksh, Kh, (kt + 1) * KS, Lk, w);
-
-        if (act) {
-            // Element (jb, r) holds key j0 + 16jb + r, allowed iff that offset is
-            // below a per-lane threshold (key length; the query row if causal).
-            // Only tiles that reach past the key length or past the wave's first
-            // query row (causal) hold masked elements.
-            if (jt + KS > klen || (causal && jt + KS - 1 > qw0 + diag)) {
-                const int j0 = jt + 4 * g;
-                const int thr = causal ? min(klen - j0, qi + diag - j0 + 1) : klen - j0;
-    #pragma unroll
-                for (int jb = 0; jb < NJB; ++jb)
-    #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        sacc[jb][r] = (16 * jb + r < thr) ? sacc[jb][r] : -INFINITY;
-            }
-            float mx = -INFINITY;
-    #pragma unroll
-            for (int jb = 0; jb < NJB; ++jb)
-    #pragma unroll
-                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sacc[jb][r]);
-            mx = max_over_groups(mx);
-            const float m_new = fmaxf(m_run, mx);
-            const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-            // Rescaling by 2^(m_run - m_new) is a multiplication by one on every
-            // lane whose maximum did not move; skip it when that holds wave-wide.
-            if (__any(m_new != m_run)) {
-                const float alpha = exp2_fast(m_run - m_use);
-                l_run *= alpha;
-    #pragma unroll
-                for (int c = 0; c < NC; ++c) oacc[c] *= alpha;
-            }
-            m_run = m_new;
-            float psum = 0.f;
-    #pragma unroll
-            for (int jb = 0; jb < NJB; ++jb)
-    #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float p = exp2_fast(sacc[jb][r] - m_use);
-                    sacc[jb][r] = p;
-                    psum += p;
-                }
-            l_run += psum;
-
-            // O^T[16c + 4g + r][qi] += sum_j V[j][16c + il'] P^T[j][qi]
-    #pragma unroll
-            for (int jb = 0; jb < NJB; ++jb) {
-                if (jb >= nlive) break;
-    #pragma unroll
-                for (int r = 0; r < 4; ++r)
-    #pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        oacc[c] = mfma16x16x4(Vsh[voffs[r][c] + 16 * jb * D], sacc[jb][r], oacc[c]);
-            }
-        }
-
-        wait_vmcnt<0>();   // K(kt+1) landed
-        __syncthreads();   // every wave is done with V(kt) and sees K(kt+1)
-        if (kt + 1 < tend) tile.issue(Vsh, Vh, (kt + 1) * KS, Lk, w);
-    }
-
-    float l = sum_over_groups(l_run);
-    // Groups 1 .. KSPLIT-1 hand their (m, l, O) to group 0 through their
-    // own K tiles, which no wave reads any more; group 0 merges the
-    // online-softmax states in group order.
-    if (hh > 0) {
-        float *xo = Ks[hh];
-        float *xm = xml + (hh - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            *reinterpret_cast<f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) = oacc[c];
-        xm[w * 64 + lane] = m_run;
-        xl[w * 64 + lane] = l;
-    }
-    __syncthreads();
-    if (hh > 0) return;
-    float mm = m_run;
-#pragma unroll
-    for (int h = 1; h < KSPLIT; ++h) mm = fmaxf(mm, xml[(h - 1) * 2 * C::NW * 64 + w * 64 + lane]);
-    const float mu = (mm == -INFINITY) ? 0.f : mm;
-    const float a0 = exp2_fast(m_run - mu);
-    l *= a0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) oacc[c] *= a0;
-#pragma unroll
-    for (int h = 1; h < KSPLIT; ++h) {
-        const float *xo = Ks[h];
-        const float *xm = xml + (h - 1) * 2 * C::NW * 64, *xl = xm + C::NW * 64;
-        const float ah = exp2_fast(xm[w * 64 + lane] - mu);
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            oacc[c] += *reinterpret_cast<const f32x4 *>(&xo[((w * NC + c) * 64 + lane) * 4]) * ah;
-        l += xl[w * 64 + lane] * ah;
-    }
-    m_run = mm;
-    if (qi < Lq) {
-        const float inv = (l > 0.f) ? 1.f / l : 0.f;
-        float *orow = O + ((size_t)head * Lq + qi) * D;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            *reinterpret_cast<f32x4 *>(orow + 16 * c + 4 * g) = oacc[c] * inv;
-        if (g == 0)
-            LSE[(size_t)head * Lq + qi] = (l > 0.f) ? (m_run + log2f(l)) * kLn2 : -INFINITY;
-    }
-}
-
-// The kernels: one workgroup per (query tile, head); the _ks2 form splits
-// the key tiles over two halves of the workgroup (grids too small to fill
-// the chip).  Two named kernels over one device body: as one kernel template
-// with the split as a third parameter, hipcc (ROCm 7.2) emitted the host
-// launch stub of only one of the two instances per head size, and the
-// library failed to link.
-#define MG_FWD_F32_ARGS                                                                    \
-    const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, \
-        float *__restrict__ O, float *__restrict__ LSE, const int32_t *__restrict__ key_len, \
-        int H, int Lq, int Lk, int causal, float scale_log2, int n_qtiles, int BH, int layer, \
-        int work_first
-template <int D, class C>
-__global__ __launch_bounds__(2 * C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
-void attn_fwd_f32_ks2(MG_FWD_F32_ARGS) {
-    fwd_f32_body<D, C, 2>(Q, K, V, O, LSE, key_len, H, Lq, Lk, causal, scale_log2, n_qtiles, BH,
-                          layer, work_first);
-}
-template <int D, class C>
-__global__ __launch_bounds__(4 * C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
-void attn_fwd_f32_ks4(MG_FWD_F32_ARGS) {
-    fwd_f32_body<D, C, 4>(Q, K, V, O, LSE, key_len, H, Lq, Lk, causal, scale_log2, n_qtiles, BH,
-                          layer, work_first);
-}
-#undef MG_FWD_F32_ARGS
 
 // ------------------------------------------------- backward: D = rowsum(dO o O)
 template <int D>
@@ -817,41 +515,6 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
-namespace {
-template <class C, class Kern>
-void launch_fwd_f32_as(Kern kern, int ksplit, const AttnProblem &p, const float *Q,
-                       const float *K, const float *V, float *O, float *LSE, hipStream_t s) {
-    const int BH = p.B * p.H;
-    const int nqt = cdiv(p.Lq, C::ROWS);
-    const dim3 grid(nqt * BH), block(C::NT * ksplit);
-    const int ly = causal_rank_layer((const void *)kern, block.x, grid.x, BH, p.causal);
-    kern<<<grid, block, 0, s>>>(Q, K, V, O, LSE, p.key_len, p.H, p.Lq, p.Lk, p.causal,
-                                p.scale * kLog2e, nqt, BH, ly, padded_work_order(p));
-}
-}  // namespace
-
-// The key-split forms: 32-row query tiles, whose keys go to two or four groups
-// of waves, four when even the 32-row grid leaves most CUs without a
-// workgroup and the key side is long.  Taken for small d <= 64 grids (see
-// launch_fwd_f32 for where they end).
-hipError_t launch_fwd_f32_keysplit(const AttnProblem &p, const float *Q, const float *K,
-                                   const float *V, float *O, float *LSE, hipStream_t s) {
-    const bool split4 = (long)cdiv(p.Lq, FwdSplitCfg::ROWS) * p.B * p.H <= MG_FWD_SPLIT4_UPTO &&
-                        p.Lk >= MG_FWD_SPLIT4_MIN_KEYS;
-    auto go = [&](auto ks2, auto ks4) {
-        if (split4)
-            launch_fwd_f32_as<FwdSplitCfg>(ks4, 4, p, Q, K, V, O, LSE, s);
-        else
-            launch_fwd_f32_as<FwdSplitCfg>(ks2, 2, p, Q, K, V, O, LSE, s);
-        return hipGetLastError();
-    };
-    switch (p.d) {
-    case 32: return go(attn_fwd_f32_ks2<32, FwdSplitCfg>, attn_fwd_f32_ks4<32, FwdSplitCfg>);
-    case 64: return go(attn_fwd_f32_ks2<64, FwdSplitCfg>, attn_fwd_f32_ks4<64, FwdSplitCfg>);
-    default: return hipErrorInvalidValue;
-    }
-}
-
 hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const float *dO,
                                  float *Dws, hipStream_t s) {
     const int rows = p.B * p.H * p.Lq;

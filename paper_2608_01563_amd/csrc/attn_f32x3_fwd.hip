@@ -2,16 +2,15 @@
 //
 // Both products take f32 operands as three bf16 parts (tiles_split.h), which
 // keeps the f32 result and needs 96 instead of 256 matrix clocks per 16x16x32
-// block.  Structure as the bf16 and accelerated forwards: 32 queries per wave
-// on 32x32x16 products, K and V tiles of KT keys split as they are staged
-// into LDS, P split straight from the accumulators.
+// block.  K and V tiles of KT keys are split once as they are staged into LDS,
+// P straight from the accumulators; every product runs on 16x16x32.
 //
-// The waves of a workgroup form a QW x KG grid over a tile: QW groups of 32
-// queries, KG groups of KT/KG keys.  With KG = 1 a workgroup takes 128
-// queries, so a split tile serves four waves.  Grids that would leave CUs
-// idle take fewer queries per workgroup and spread a tile's keys over the
-// waves instead; the key groups keep online-softmax states of their own,
-// which the first group merges through LDS at the end.
+// The waves of a workgroup form a QW x KG grid over a tile: QW groups of
+// QB 16-query blocks, KG groups of KT/KG keys.  With KG = 1 a workgroup takes
+// the most queries, so a split tile serves all eight waves.  Smaller grids take
+// fewer queries per workgroup and spread a tile's keys over the waves instead;
+// the key groups keep online-softmax states of their own, which the first
+// group merges through LDS at the end.
 #include <type_traits>
 
 #include "device_common.h"
@@ -350,29 +349,44 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-// Which form (QB, QW, KG, KT): workgroups of eight waves throughout, one tile
-// split for all of them.  Figures: GPU time in us at d = 64 unless named, the
-// f32 matrix-core forward this replaces in front.
+// Which form (QB, QW, KG, KT): a tile is split once for all the waves of a
+// workgroup, eight but for short rows.  Figures: GPU time in us at d = 64 unless named, the
+// f32 matrix-core forwards this replaces in front.
 //   128 rows, one key group, while they give two workgroups per CU: B8 H8 L1024
 //     causal 72.8 -> 54.7, B16 H12 L512 padded 70.8 -> 60.9, B4 H16 L2048 515
 //     -> 341 (d = 32: 280 -> 200); short key sides too (Lk 77: 11.6 -> 11.1,
 //     two key groups 12.3).
 //   64 rows, two key groups, below that: B2 H6 L1500 84.2 -> 73.8, B4 H8 L512
-//     23.8 -> 18.7, B3 H6 L1500 108 -> 74.4, B16 H8 L512 causal 40.6 -> 34.3.
-//   The f32 key-split forms keep grids of fewer than 256 64-row tiles (512 if
-//     causal), where a row's chain of keys matters more than the rate:
-//     B1 H8 L2000 causal 50.1, here 58.7; B2 H4 L1024 causal 24.2, here 32.0.
-//   d = 128 (77 -> the few-rows forward's domain first): two key groups below
-//     192 128-row tiles (B2 H8 L1024 causal 77.8 -> 58.2), then 128 rows
-//     (B4 H16 L1024 causal 161 -> 104), 256 rows of two 16-row blocks per wave
-//     when those fill two rounds (B4 H16 L2048 1061 -> 572, 128 rows: 676).
+//     23.8 -> 18.7, B3 H6 L1500 108 -> 74.4, B16 H8 L512 causal 40.6 -> 34.3,
+//     B1 H4 L2500 97.7 -> 72.0 (four groups 97.7).
+//   32 rows, four key groups, where a row's chain of keys sets the time: one
+//     round of workgroups (at d = 64 the 128-key tiles leave room for one per
+//     CU), two for long causal chains, two to four at d = 32.  B2 H6 L1200
+//     causal 36.8 -> 30.0 (two groups 36.2), B1 H4 L4096 causal 96.2 -> 84.6
+//     (112), B4 H6 L300 11.6 -> 10.9 (12.7); d = 32 B1 H8 L2000 causal 34.1 ->
+//     24.6 (41.4), B2 H8 L1000 23.0 -> 21.2 (23.1).
+//   32 rows, two key groups, four waves for short key sides: with so few tiles
+//   the time is the workgroup's start and end, which more of them per CU hide.
+//   B8 H8 L256 causal 11.5 -> 11.0 (the f32 kernel 10.7), B8 H12 L200 padded
+//     14.0 -> 12.9, d = 32 9.6 -> 8.5, L100 6.4 -> 5.5, B16 H8 L64 6.3 -> 5.1;
+//     but L200 without masks 10.9 -> 13.2, B4 H8 L256 causal 9.1 -> 10.1, B16
+//     H12 L256 padded 23.4 -> 27.1.
+//   d = 128: two key groups below 192 128-row tiles (B2 H8 L1024 causal 77.8 ->
+//     58.2), then 128 rows (B4 H16 L1024 causal 161 -> 104), 256 rows of two
+//     16-row blocks per wave when those fill two rounds (B4 H16 L2048 1061 ->
+//     572, 128 rows: 676).
 hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K, const float *V,
                           float *O, float *LSE, hipStream_t s) {
     const int BH = p.B * p.H;
-    const long rows64 = (long)cdiv(p.Lq, 64) * BH, rows128 = (long)cdiv(p.Lq, 128) * BH;
+    const long rows32 = (long)cdiv(p.Lq, 32) * BH, rows64 = (long)cdiv(p.Lq, 64) * BH,
+               rows128 = (long)cdiv(p.Lq, 128) * BH;
     const bool wide = rows128 >= 512 || (rows64 >= 512 && p.Lk <= 128);
-    if (p.d <= 64 && !wide && rows64 < (p.causal ? 512 : 256) && p.Lk > 64)
-        return launch_fwd_f32_keysplit(p, Q, K, V, O, LSE, s);
+    const bool chain = p.d == 32 ? rows32 <= (p.causal ? 1024 : 512)
+                                 : rows32 <= (p.causal && p.Lk >= 1024 ? 512 : 256);
+    const bool brief =
+        p.Lk <= (p.d == 32 ? 64 : 128) ||
+        (p.Lk <= 256 && rows32 <= 1024 &&
+         (p.d == 32 ? p.key_len && rows32 > 256 : (p.causal || p.key_len) && !chain));
     auto go = [&](auto kern, int rows, int nt) {
         const int nqt = cdiv(p.Lq, rows);
         const dim3 grid(nqt * BH);
@@ -384,8 +398,14 @@ hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K, 
 #define MG_GO(D, QB, QW, KG, KT, DB, OCC) \
     go(attn_fwd_f32x3<D, QB, QW, KG, KT, DB, OCC>, 16 * QB * QW, 64 * QW * KG)
     switch (p.d) {
-    case 32: return wide ? MG_GO(32, 1, 8, 1, 64, false, 4) : MG_GO(32, 1, 4, 2, 64, false, 4);
-    case 64: return wide ? MG_GO(64, 1, 8, 1, 64, false, 4) : MG_GO(64, 1, 4, 2, 64, false, 4);
+    case 32:
+        return wide ? MG_GO(32, 1, 8, 1, 64, false, 4)
+                    : brief ? MG_GO(32, 1, 2, 2, 64, false, 4)
+                    : chain ? MG_GO(32, 1, 2, 4, 128, false, 4) : MG_GO(32, 1, 4, 2, 64, false, 4);
+    case 64:
+        return wide ? MG_GO(64, 1, 8, 1, 64, false, 4)
+                    : brief ? MG_GO(64, 1, 2, 2, 64, false, 3)
+                    : chain ? MG_GO(64, 1, 2, 4, 128, false, 2) : MG_GO(64, 1, 4, 2, 64, false, 4);
     case 128:
         if ((long)cdiv(p.Lq, 256) * BH >= 512) return MG_GO(128, 2, 8, 1, 32, true, 2);
         return rows128 >= 192 ? MG_GO(128, 1, 8, 1, 32, true, 2)

@@ -477,14 +477,21 @@ hipError_t by_shape(const AttnProblem &p, F &&f) {
 // once per block.  Measured against the query-stationary forwards (GPU time,
 // this : those, us):
 //   strict, 256 blocks:  B4 H4 L256 d64 6.8 : 9.2, B1 H8 L512 d128 15.7 : 40.8;
-//     512: B8 H8 L128 d64 7.1 : 6.3, B2 H4 L1024 d64 22 : 24, B1 H4 L2048 d128 93 : 150
+//     512: B1 H4 L2048 d128 93 : 150; d <= 64 for masks that shorten the rows
+//     and short key sides: B2 H8 L400 causal 11.2 : 12.5, B1 H8 L1000 causal
+//     22.0 : 22.7 (d = 32: 13.2 : 13.8), B8 H6 L150 padded 8.3 : 8.7, B4 H6
+//     Lq300 Lk77 6.1 : 6.7, but B4 H6 L300 12.6 : 10.9, B8 H8 L128 7.1 : 6.7,
+//     B16 H8 L64 5.9 : 5.1
 //   bf16, 256: B4 H4 L256 4.0 : 7.2; 512: B2 H4 L1024 9.8 : 16.1, B8 H8 L128
 //     4.1 : 4.9; 1024: B8 H8 L256 8.2 : 6.5
 //   accelerated, 256: B4 H4 L256 5.4 : 8.8; 512: B1 H4 L2048 d128 76 : 54
 bool use_few_rows(const AttnProblem &p, mg_contract_t contract) {
     const bool wide = contract == MG_CONTRACT_FAST_BF16 ||
                       (contract == MG_CONTRACT_STRICT_F32 && p.d == 128);
-    return p.Lq <= kFewRows || row_blocks(p) <= (wide ? 512 : 256);
+    const bool two_rounds =
+        wide || (contract == MG_CONTRACT_STRICT_F32 &&
+                 (p.causal || (p.d == 64 && p.Lk <= (p.key_len ? 160 : 96) && p.Lk > 64)));
+    return p.Lq <= kFewRows || row_blocks(p) <= (two_rounds ? 512 : 256);
 }
 
 hipError_t launch_fwd_few_f32(const AttnProblem &p, const float *Q, const float *K, const float *V,

@@ -33,13 +33,10 @@ struct AttnProblem {
 // ones to whichever CU frees up first.  Non-causal grids get 0.
 int causal_rank_layer(const void *kernel, int block, long grid, int BH, int causal);
 
-// Forward, strict f32: O, LSE from Q, K, V.  The first runs on the bf16 matrix
-// cores, operands split into three bf16 parts, and hands small grids to the
-// second (f32 matrix cores, d <= 64).
+// Forward, strict f32: O, LSE from Q, K, V (on the bf16 matrix cores, operands
+// split into three bf16 parts).
 hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K,
                           const float *V, float *O, float *LSE, hipStream_t s);
-hipError_t launch_fwd_f32_keysplit(const AttnProblem &p, const float *Q, const float *K,
-                                   const float *V, float *O, float *LSE, hipStream_t s);
 // Forward, bf16 inputs/outputs, f32 accumulation.
 hipError_t launch_fwd_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
                            const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s);

@@ -14,7 +14,6 @@
 #include "device_common.h"
 #include "host_runtime.h"
 #include "tiles_bf16.h"
-#include "tiles_direct.h"
 
 namespace mg {
 
@@ -39,9 +38,11 @@ using RowTile = Bf16Tile<64, 128, 4, 32, 2, 3, 1>;     // forward K, dQ K and V
 using TrTile = Bf16Tile<64, 128, 4, 64, 1, 1, 4>;      // forward V
 using Plain32 = Bf16Tile<64, 128, 4, 32, 0, 0, 0>;
 using Plain64 = Bf16Tile<64, 128, 4, 64, 0, 0, 0>;
-// The strict f32 forward's K and V tiles at d = 64 (rows of 256 bytes, the
-// 16-byte chunks of row r permuted by j -> j ^ (r % 16)).
-using F32FwdTile = DirectTile<64, 64, 4>;
+// A tile of unpadded f32 rows at d = 64 (256 bytes, the 16-byte chunks of row r
+// permuted by j -> j ^ (r % 16)): byte offset of element (row, col).
+__host__ __device__ inline int f32_tile_at(int row, int col) {
+    return 256 * row + 16 * ((col >> 2) ^ (row & 15)) + 4 * (col & 3);
+}
 
 // Row and column that lane l reads in the block-layout patterns (7..16).
 __host__ __device__ inline int block_row(int p, int l) {
@@ -64,8 +65,8 @@ __host__ __device__ inline int block_col(int p, int l) {
 // Byte offset of lane `l`'s read in pattern `p` for rows of `rb` bytes.
 __host__ __device__ inline int probe_offset(int p, int l, int rb) {
     const int il = l & 15, g = l >> 4, jr = il >> 2, jc = 4 * (il & 3);
-    if (p == 17) return 4 * F32FwdTile::at(il, 16 * g);     // K: row l%16, group l/16
-    if (p == 18) return 4 * F32FwdTile::at(4 * g, il);      // V: row 4(l/16), word l%16
+    if (p == 17) return f32_tile_at(il, 16 * g);     // K: row l%16, group l/16
+    if (p == 18) return f32_tile_at(4 * g, il);      // V: row 4(l/16), word l%16
     if (p >= 7) {
         const int r = block_row(p, l), e = block_col(p, l);
         switch (p) {

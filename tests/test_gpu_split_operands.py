@@ -41,6 +41,42 @@ def test_large_grids(gpu_lib, B, H, Lq, Lk, mode, d):
         assert rel <= REL, (n, rel)
 
 
+# (B, H, Lq, Lk, mode): the forward's forms of 32 query rows, four key groups
+# (long chains) and two (short key sides), above the few-rows kernel's limit
+SMALL = [
+    (2, 6, 1100, 1100, "causal"), (1, 8, 600, 301, "full"), (1, 8, 523, 33, "full"),
+    (8, 8, 250, 250, "causal"), (8, 12, 150, 150, "padded"), (16, 9, 66, 61, "full"),
+    (4, 8, 300, 127, "full"), (4, 8, 261, 129, "full"),
+]
+
+
+@pytest.mark.parametrize("d", [32, 64])
+@pytest.mark.parametrize("B,H,Lq,Lk,mode", SMALL)
+def test_small_grids(gpu_lib, B, H, Lq, Lk, mode, d):
+    test_large_grids(gpu_lib, B, H, Lq, Lk, mode, d)
+
+
+@pytest.mark.parametrize("d", [32, 64])
+@pytest.mark.parametrize("H,Lq,Lk", [(8, 600, 301), (40, 257, 61)])
+def test_small_grids_carry_infinities(gpu_lib, H, Lq, Lk, d):
+    """An infinite value entry: its column is infinite, the rest is right."""
+    import torch
+    import paper_2608_01563_amd as mg
+    say("split operands small grid, infinity, H=%d Lq=%d Lk=%d d=%d" % (H, Lq, Lk, d))
+    g = torch.Generator().manual_seed(Lk)
+    Q = torch.randn(1, H, Lq, d, generator=g)
+    K, V = torch.randn(1, H, Lk, d, generator=g), torch.randn(1, H, Lk, d, generator=g)
+    V[0, 1, 20, 5] = np.inf
+    O, LSE = mg.attention_forward(Q.cuda(), K.cuda(), V.cuda(), causal=False, scale=d ** -0.5)
+    S = d ** -0.5 * torch.matmul(Q.double(), K.double().transpose(-1, -2).contiguous())
+    ref = torch.matmul(torch.softmax(S, -1), V.double())
+    O = O.cpu().double()
+    assert torch.isposinf(O[0, 1, :, 5]).all()
+    O[0, 1, :, 5] = ref[0, 1, :, 5] = 0
+    assert (O - ref).norm() / ref.norm() <= REL
+    assert (LSE.cpu() - torch.logsumexp(S, -1)).abs().max() <= 1e-5
+
+
 def plain(Q, K, V, dO, scale):
     """The equations in f64 torch, infinities and NaN carried as they come."""
     import torch
