@@ -518,7 +518,8 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // Pair, from 448 64-key tiles or with short query sides: B4 H8 L1024 200 : 169,
 // B4 H16 L512 causal 75 : 66, B3 H6 Lq814 Lk1850 221 : 192, B8 H8 L256 causal
 // 42.7 : 32.6; not B2 H6 L1500 (288 tiles) 186 : 224, B1 H4 L2500 179 : 209, B2
-// H6 L1200 causal 86 : 105.
+// H6 L1200 causal 86 : 105; nor one tile a head, where the fused kernel is the
+// whole backward: B16 H16 L64 causal 13.5 : 17.6 (Lq128 Lk60 29.1 : 26.5).
 // d = 128, against separate f32 kernels: pair up to 128 128-row tiles (B2 H8
 // L1024 causal 354 -> 157, four-wave workgroups 198), then eight (B4 H8 L1024
 // 270, pair 316; B4 H16 L2048 3907 -> 2006).
@@ -529,6 +530,7 @@ static Form split_form(const AttnProblem &p) {
         return std::max(cdiv(p.Lq, 128), cdiv(p.Lk, 128)) * BH > 128 ? Form::kEight : Form::kPair;
     const long q64 = cdiv(p.Lq, 64) * BH, k64 = cdiv(p.Lk, 64) * BH;
     if (cdiv(p.Lq, 128) * BH >= 512 && k64 >= 512) return Form::kWide;
+    if (p.Lq <= 64 && p.Lk <= 64) return Form::kNone;
     if (q64 >= 224 && (k64 >= 448 || (k64 >= 224 && p.Lq <= 512))) return Form::kPair;
     return Form::kNone;
 }
