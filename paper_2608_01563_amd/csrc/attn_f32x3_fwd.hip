@@ -58,7 +58,7 @@ __device__ __noinline__ void fwd_rows_plain(const float *Q, const float *K, cons
 #pragma unroll
         for (int e = 0; e < NE; ++e)
             if (on) O[(size_t)i * D + 64 * e + lane] = o[e] * inv;
-        if (lane == 0) LSE[i] = (l > 0.f) ? (m + log2f(l)) * kLn2 : -INFINITY;
+        if (lane == 0) LSE[i] = row_lse(m, l);
     }
 }
 
@@ -326,7 +326,7 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         const int q = qi + 16 * qb;
         if (q < Lq) {
             const float inv = (l[qb] > 0.f) ? 1.f / l[qb] : 0.f;
-            const float lse = (l[qb] > 0.f) ? (m_run[qb] + log2f(l[qb])) * kLn2 : -INFINITY;
+            const float lse = row_lse(m_run[qb], l[qb]);
             float chk = (l[qb] > 0.f) ? lse : l[qb];   // 0 or NaN where l is not positive
             float *orow = Oh + (size_t)q * D;
 #pragma unroll

@@ -99,7 +99,7 @@ __device__ __forceinline__ void merge_and_store(const float *xo, const float (*m
             o += *reinterpret_cast<const f32x4 *>(&xo[state_at<DV>(w, q, c4)]) * a;
         }
         store(q, 4 * c4, o * ((l > 0.f) ? 1.f / l : 0.f));
-        if (LSE != nullptr && c4 == 0) LSE[q] = (l > 0.f) ? (m + log2f(l)) * kLn2 : -INFINITY;
+        if (LSE != nullptr && c4 == 0) LSE[q] = row_lse(m, l);
     }
 }
 

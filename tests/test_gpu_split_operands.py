@@ -77,6 +77,29 @@ def test_small_grids_carry_infinities(gpu_lib, H, Lq, Lk, d):
     assert (LSE.cpu() - torch.logsumexp(S, -1)).abs().max() <= 1e-5
 
 
+@pytest.mark.parametrize("B,H,Lq,Lk,d,mode", [
+    (2, 6, 1500, 1500, 64, "full"), (1, 16, 1587, 1587, 32, "full"),   # key groups
+    (2, 8, 1024, 1024, 128, "causal"), (8, 8, 1024, 1024, 64, "causal"),
+    (2, 4, 5, 1364, 64, "full"), (2, 6, 1, 1521, 128, "full"),         # few rows
+])
+def test_lse_rounds_once(gpu_lib, B, H, Lq, Lk, d, mode):
+    """LSE of long rows is within the rounding of its last operations: half an
+    ulp of a value of [4, 8), 2^-22 at most and 2^-22 / sqrt(3) = 1.4e-7 on
+    average, 2.3e-8 of a value of 6 and more; 2^-25 leaves room for the scores'
+    own error.  Rounded at every step of (m + log2 l) ln 2 it is 5e-8."""
+    import torch
+    import paper_2608_01563_amd as mg
+    say("LSE B=%d H=%d Lq=%d Lk=%d d=%d %s" % (B, H, Lq, Lk, d, mode))
+    g = torch.Generator(device="cuda").manual_seed(Lq + Lk)
+    Q, K, V = (torch.randn(B, H, L, d, generator=g, device="cuda") for L in (Lq, Lk, Lk))
+    _, LSE = mg.attention_forward(Q, K, V, causal=mode == "causal", scale=d ** -0.5)
+    S = d ** -0.5 * torch.matmul(Q.double(), K.double().transpose(-1, -2).contiguous())
+    if mode == "causal":
+        S += torch.full((Lq, Lk), -np.inf, dtype=torch.float64, device="cuda").triu(1 + Lk - Lq)
+    ref = torch.logsumexp(S, -1)
+    assert ((LSE.double() - ref).norm() / ref.norm()).item() <= 2.0 ** -25
+
+
 def plain(Q, K, V, dO, scale):
     """The equations in f64 torch, infinities and NaN carried as they come."""
     import torch
