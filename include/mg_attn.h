@@ -18,10 +18,13 @@
  *   MG_CONTRACT_STRICT_F32  every tensor f32; f32 products and f32
  *                           accumulation (the paper's --strict mode).  Small
  *                           problems multiply on f32 matrix cores; large ones
- *                           and d = 128 take each f32 operand as the sum of
- *                           three bf16 parts (24 significant bits) and six
- *                           bf16 matrix products per f32 product, with no
- *                           larger error against 64 bits.
+ *                           and d = 128 take each f32 operand, scaled by a
+ *                           power of two so that no part underflows, as the
+ *                           sum of three bf16 parts (24 significant bits) and
+ *                           six bf16 matrix products per f32 product, with no
+ *                           larger error against 64 bits.  Rows that the parts
+ *                           cannot carry (infinities, NaN, operands above
+ *                           2^103, sums above 2^79) are recomputed in f32.
  *   MG_CONTRACT_FAST_BF16   Q,K,V,O,dO,dQ,dK,dV are bf16; products run on
  *                           bf16 matrix cores with f32 accumulation, P and dS
  *                           are rounded to bf16 (nearest even) as operands;

@@ -22,8 +22,9 @@
  *
  * Contracts: MG_CONTRACT_STRICT_F32 and MG_CONTRACT_ACCELERATED (whose
  * backward matrices stay f32, Sec. 4.2) both form f32 products (each f32
- * operand as the sum of three bf16 parts, six bf16 matrix products per f32
- * product) with f32 accumulation and give identical results; MG_CONTRACT_FAST_BF16 returns
+ * operand, scaled by a power of two, as the sum of three bf16 parts, six bf16
+ * matrix products per f32 product; outputs these cannot carry are recomputed in
+ * f32) with f32 accumulation and give identical results; MG_CONTRACT_FAST_BF16 returns
  * MG_ERR_UNSUPPORTED.  Status codes, the error detail and the per-launch
  * timing hooks are those of mg_attn.h.
  *

@@ -9,6 +9,10 @@
 // pair of the fused kernel in attn_f32.hip, and drop that kernel's dQ partials
 // (written and read back, 151 MB at B8 H8 L1024 d64), their reduction and the
 // separate D launch.
+//
+// Operands are split as 2^24 times their values (tiles_split.h): S and dP come
+// out 2^48 times, the factors below bring dS to 2^24 times (its split) and the
+// results back.
 #include <algorithm>
 
 #include "device_common.h"
@@ -158,12 +162,15 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
 #pragma unroll
                 for (int e = 0; e < 4; ++e) dsum = fmaf(x[e], u[e], fmaf(y[e], v[e], dsum));
             }
-            qreg[s][qb] = split8(a, b);
-            oreg[s][qb] = split8(x, y);
+            qreg[s][qb] = split8_up(a, b);
+            oreg[s][qb] = split8_up(x, y);
         }
         Di[qb] = sum_over_groups(dsum);
         if (q < Lq && g == 0 && gr == 0) Dws[(size_t)head * Lq + q] = Di[qb];
     }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) Di[qb] *= kUp;
+    const float s_scale = scale_log2 * kDownProduct;
     const int key0 = 16 * NKB * gr;   // this group's keys of a tile
     const int ka = Tile::at(il, 8 * g) + 32 * key0;
     const int kt_[2] = {Tile::at(4 * g + jr, jc) + 32 * key0,
@@ -193,7 +200,7 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         const int jt = kt * KT + key0;
         if (jt < klen && (!causal || jt <= qw0 + WQ - 1 + diag)) {
             const uint16_t *Kc = Ks + cur, *Vc = Vs + cur;
-            f32x4 sacc[NKB][QB], pacc[NKB][QB];   // S^T, dP^T[16kb + 4g + r][qi + 16qb]
+            f32x4 sacc[NKB][QB], pacc[NKB][QB];   // 2^48 S^T, dP^T[16kb + 4g + r][qi + 16qb]
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
@@ -211,7 +218,7 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                 }
             // two products' operand reads in flight (d = 128: 89 -> 82 us at B2 H8 L1024)
             sched_reads_ahead<6 * NS * NKB, 12 * QB * NS * NKB, 6, 3, 6 * QB, 0>();
-            // dS^T = P^T (dP^T - D), P^T = exp2(S^T * scale*log2e - LSE*log2e)
+            // 2^24 dS^T = P^T 2^24 (dP^T - D), P^T = exp2(S^T * scale*log2e - LSE*log2e)
             const bool masked = jt + 16 * NKB > klen || (causal && jt + 16 * NKB - 1 > qw0 + diag);
             const int j0 = jt + 4 * g;
 #pragma unroll
@@ -221,8 +228,8 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                 for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float p = exp2_fast(fmaf(sacc[kb][qb][r], scale_log2, -lse2[qb]));
-                        pacc[kb][qb][r] = p * (pacc[kb][qb][r] - Di[qb]);
+                        const float p = exp2_fast(fmaf(sacc[kb][qb][r], s_scale, -lse2[qb]));
+                        pacc[kb][qb][r] = p * fmaf(pacc[kb][qb][r], kDown, -Di[qb]);
                     }
                 if (masked) {
 #pragma unroll
@@ -290,7 +297,7 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             float *row = dQ + qoff + (size_t)q * D;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const f32x4 v = dqacc[c][qb] * scale;
+                const f32x4 v = dqacc[c][qb] * kDownProduct * scale;
                 *reinterpret_cast<f32x4 *>(row + 16 * c + 4 * g) = v;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) chk = fmaf(v[e], 0.f, chk);   // NaN if not finite
@@ -366,7 +373,7 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         so.store(Os + buf * 2 * TS, tid);
         if (tid < QT) {
             lse2s[buf][tid] = lse_pre * kLog2e;
-            Ds[buf][tid] = d_pre;
+            Ds[buf][tid] = d_pre * kUp;
         }
     };
     if (qstart < qstop) load(qstart);
@@ -383,9 +390,10 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             x = *reinterpret_cast<const f32x4 *>(V + off);
             y = *reinterpret_cast<const f32x4 *>(V + off + 4);
         }
-        kreg[s][0] = split8(a, b);
-        vreg[s][0] = split8(x, y);
+        kreg[s][0] = split8_up(a, b);
+        vreg[s][0] = split8_up(x, y);
     }
+    const float s_scale = scale_log2 * kDownProduct;
     const int row0 = 16 * NIB * gr;   // this group's rows of a tile
     const int qa = Tile::at(il, 8 * g) + 32 * row0;
     const int qb_[2] = {Tile::at(4 * g + jr, jc) + 32 * row0,
@@ -411,7 +419,7 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         const int rt = qt * QT + row0;
         if (wkey0 < klen && (!causal || wkey0 - diag <= rt + 16 * NIB - 1)) {
             const uint16_t *Qc = Qs + cur * 2 * TS, *Oc = Os + cur * 2 * TS;
-            f32x4 sacc[NIB][1], pacc[NIB][1];   // S, dP[16ib + 4g + r][kj]
+            f32x4 sacc[NIB][1], pacc[NIB][1];   // 2^48 S, dP[16ib + 4g + r][kj]
 #pragma unroll
             for (int ib = 0; ib < NIB; ++ib) {
                 sacc[ib][0] = zero4();
@@ -434,10 +442,10 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                 const f32x4 dd = *reinterpret_cast<const f32x4 *>(&Ds[cur][row0 + 16 * ib + 4 * g]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    float p = exp2_fast(fmaf(sacc[ib][0][r], scale_log2, -l2[r]));
+                    float p = exp2_fast(fmaf(sacc[ib][0][r], s_scale, -l2[r]));
                     if (masked && 16 * ib + r < thr) p = 0.f;
-                    sacc[ib][0][r] = p;
-                    pacc[ib][0][r] = p * (pacc[ib][0][r] - dd[r]);
+                    sacc[ib][0][r] = p * kUp;
+                    pacc[ib][0][r] = p * fmaf(pacc[ib][0][r], kDown, -dd[r]);
                 }
             }
             // dV^T[16c + .][kj] += dO^T[16c + il'][i] P[i][kj]; dK^T likewise with Q, dS
@@ -488,8 +496,8 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         float chk = 0.f;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const f32x4 a = keep ? dkacc[c][0] * scale : zero4();
-            const f32x4 b = keep ? dvacc[c][0] : zero4();
+            const f32x4 a = keep ? dkacc[c][0] * kDownProduct * scale : zero4();
+            const f32x4 b = keep ? dvacc[c][0] * kDownProduct : zero4();
             *reinterpret_cast<f32x4 *>(dkrow + 16 * c + 4 * g) = a;
             *reinterpret_cast<f32x4 *>(dvrow + 16 * c + 4 * g) = b;
 #pragma unroll

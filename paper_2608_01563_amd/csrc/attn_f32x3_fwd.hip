@@ -121,7 +121,8 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         sk.load(Kh, 0, klen, tid);
         sv.load(Vh, 0, klen, tid);
     }
-    // B operand of S^T = K Q^T: parts of Q[qi + 16qb][32s + 8g + e] * scale*log2(e).
+    // B operand of S^T = K Q^T: parts of kUp Q[qi + 16qb][32s + 8g + e] * scale*log2(e).
+    const float q_scale = scale_log2 * kUp;
     Split8 qreg[NS][QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
@@ -130,8 +131,8 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             f32x4 a = zero4(), b = zero4();
             if (qi + 16 * qb < Lq) {
                 const float *qp = Qh + (size_t)(qi + 16 * qb) * D + 32 * s + 8 * g;
-                a = *reinterpret_cast<const f32x4 *>(qp) * scale_log2;
-                b = *reinterpret_cast<const f32x4 *>(qp + 4) * scale_log2;
+                a = *reinterpret_cast<const f32x4 *>(qp) * q_scale;
+                b = *reinterpret_cast<const f32x4 *>(qp + 4) * q_scale;
             }
             qreg[s][qb] = split8(a, b);
         }
@@ -141,8 +142,9 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     const int ka = Tile::at(il, 8 * g) + 32 * k0w;
     const int va[2] = {Tile::at(4 * g + jr, jc) + 32 * k0w, Tile::at(4 * g + jr, 16 + jc) + 32 * k0w};
 
+    // P stays unscaled: at most 2^kSlack, it loses no bits that reach O.
     float m_run[QB], l_run[QB];   // base-2 units
-    f32x4 oacc[NC][QB];           // O^T[16c + 4g + r][qi + 16qb]
+    f32x4 oacc[NC][QB];           // kUp O^T[16c + 4g + r][qi + 16qb]
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         m_run[qb] = -INFINITY;
@@ -176,7 +178,7 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
         }
         // some key of the share is allowed for some query of the wave
         const bool live = jw < klen && (!causal || jw <= qw0 + WQ - 1 + diag);
-        f32x4 sacc[NKB][QB];   // S^T[16kb + 4g + r][qi + 16qb]
+        f32x4 sacc[NKB][QB];   // kUp^2 S^T[16kb + 4g + r][qi + 16qb]
         if (live) {
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
@@ -219,7 +221,7 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                     mx[qb] = max3_f32(mx[qb], sacc[x >> 2][qb][x & 3],
                                       sacc[(x + 1) >> 2][qb][(x + 1) & 3]);
                 mx[qb] = max3_f32(mx[qb], sacc[NKB - 1][qb][3], sacc[NKB - 1][qb][3]);
-                mx[qb] = max_over_groups(mx[qb]);
+                mx[qb] = max_over_groups(mx[qb]) * kDownProduct;
                 grew = grew || mx[qb] - m_run[qb] > kSlack;
             }
             // m is only an offset, at most kSlack below the true maximum (see
@@ -245,7 +247,7 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                 for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float p = exp2_fast(sacc[kb][qb][r] - m2);
+                        const float p = exp2_fast(fmaf(sacc[kb][qb][r], kDownProduct, -m2));
                         sacc[kb][qb][r] = p;
                         psum += p;
                     }
@@ -325,9 +327,11 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     for (int qb = 0; qb < QB; ++qb) {
         const int q = qi + 16 * qb;
         if (q < Lq) {
-            const float inv = (l[qb] > 0.f) ? 1.f / l[qb] : 0.f;
+            const float inv = (l[qb] > 0.f) ? kDown / l[qb] : 0.f;
             const float lse = row_lse(m_run[qb], l[qb]);
-            float chk = (l[qb] > 0.f) ? lse : l[qb];   // 0 or NaN where l is not positive
+            // l is 0 where the row sees no key, else only if every score is -inf
+            const bool sees = (causal ? min(klen, q + diag + 1) : klen) > 0;
+            float chk = sees ? lse : 0.f;
             float *orow = Oh + (size_t)q * D;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {

@@ -92,10 +92,10 @@ struct ConvLds {
     uint16_t A[2][kTile], B[2][kTile];   // double-buffered operands
 };
 
-// Four f32 into the three planes at u16 offset o (8-byte stores), or at four
-// separate offsets.
+// kUp times four f32 into the three planes at u16 offset o (8-byte stores), or
+// at four separate offsets.
 __device__ __forceinline__ void store_split4(uint16_t *t, int o, f32x4 v) {
-    const float x[4] = {v[0], v[1], v[2], v[3]};
+    const float x[4] = {v[0] * kUp, v[1] * kUp, v[2] * kUp, v[3] * kUp};
     uint32_t p[3][2];
     split_pairs<2>(x, p);
 #pragma unroll
@@ -104,7 +104,7 @@ __device__ __forceinline__ void store_split4(uint16_t *t, int o, f32x4 v) {
             (uint64_t)p[k][0] | ((uint64_t)p[k][1] << 32);
 }
 __device__ __forceinline__ void store_split4(uint16_t *t, const int (&o)[4], f32x4 v) {
-    const float x[4] = {v[0], v[1], v[2], v[3]};
+    const float x[4] = {v[0] * kUp, v[1] * kUp, v[2] * kUp, v[3] * kUp};
     uint32_t p[3][2];
     split_pairs<2>(x, p);
 #pragma unroll
@@ -115,7 +115,7 @@ __device__ __forceinline__ void store_split4(uint16_t *t, const int (&o)[4], f32
 }
 
 // acc[i] += A[16i + .][:] B[:][.] over one 32-deep step, six
-// products of bf16 parts each.
+// products of bf16 parts each (kUp^2 times the sum).
 __device__ __forceinline__ void mma_step(f32x4 (&acc)[2], const Split8 (&a)[2], const Split8 &b) {
     constexpr int I[6] = {2, 1, 1, 0, 0, 0}, J[6] = {0, 1, 0, 2, 1, 0};
 #pragma unroll
@@ -305,7 +305,7 @@ __device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int k = k0 + 32 * wm + 16 * i + 4 * g + r;
-            if (k < p.K && j < RSC) dst[(size_t)k * RSC + j] = acc[i][r];
+            if (k < p.K && j < RSC) dst[(size_t)k * RSC + j] = acc[i][r] * kDownProduct;
             chk = fmaf(acc[i][r], 0.f, chk);   // NaN if not finite
         }
     if (!__all(finite_f32(chk))) {
@@ -547,7 +547,7 @@ __device__ __forceinline__ void dgrad_tile(int bid, ConvLds &L, const DgradJob &
             const int on = fdiv(mo, job.HWc), oij = mo - on * HWc;
             const int oi = fdiv(oij, job.Wc_), oj = oij - oi * job.Wc;
             const size_t pix = ((size_t)on * p.H + job.a + p.sh * oi) * p.W + job.b + p.sw * oj;
-            if (c < p.C) dst[pix * p.C + c] = acc[ii][r];
+            if (c < p.C) dst[pix * p.C + c] = acc[ii][r] * kDownProduct;
             chk = fmaf(acc[ii][r], 0.f, chk);   // NaN if not finite
         }
     if (!__all(finite_f32(chk))) {

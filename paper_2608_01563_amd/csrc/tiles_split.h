@@ -17,17 +17,24 @@
 // sixteen products before it rounds.  At a sixteenth of the bf16 rate the f32
 // instructions take 256 clocks for a 16x16x32 block, the six terms 96.
 //
-// Range: bf16 has f32's exponents.  Parts below the smallest normal number
-// (2^-126) are flushed, so operands below about 2^-110 lose low bits (2.7e-5
-// relative at 1e-36).  An infinite or NaN operand, or one that rounds to an
-// infinite h (above 3.39e38), makes the sum NaN; the kernels check their
-// results and recompute rows that are not finite with plain f32 arithmetic.
+// Range: bf16 has f32's exponents, and parts below the smallest normal number
+// (2^-126) are flushed.  So the parts are those of 2^24 x: the lowest bit of
+// any f32, 2^-149, then lies in a normal part, and a product is 2^48 x y, which
+// the kernels undo by exact factors (unscaled, operands below 2^-102 lose low
+// bits: V about 2^-118, relative error of O 8.8e-6 against 3.3e-7).  An infinite
+// or NaN operand, one above 2^103, or a sum above 2^79 makes the result
+// infinite or NaN; the kernels check their results and recompute what is not
+// finite with plain f32 arithmetic.
 #pragma once
 
 #include "device_common.h"
 #include "tiles_bf16.h"
 
 namespace mg {
+
+constexpr float kUp = 0x1p24f;            // operands are split as kUp x ...
+constexpr float kDown = 0x1p-24f;
+constexpr float kDownProduct = 0x1p-48f;  // ... so products carry 2^48
 
 struct Split8 {
     bf16x8 p[3];   // h, m, l of eight values
@@ -85,6 +92,9 @@ __device__ __forceinline__ Split8 split8(f32x4 a, f32x4 b) {
     return split8(x);
 }
 
+// Parts of an operand as it lies in memory, kUp times it.
+__device__ __forceinline__ Split8 split8_up(f32x4 a, f32x4 b) { return split8(a * kUp, b * kUp); }
+
 // acc[n] += a * b[n] in six terms, smallest first; consecutive instructions
 // share an operand.
 template <int N>
@@ -97,7 +107,7 @@ __device__ __forceinline__ void mfma_split(const Split8 &a, const Split8 (&b)[N]
 }
 
 // An f32 [ROWS][D] tile that passes through registers, is split and lands in
-// LDS as three planes of TILE's layout (a Bf16Tile of the same shape), plane
+// LDS (kUp times it) as three planes of TILE's layout (a Bf16Tile of the same shape), plane
 // k at dst + k * TILE::kSize.  A thread moves chunks of eight floats of a row:
 // two 16-byte buffer loads, three 16-byte LDS stores.  Rows at or beyond L
 // arrive as zeros (the descriptor ends at row L).
@@ -126,7 +136,7 @@ struct SplitStager {
             if (!kExact && f >= kChunks) continue;
             const int r = f / kCpr;
             const int o = TILE::at(r, 8 * (f - r * kCpr));
-            const Split8 s = split8(buf[u][0], buf[u][1]);
+            const Split8 s = split8_up(buf[u][0], buf[u][1]);
 #pragma unroll
             for (int k = 0; k < 3; ++k)
                 *reinterpret_cast<u32x4 *>(dst + k * TILE::kSize + o) =

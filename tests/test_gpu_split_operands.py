@@ -114,6 +114,54 @@ def plain(Q, K, V, dO, scale):
             "dV": torch.matmul(P.transpose(-1, -2).contiguous(), dO)}
 
 
+# (B, H, L, d): forward and backward forms: 128 rows; 64 rows, wave groups; 32
+# rows and four groups before the f32 backward; d = 128 in both
+FORMS = [(8, 64, 130, 64), (4, 60, 193, 64), (1, 8, 700, 64), (8, 64, 130, 32), (8, 64, 130, 128),
+         (1, 30, 200, 128)]
+
+
+@pytest.mark.parametrize("B,H,L,d", FORMS)
+@pytest.mark.parametrize("what", ["Q", "K", "V", "dO"])
+def test_small_operands_keep_their_bits(gpu_lib, what, B, H, L, d):
+    """An operand of about 2^-120, whose lower parts would fall below bf16's
+    smallest normal number, gives results as close as one of 1."""
+    import torch
+    import paper_2608_01563_amd as mg
+    say("split operands, %s small, B=%d H=%d L=%d d=%d" % (what, B, H, L, d))
+    g = torch.Generator(device="cuda").manual_seed(L + d)
+    t = {n: torch.randn(B, H, L, d, generator=g, device="cuda") for n in ("Q", "K", "V", "dO")}
+    t[what] *= 2.0 ** -120
+    Q, K, V, dO = t["Q"], t["K"], t["V"], t["dO"]
+    O, LSE = mg.attention_forward(Q, K, V, causal=False, scale=d ** -0.5)
+    got = dict(zip(("dQ", "dK", "dV"),
+                   mg.attention_backward(Q, K, V, O, LSE, dO, causal=False, scale=d ** -0.5)))
+    got.update(O=O, LSE=LSE)
+    ref = plain(Q, K, V, dO, d ** -0.5)
+    for n, v in got.items():
+        rel = ((v.double() - ref[n]).norm() / ref[n].norm()).item()
+        assert rel <= REL, (n, rel)
+
+
+@pytest.mark.parametrize("which", ["X", "W", "dY"])
+@pytest.mark.parametrize("K", [36, 50])   # 16- and 4-byte loads
+def test_small_operands_keep_their_bits_in_convolutions(gpu_lib, K, which):
+    import torch
+    import paper_2608_01563_amd as mg
+    say("split operands convolution, %s small, K=%d" % (which, K))
+    g = torch.Generator(device="cuda").manual_seed(K)
+    t = {"X": torch.randn(2, 9, 9, K, generator=g, device="cuda"),
+         "W": torch.randn(K, 3, 3, K, generator=g, device="cuda"),
+         "dY": torch.randn(2, 9, 9, K, generator=g, device="cuda")}
+    t[which] *= 2.0 ** -120
+    got = mg.conv2d_backward(t["X"], t["W"], t["dY"], pad=(1, 1))
+    x, w = (t[n].double().cpu().permute(0, 3, 1, 2).requires_grad_() for n in ("X", "W"))
+    torch.nn.functional.conv2d(x, w, padding=1).backward(t["dY"].double().cpu().permute(0, 3, 1, 2))
+    for n, v, r in zip(("dX", "dW"), got, (x.grad, w.grad)):
+        r = r.permute(0, 2, 3, 1)
+        rel = ((v.double().cpu() - r).norm() / r.norm()).item()
+        assert rel <= REL, (n, rel)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("what,value", [("V", np.inf), ("V", -np.inf), ("V", np.nan),
                                         ("dO", np.inf), ("dO", 3.4e38), ("V", 3.4e38),
