@@ -24,7 +24,8 @@
  *                           six bf16 matrix products per f32 product, with no
  *                           larger error against 64 bits.  Rows that the parts
  *                           cannot carry (infinities, NaN, operands above
- *                           2^103, sums above 2^79) are recomputed in f32.
+ *                           2^103, sums above 2^79) are recomputed in f32,
+ *                           which takes up to three times as long.
  *   MG_CONTRACT_FAST_BF16   Q,K,V,O,dO,dQ,dK,dV are bf16; products run on
  *                           bf16 matrix cores with f32 accumulation, P and dS
  *                           are rounded to bf16 (nearest even) as operands;

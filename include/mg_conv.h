@@ -24,7 +24,7 @@
  * backward matrices stay f32, Sec. 4.2) both form f32 products (each f32
  * operand, scaled by a power of two, as the sum of three bf16 parts, six bf16
  * matrix products per f32 product; outputs these cannot carry are recomputed in
- * f32) with f32 accumulation and give identical results; MG_CONTRACT_FAST_BF16 returns
+ * f32, up to four times as long) with f32 accumulation and give identical results; MG_CONTRACT_FAST_BF16 returns
  * MG_ERR_UNSUPPORTED.  Status codes, the error detail and the per-launch
  * timing hooks are those of mg_attn.h.
  *

@@ -17,76 +17,97 @@
 
 #include "device_common.h"
 #include "launch.h"
+#include "rows_f32.h"
 #include "tiles_split.h"
 #include "work_order.h"
 
 namespace mg {
 namespace {
 
-// Wave-wide sum of a lane's products over the head dimension.
+// Rows (dQ) or keys (dK, dV) whose fast result is not finite, in plain f32
+// (rows_f32.h): 16 at a time.  Ends early where every value is NaN.
 template <int D>
-__device__ __forceinline__ float wave_dot(const float *a, const float *b, int lane) {
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < (D + 63) / 64; ++e)
-        if (64 * e + lane < D) s = fmaf(a[64 * e + lane], b[64 * e + lane], s);
-    for (int x = 32; x >= 1; x >>= 1) s += xor_lanes(s, x);
-    return s;
-}
-
-// Rows (dQ) or keys (dK, dV) whose fast result is not finite: plain f32
-// arithmetic, one at a time over the wave, keys outside the mask left out.
-template <int D>
-__device__ __noinline__ void dq_rows_plain(const float *Q, const float *K, const float *V,
+__device__ __forceinline__ void dq_rows_plain(const float *Q, const float *K, const float *V,
                                            const float *dO, const float *LSE, const float *Dw,
-                                           float *dQ, int row0, int nrows, int Lq, int kend,
+                                           float *dQ, int row0, int nrows, int Lq, int klen,
                                            int causal, int diag, float scale, float scale_log2,
                                            int lane) {
-    constexpr int NE = (D + 63) / 64;
-    for (int i = row0; i < min(row0 + nrows, Lq); ++i) {
-        float acc[NE] = {};
-        const float lse2 = LSE[i] * kLog2e, Di = Dw[i];
-        const int n = causal ? min(kend, i + diag + 1) : kend;
-        for (int j = 0; j < n; ++j) {
-            const float s = wave_dot<D>(Q + (size_t)i * D, K + (size_t)j * D, lane);
-            const float dp = wave_dot<D>(dO + (size_t)i * D, V + (size_t)j * D, lane);
-            const float ds = exp2_fast(s * scale_log2 - lse2) * (dp - Di);
+    constexpr int NC = D / 16;
+    const int il = lane & 15, g = lane >> 4;
+    for (int i0 = row0; i0 < min(row0 + nrows, Lq); i0 += 16) {
+        const int i = i0 + il;
+        const bool row = i < Lq;
+        f32x4 q[NC], go[NC], acc[NC];
+        load_row16<D>(q, Q + (size_t)i * D, row, g);
+        load_row16<D>(go, dO + (size_t)i * D, row, g);
 #pragma unroll
-            for (int e = 0; e < NE; ++e)
-                if (64 * e + lane < D) acc[e] = fmaf(ds, K[(size_t)j * D + 64 * e + lane], acc[e]);
+        for (int c = 0; c < NC; ++c) acc[c] = zero4();
+        const float lse2 = row ? LSE[i] * kLog2e : 0.f, Di = row ? Dw[i] : 0.f;
+        const int sees = causal ? min(klen, i + diag + 1) : klen;          // keys of this row
+        const int all = causal ? min(klen, i0 + diag + 1) : klen;          // ... of every row
+        const int some = causal ? min(klen, min(i0 + 16, Lq) + diag) : klen;   // ... of any row
+        for (int j0 = 0; j0 < some; j0 += 16) {
+            const f32x4 s = dot16<D>(K + (size_t)j0 * D, klen - j0, q, il, g);
+            const f32x4 dp = dot16<D>(V + (size_t)j0 * D, klen - j0, go, il, g);
+            f32x4 ds;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ds[r] = exp2_fast(s[r] * scale_log2 - lse2) * (dp[r] - Di);
+            if (j0 + 16 <= all)
+                add16<D>(acc, K + (size_t)j0 * D, 16, ds, il, g);
+            else
+                add16_visible<D>(acc, K + (size_t)j0 * D, klen - j0, ds, il, g,
+                                 [&](int x) { return j0 + x < sees; });
+            if (__all(!row || all_nan(acc))) break;
         }
+        if (row) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (64 * e + lane < D) dQ[(size_t)i * D + 64 * e + lane] = acc[e] * scale;
+            for (int c = 0; c < NC; ++c)
+                *reinterpret_cast<f32x4 *>(dQ + (size_t)i * D + 16 * c + 4 * g) = acc[c] * scale;
+        }
     }
 }
 
 template <int D>
-__device__ __noinline__ void dkdv_keys_plain(const float *Q, const float *K, const float *V,
+__device__ __forceinline__ void dkdv_keys_plain(const float *Q, const float *K, const float *V,
                                              const float *dO, const float *LSE, const float *Dw,
-                                             float *dK, float *dV, int key0, int nkeys, int klen,
-                                             int Lq, int causal, int diag, float scale,
-                                             float scale_log2, int lane) {
-    constexpr int NE = (D + 63) / 64;
-    for (int j = key0; j < min(key0 + nkeys, klen); ++j) {
-        float ak[NE] = {}, av[NE] = {};
-        for (int i = causal ? max(0, j - diag) : 0; i < Lq; ++i) {
-            const float s = wave_dot<D>(Q + (size_t)i * D, K + (size_t)j * D, lane);
-            const float dp = wave_dot<D>(dO + (size_t)i * D, V + (size_t)j * D, lane);
-            const float p = exp2_fast(s * scale_log2 - LSE[i] * kLog2e), ds = p * (dp - Dw[i]);
+                                             float *dK, float *dV, int key0, int klen, int Lq,
+                                             int causal, int diag, float scale, float scale_log2,
+                                             int lane) {
+    constexpr int NC = D / 16;
+    const int il = lane & 15, g = lane >> 4;
+    const int j = key0 + il;
+    const bool key = j < klen;
+    f32x4 k[NC], v[NC], ak[NC], av[NC];
+    load_row16<D>(k, K + (size_t)j * D, key, g);
+    load_row16<D>(v, V + (size_t)j * D, key, g);
 #pragma unroll
-            for (int e = 0; e < NE; ++e)
-                if (64 * e + lane < D) {
-                    av[e] = fmaf(p, dO[(size_t)i * D + 64 * e + lane], av[e]);
-                    ak[e] = fmaf(ds, Q[(size_t)i * D + 64 * e + lane], ak[e]);
-                }
+    for (int c = 0; c < NC; ++c) ak[c] = av[c] = zero4();
+    for (int i0 = causal ? max(0, key0 - diag) / 16 * 16 : 0; i0 < Lq; i0 += 16) {
+        const f32x4 s = dot16<D>(Q + (size_t)i0 * D, Lq - i0, k, il, g);
+        const f32x4 dp = dot16<D>(dO + (size_t)i0 * D, Lq - i0, v, il, g);
+        f32x4 p, ds;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + 4 * g + r;
+            p[r] = (i < Lq) ? exp2_fast(s[r] * scale_log2 - LSE[i] * kLog2e) : 0.f;
+            ds[r] = (i < Lq) ? p[r] * (dp[r] - Dw[i]) : 0.f;
         }
+        if (!causal || i0 + diag >= key0 + 15) {
+            add16<D>(av, dO + (size_t)i0 * D, Lq - i0, p, il, g);
+            add16<D>(ak, Q + (size_t)i0 * D, Lq - i0, ds, il, g);
+        } else {
+            const auto sees = [&](int x) { return i0 + x + diag >= j; };
+            add16_visible<D>(av, dO + (size_t)i0 * D, Lq - i0, p, il, g, sees);
+            add16_visible<D>(ak, Q + (size_t)i0 * D, Lq - i0, ds, il, g, sees);
+        }
+        if (__all(!key || (all_nan(ak) && all_nan(av)))) break;
+    }
+    if (key) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (64 * e + lane < D) {
-                dK[(size_t)j * D + 64 * e + lane] = ak[e] * scale;
-                dV[(size_t)j * D + 64 * e + lane] = av[e];
-            }
+        for (int c = 0; c < NC; ++c) {
+            *reinterpret_cast<f32x4 *>(dK + (size_t)j * D + 16 * c + 4 * g) = ak[c] * scale;
+            *reinterpret_cast<f32x4 *>(dV + (size_t)j * D + 16 * c + 4 * g) = av[c];
+        }
     }
 }
 
@@ -507,7 +528,7 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
     }
     if (!__all(fine))
         dkdv_keys_plain<D>(Qh, K + hoff, V + hoff, dOh, LSE + (size_t)head * Lq,
-                           Dws + (size_t)head * Lq, dK + hoff, dV + hoff, wkey0, 16, klen, Lq,
+                           Dws + (size_t)head * Lq, dK + hoff, dV + hoff, wkey0, klen, Lq,
                            causal, diag, scale, scale_log2, lane);
 }
 

@@ -15,50 +15,72 @@
 
 #include "device_common.h"
 #include "launch.h"
+#include "rows_f32.h"
 #include "tiles_split.h"
 #include "work_order.h"
 
 namespace mg {
 namespace {
 
-// Rows whose fast result is not finite: plain f32 arithmetic, one row at a
-// time over the wave (lane = head-dimension index mod 64).  Keys outside the
-// mask take no part.
+// Rows whose fast result is not finite, in plain f32 (rows_f32.h): 16 rows from
+// row0 at a time.  Ends early where every row's sum is NaN, which then is all
+// its O.
 template <int D>
-__device__ __noinline__ void fwd_rows_plain(const float *Q, const float *K, const float *V, float *O,
-                               float *LSE, int row0, int nrows, int Lq, int kend, int causal,
-                               int diag, float scale_log2, int lane) {
-    constexpr int NE = (D + 63) / 64;
-    const bool on = lane < D;
-    for (int i = row0; i < min(row0 + nrows, Lq); ++i) {
-        float q[NE], o[NE];
+__device__ __forceinline__ void fwd_rows_plain(const float *Q, const float *K, const float *V, float *O,
+                                            float *LSE, int row0, int nrows, int Lq, int klen,
+                                            int causal, int diag, float scale_log2, int lane) {
+    constexpr int NC = D / 16;
+    const int il = lane & 15, g = lane >> 4;
+    for (int i0 = row0; i0 < min(row0 + nrows, Lq); i0 += 16) {
+        const int i = i0 + il;
+        const bool row = i < Lq;
+        f32x4 q[NC], o[NC];
+        load_row16<D>(q, Q + (size_t)i * D, row, g);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            q[e] = on ? Q[(size_t)i * D + 64 * e + lane] * scale_log2 : 0.f;
-            o[e] = 0.f;
+        for (int c = 0; c < NC; ++c) {
+            q[c] *= scale_log2;
+            o[c] = zero4();
         }
-        const int n = causal ? min(kend, i + diag + 1) : kend;
+        const int sees = causal ? min(klen, i + diag + 1) : klen;          // keys of this row
+        const int all = causal ? min(klen, i0 + diag + 1) : klen;          // ... of every row
+        const int some = causal ? min(klen, min(i0 + 16, Lq) + diag) : klen;   // ... of any row
         float m = -INFINITY, l = 0.f;
-        for (int j = 0; j < n; ++j) {
-            float s = 0.f;
+        for (int j0 = 0; j0 < some; j0 += 16) {
+            f32x4 p = dot16<D>(K + (size_t)j0 * D, klen - j0, q, il, g);
+            float mx = m;
 #pragma unroll
-            for (int e = 0; e < NE; ++e)
-                if (on) s = fmaf(q[e], K[(size_t)j * D + 64 * e + lane], s);
-            for (int x = 32; x >= 1; x >>= 1) s += xor_lanes(s, x);
-            const float mn = fmaxf(m, s);
-            const float mu = (mn == -INFINITY) ? 0.f : mn;
-            const float a = exp2_fast(m - mu), p = exp2_fast(s - mu);
-            l = l * a + p;
+            for (int r = 0; r < 4; ++r) {
+                if (j0 + 4 * g + r >= sees) p[r] = -INFINITY;
+                mx = fmaxf(mx, p[r]);
+            }
+            mx = max_over_groups(mx);
+            const float mu = (mx == -INFINITY) ? 0.f : mx;
+            const float alpha = exp2_fast(m - mu);
+            m = mx;
+            l *= alpha;
 #pragma unroll
-            for (int e = 0; e < NE; ++e)
-                if (on) o[e] = fmaf(p, V[(size_t)j * D + 64 * e + lane], o[e] * a);
-            m = mn;
+            for (int r = 0; r < 4; ++r) {
+                p[r] = exp2_fast(p[r] - mu);
+                l += p[r];
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) o[c] *= alpha;
+            if (j0 + 16 <= all)
+                add16<D>(o, V + (size_t)j0 * D, 16, p, il, g);
+            else
+                add16_visible<D>(o, V + (size_t)j0 * D, klen - j0, p, il, g,
+                                 [&](int x) { return j0 + x < sees; });
+            const float lt = sum_over_groups(l);
+            if (__all(!row || lt != lt)) break;
         }
+        l = sum_over_groups(l);
         const float inv = (l > 0.f) ? 1.f / l : 0.f;
+        if (row) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e)
-            if (on) O[(size_t)i * D + 64 * e + lane] = o[e] * inv;
-        if (lane == 0) LSE[i] = row_lse(m, l);
+            for (int c = 0; c < NC; ++c)
+                *reinterpret_cast<f32x4 *>(O + (size_t)i * D + 16 * c + 4 * g) = o[c] * inv;
+            if (g == 0) LSE[i] = row_lse(m, l);
+        }
     }
 }
 

@@ -151,21 +151,55 @@ struct DgradJobs {
     int n;
 };
 
-// An output whose split sum is not finite: the same terms in plain f32.
-__device__ __forceinline__ float wgrad_plain(const WgradJob &job, const ConvProblem &p,
-                                          const ConvDivs &dv, int k, int j, int m0, int m1) {
+// Outputs whose split sum is not finite: the same terms in plain f32, padding
+// left out.  Four or eight outputs of a lane that share one operand of every
+// term advance together, kPlain terms' loads in flight; a wave ends where every
+// sum it still wants is NaN.  One output at a time, one term in flight, NaN inputs
+// took N4 14x14 256 -> 256 3x3 from 38 us to 1350, a NaN in W to 640; so 145 and 98 us.
+constexpr int kPlain = 2;
+template <int N>
+__device__ __forceinline__ bool undecided(const float (&sum)[N], unsigned want) {
+    bool any = false;
+#pragma unroll
+    for (int x = 0; x < N; ++x) any = any || ((want >> x & 1) && sum[x] == sum[x]);
+    return any;
+}
+
+// Outputs k[x], j of the filter gradient over positions [m0, m1); bits of `want`.
+__device__ __forceinline__ void wgrad_plain(float (&sum)[8], unsigned want,
+                                            __amdgpu_buffer_rsrc_t rdy, __amdgpu_buffer_rsrc_t rx,
+                                            const ConvProblem &p, const ConvDivs &dv, int kbase,
+                                            int j, int m0, int m1) {
     const int rs = fdiv(j, dv.C), c = j - rs * p.C;
     const int r = fdiv(rs, dv.S), s = rs - r * p.S;
-    float sum = 0.f;
-    for (int m = m0; m < m1; ++m) {
-        const int n = fdiv(m, dv.PQ), pq = m - n * p.P * p.Q;
-        const int pp = fdiv(pq, dv.Q), qq = pq - pp * p.Q;
-        const int h = pp * p.sh - p.ph + r, w = qq * p.sw - p.pw + s;
-        if ((unsigned)h >= (unsigned)p.H || (unsigned)w >= (unsigned)p.W) continue;   // padding
-        sum = fmaf(job.dY[(size_t)m * p.K + k],
-                   job.X[(((size_t)n * p.H + h) * p.W + w) * p.C + c], sum);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) sum[x] = 0.f;
+#pragma unroll 1
+    for (int m = m0; m < m1; m += kPlain) {
+        float a[kPlain][8], b[kPlain];
+        bool ok[kPlain];
+#pragma unroll
+        for (int u = 0; u < kPlain; ++u) {
+            const int n = fdiv(m + u, dv.PQ), pq = m + u - n * p.P * p.Q;
+            const int pp = fdiv(pq, dv.Q), qq = pq - pp * p.Q;
+            const int h = pp * p.sh - p.ph + r, w = qq * p.sw - p.pw + s;
+            ok[u] = want != 0 && m + u < m1 && (unsigned)h < (unsigned)p.H &&
+                    (unsigned)w < (unsigned)p.W;
+            b[u] = buffer_load_f32(rx, ok[u] ? 4 * (((n * p.H + h) * p.W + w) * p.C + c) : kOOB);
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const int k = kbase + 16 * (x >> 2) + (x & 3);
+                a[u][x] = buffer_load_f32(rdy, (want >> x & 1) ? 4 * ((m + u) * p.K + k) : kOOB);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kPlain; ++u)
+            if (ok[u]) {
+#pragma unroll
+                for (int x = 0; x < 8; ++x) sum[x] = fmaf(a[u][x], b[u], sum[x]);
+            }
+        if (!__any(undecided(sum, want))) break;
     }
-    return sum;
 }
 
 // ------------------------------------------------------- filter gradient --
@@ -309,13 +343,17 @@ __device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &
             chk = fmaf(acc[i][r], 0.f, chk);   // NaN if not finite
         }
     if (!__all(finite_f32(chk))) {
-#pragma unroll 1
-        for (int x = 0; x < 8; ++x) {
-            const int k = k0 + 32 * wm + 16 * (x >> 2) + 4 * g + (x & 3);
-            if (k < p.K && j < RSC && !finite_f32(dst[(size_t)k * RSC + j]))
-                dst[(size_t)k * RSC + j] =
-                    wgrad_plain(job, p, dv, k, j, st0 * BK, min(st1 * BK, M));
-        }
+        const int kbase = k0 + 32 * wm + 4 * g;
+        unsigned want = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            if (kbase + 16 * (x >> 2) + (x & 3) < p.K && j < RSC && !finite_f32(acc[x >> 2][x & 3]))
+                want |= 1u << x;
+        float sum[8];
+        wgrad_plain(sum, want, rdy, rx, p, dv, kbase, j < RSC ? j : 0, st0 * BK, min(st1 * BK, M));
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            if (want >> x & 1) dst[(size_t)(kbase + 16 * (x >> 2) + (x & 3)) * RSC + j] = sum[x];
     }
 }
 
@@ -374,19 +412,57 @@ __global__ __launch_bounds__(256) void conv_split_reduce_f32(ReduceJob a, Reduce
         split_reduce(blockIdx.x - a.blocks, b);
 }
 
-__device__ __forceinline__ float dgrad_plain(const DgradJob &job, const ConvProblem &p,
-                                          const ConvDivs &dv, int n, int i, int j, int c, int j0,
-                                          int j1) {
-    float sum = 0.f;
-    for (int x = j0; x < j1; ++x) {
-        const int t = fdiv(x, dv.K), k = x - t * p.K;
+// Outputs of class pixels m0 .. m0 + 3, channel c of the data gradient over the
+// class's reduction columns [j0, j1), tap by tap; bits of `want`.
+__device__ __forceinline__ void dgrad_plain(float (&sum)[4], unsigned want, const DgradJob &job,
+                                            __amdgpu_buffer_rsrc_t rdy, __amdgpu_buffer_rsrc_t rw,
+                                            const ConvProblem &p, const ConvDivs &dv, int m0,
+                                            int c, int j0, int j1) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) sum[x] = 0.f;
+#pragma unroll 1
+    for (int x0 = j0; x0 < j1;) {   // columns x0 .. of one tap (tr, ts)
+        const int t = fdiv(x0, dv.K), k0 = x0 - t * p.K;
         const int tr = fdiv(t, job.Sc_), ts = t - tr * job.Sc;
-        const int pp = i + job.da - tr, qq = j + job.db - ts;
-        if ((unsigned)pp >= (unsigned)p.P || (unsigned)qq >= (unsigned)p.Q) continue;
-        const size_t w = (((size_t)k * p.R + job.r0 + p.sh * tr) * p.S + job.s0 + p.sw * ts) * p.C;
-        sum = fmaf(job.dY[(((size_t)n * p.P + pp) * p.Q + qq) * p.K + k], job.Wt[w + c], sum);
+        const int k1 = min(p.K, k0 + j1 - x0);
+        x0 += k1 - k0;
+        unsigned dy[4];   // byte offset of dY[n][p][q][k0] of each pixel, kOOB outside
+        bool some = false;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int n = fdiv(m0 + x, job.HWc), ij = m0 + x - n * (job.Hc * job.Wc);
+            const int i = fdiv(ij, job.Wc_), j = ij - i * job.Wc;
+            const int pp = i + job.da - tr, qq = j + job.db - ts;
+            const bool ok = (want >> x & 1) && (unsigned)pp < (unsigned)p.P &&
+                            (unsigned)qq < (unsigned)p.Q;
+            dy[x] = ok ? 4u * (((n * p.P + pp) * p.Q + qq) * p.K + k0) : kOOB;
+            some = some || ok;
+        }
+        if (!__any(some)) continue;
+        const unsigned wstep = 4u * p.R * p.S * p.C;
+        unsigned w = 4u * (((k0 * p.R + job.r0 + p.sh * tr) * p.S + job.s0 + p.sw * ts) * p.C + c);
+#pragma unroll 1
+        for (int k = k0; k < k1; k += kPlain) {
+            float a[kPlain][4], b[kPlain];
+#pragma unroll
+            for (int u = 0; u < kPlain; ++u) {   // what lies past the tap is not added
+                b[u] = buffer_load_f32(rw, c < p.C ? w + u * wstep : kOOB);
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    a[u][x] = buffer_load_f32(rdy, dy[x] == kOOB ? kOOB : dy[x] + 4 * u);
+            }
+#pragma unroll
+            for (int u = 0; u < kPlain; ++u)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (k + u < k1 && dy[x] != kOOB) sum[x] = fmaf(a[u][x], b[u], sum[x]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (dy[x] != kOOB) dy[x] += 4 * kPlain;
+            w += kPlain * wstep;
+        }
+        if (!__any(undecided(sum, want))) break;
     }
-    return sum;
 }
 
 // --------------------------------------------------------- data gradient --
@@ -552,15 +628,23 @@ __device__ __forceinline__ void dgrad_tile(int bid, ConvLds &L, const DgradJob &
         }
     if (!__all(finite_f32(chk))) {
 #pragma unroll 1
-        for (int x = 0; x < 8; ++x) {
-            const int mo = m0 + 32 * wm + 16 * (x >> 2) + 4 * g + (x & 3);
-            if (mo >= Mc || c >= p.C) continue;
-            const int on = fdiv(mo, job.HWc), oij = mo - on * HWc;
-            const int oi = fdiv(oij, job.Wc_), oj = oij - oi * job.Wc;
-            const size_t pix = ((size_t)on * p.H + job.a + p.sh * oi) * p.W + job.b + p.sw * oj;
-            if (!finite_f32(dst[pix * p.C + c]))
-                dst[pix * p.C + c] =
-                    dgrad_plain(job, p, dv, on, oi, oj, c, st0 * BK, min(st1 * BK, RSKc));
+        for (int ii = 0; ii < 2; ++ii) {
+            const int mo = m0 + 32 * wm + 16 * ii + 4 * g;
+            unsigned want = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (mo + r < Mc && c < p.C && !finite_f32(ii ? acc[1][r] : acc[0][r])) want |= 1u << r;
+            float sum[4];
+            dgrad_plain(sum, want, job, rdy, rw, p, dv, mo, c, st0 * BK, min(st1 * BK, RSKc));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (!(want >> r & 1)) continue;
+                const int on = fdiv(mo + r, job.HWc), oij = mo + r - on * HWc;
+                const int oi = fdiv(oij, job.Wc_), oj = oij - oi * job.Wc;
+                const size_t pix =
+                    ((size_t)on * p.H + job.a + p.sh * oi) * p.W + job.b + p.sw * oj;
+                dst[pix * p.C + c] = sum[r];
+            }
         }
     }
 }
