@@ -33,6 +33,7 @@ __device__ __forceinline__ void dq_rows_plain(const float *Q, const float *K, co
                                            int causal, int diag, float scale, float scale_log2,
                                            int lane) {
     constexpr int NC = D / 16;
+    hide(lane, klen);
     const int il = lane & 15, g = lane >> 4;
     for (int i0 = row0; i0 < min(row0 + nrows, Lq); i0 += 16) {
         const int i = i0 + il;
@@ -74,6 +75,7 @@ __device__ __forceinline__ void dkdv_keys_plain(const float *Q, const float *K, 
                                              int causal, int diag, float scale, float scale_log2,
                                              int lane) {
     constexpr int NC = D / 16;
+    if constexpr (D < 128) hide(lane, klen);   // d = 128 has no register to spare for it
     const int il = lane & 15, g = lane >> 4;
     const int j = key0 + il;
     const bool key = j < klen;
@@ -219,7 +221,7 @@ void attn_dq_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             sv.load(Vh, (kt + 2) * KT, klen, tid);
         }
         const int jt = kt * KT + key0;
-        if (jt < klen && (!causal || jt <= qw0 + WQ - 1 + diag)) {
+        if (qw0 < Lq && jt < klen && (!causal || jt <= qw0 + WQ - 1 + diag)) {
             const uint16_t *Kc = Ks + cur, *Vc = Vs + cur;
             f32x4 sacc[NKB][QB], pacc[NKB][QB];   // 2^48 S^T, dP^T[16kb + 4g + r][qi + 16qb]
 #pragma unroll

@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "fwd_forms.h"
 #include "launch.h"
 #include "rows_f32.h"
 #include "tiles_split.h"
@@ -30,6 +31,7 @@ __device__ __forceinline__ void fwd_rows_plain(const float *Q, const float *K, c
                                             float *LSE, int row0, int nrows, int Lq, int klen,
                                             int causal, int diag, float scale_log2, int lane) {
     constexpr int NC = D / 16;
+    hide(lane, klen);
     const int il = lane & 15, g = lane >> 4;
     for (int i0 = row0; i0 < min(row0 + nrows, Lq); i0 += 16) {
         const int i = i0 + il;
@@ -199,7 +201,7 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
             }
         }
         // some key of the share is allowed for some query of the wave
-        const bool live = jw < klen && (!causal || jw <= qw0 + WQ - 1 + diag);
+        const bool live = qw0 < Lq && jw < klen && (!causal || jw <= qw0 + WQ - 1 + diag);
         f32x4 sacc[NKB][QB];   // kUp^2 S^T[16kb + 4g + r][qi + 16qb]
         if (live) {
 #pragma unroll
@@ -375,44 +377,12 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-// Which form (QB, QW, KG, KT): a tile is split once for all the waves of a
-// workgroup, eight but for short rows.  Figures: GPU time in us at d = 64 unless named, the
-// f32 matrix-core forwards this replaces in front.
-//   128 rows, one key group, while they give two workgroups per CU: B8 H8 L1024
-//     causal 72.8 -> 54.7, B16 H12 L512 padded 70.8 -> 60.9, B4 H16 L2048 515
-//     -> 341 (d = 32: 280 -> 200); short key sides too (Lk 77: 11.6 -> 11.1,
-//     two key groups 12.3).
-//   64 rows, two key groups, below that: B2 H6 L1500 84.2 -> 73.8, B4 H8 L512
-//     23.8 -> 18.7, B3 H6 L1500 108 -> 74.4, B16 H8 L512 causal 40.6 -> 34.3,
-//     B1 H4 L2500 97.7 -> 72.0 (four groups 97.7).
-//   32 rows, four key groups, where a row's chain of keys sets the time: one
-//     round of workgroups (at d = 64 the 128-key tiles leave room for one per
-//     CU), two for long causal chains, two to four at d = 32.  B2 H6 L1200
-//     causal 36.8 -> 30.0 (two groups 36.2), B1 H4 L4096 causal 96.2 -> 84.6
-//     (112), B4 H6 L300 11.6 -> 10.9 (12.7); d = 32 B1 H8 L2000 causal 34.1 ->
-//     24.6 (41.4), B2 H8 L1000 23.0 -> 21.2 (23.1).
-//   32 rows, two key groups, four waves for short key sides: with so few tiles
-//   the time is the workgroup's start and end, which more of them per CU hide.
-//   B8 H8 L256 causal 11.5 -> 11.0 (the f32 kernel 10.7), B8 H12 L200 padded
-//     14.0 -> 12.9, d = 32 9.6 -> 8.5, L100 6.4 -> 5.5, B16 H8 L64 6.3 -> 5.1;
-//     but L200 without masks 10.9 -> 13.2, B4 H8 L256 causal 9.1 -> 10.1, B16
-//     H12 L256 padded 23.4 -> 27.1.
-//   d = 128: two key groups below 192 128-row tiles (B2 H8 L1024 causal 77.8 ->
-//     58.2), then 128 rows (B4 H16 L1024 causal 161 -> 104), 256 rows of two
-//     16-row blocks per wave when those fill two rounds (B4 H16 L2048 1061 ->
-//     572, 128 rows: 676).
+// Instances per form.  With one key group a tile is split once for all the
+// waves of a workgroup; kRows64 streams 32-key tiles, whose LDS (24 KB at d = 64)
+// leaves room for four workgroups per CU.
 hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K, const float *V,
-                          float *O, float *LSE, hipStream_t s) {
+                          float *O, float *LSE, FwdForm form, hipStream_t s) {
     const int BH = p.B * p.H;
-    const long rows32 = (long)cdiv(p.Lq, 32) * BH, rows64 = (long)cdiv(p.Lq, 64) * BH,
-               rows128 = (long)cdiv(p.Lq, 128) * BH;
-    const bool wide = rows128 >= 512 || (rows64 >= 512 && p.Lk <= 128);
-    const bool chain = p.d == 32 ? rows32 <= (p.causal ? 1024 : 512)
-                                 : rows32 <= (p.causal && p.Lk >= 1024 ? 512 : 256);
-    const bool brief =
-        p.Lk <= (p.d == 32 ? 64 : 128) ||
-        (p.Lk <= 256 && rows32 <= 1024 &&
-         (p.d == 32 ? p.key_len && rows32 > 256 : (p.causal || p.key_len) && !chain));
     auto go = [&](auto kern, int rows, int nt) {
         const int nqt = cdiv(p.Lq, rows);
         const dim3 grid(nqt * BH);
@@ -422,23 +392,32 @@ hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K, 
         return hipGetLastError();
     };
 #define MG_GO(D, QB, QW, KG, KT, DB, OCC) \
-    go(attn_fwd_f32x3<D, QB, QW, KG, KT, DB, OCC>, 16 * QB * QW, 64 * QW * KG)
-    switch (p.d) {
-    case 32:
-        return wide ? MG_GO(32, 1, 8, 1, 64, false, 4)
-                    : brief ? MG_GO(32, 1, 2, 2, 64, false, 4)
-                    : chain ? MG_GO(32, 1, 2, 4, 128, false, 4) : MG_GO(32, 1, 4, 2, 64, false, 4);
-    case 64:
-        return wide ? MG_GO(64, 1, 8, 1, 64, false, 4)
-                    : brief ? MG_GO(64, 1, 2, 2, 64, false, 3)
-                    : chain ? MG_GO(64, 1, 2, 4, 128, false, 2) : MG_GO(64, 1, 4, 2, 64, false, 4);
-    case 128:
-        if ((long)cdiv(p.Lq, 256) * BH >= 512) return MG_GO(128, 2, 8, 1, 32, true, 2);
-        return rows128 >= 192 ? MG_GO(128, 1, 8, 1, 32, true, 2)
-                              : MG_GO(128, 1, 4, 2, 64, false, 2);
-    default: return hipErrorInvalidValue;
+    return go(attn_fwd_f32x3<D, QB, QW, KG, KT, DB, OCC>, 16 * QB * QW, 64 * QW * KG)
+    if (p.d == 32) switch (form) {
+        case FwdForm::kRows32: MG_GO(32, 1, 2, 2, 64, false, 4);
+        case FwdForm::kRows32Quad: MG_GO(32, 1, 2, 4, 128, false, 4);
+        case FwdForm::kRows64: MG_GO(32, 1, 4, 1, 32, false, 4);
+        case FwdForm::kRows64Pair: MG_GO(32, 1, 4, 2, 64, false, 4);
+        case FwdForm::kRows128: MG_GO(32, 1, 8, 1, 64, false, 4);
+        default: break;
+    }
+    if (p.d == 64) switch (form) {
+        case FwdForm::kRows32: MG_GO(64, 1, 2, 2, 64, false, 3);
+        case FwdForm::kRows32Quad: MG_GO(64, 1, 2, 4, 128, false, 2);
+        case FwdForm::kRows64: MG_GO(64, 1, 4, 1, 32, false, 4);
+        case FwdForm::kRows64Pair: MG_GO(64, 1, 4, 2, 64, false, 4);
+        case FwdForm::kRows128: MG_GO(64, 1, 8, 1, 64, false, 4);
+        default: break;
+    }
+    if (p.d == 128) switch (form) {
+        case FwdForm::kRows64: MG_GO(128, 1, 4, 1, 32, false, 2);
+        case FwdForm::kRows64Pair: MG_GO(128, 1, 4, 2, 64, false, 2);
+        case FwdForm::kRows128: MG_GO(128, 1, 8, 1, 32, true, 2);
+        case FwdForm::kRows256: MG_GO(128, 2, 8, 1, 32, true, 2);
+        default: break;
     }
 #undef MG_GO
+    return hipErrorInvalidValue;
 }
 
 }  // namespace mg

@@ -28,13 +28,12 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "fwd_forms.h"
 #include "launch.h"
 #include "tiles_bf16.h"
 
 namespace mg {
 namespace {
-
-constexpr int kFewRows = 16;
 
 // Online softmax of one 16-row block of queries (lane % 16), whose scores (in
 // base-2 units, masked to -inf) lie in NB registers x 4 lane groups.
@@ -115,20 +114,19 @@ __device__ __forceinline__ f16x8 to_f16x8(f32x4 a, f32x4 b) {
 }
 
 // ---------------------------------------------------------------------- f32 --
-template <int D, int DV, int NW, bool ROUND>
-__global__ __launch_bounds__(64 * NW)
+template <int D, int DV, int NW, int KT, bool ROUND>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void attn_fwd_few_f32(const float *__restrict__ Q, const float *__restrict__ K,
                       const float *__restrict__ V, float *__restrict__ O,
                       float *__restrict__ LSE, const int32_t *__restrict__ key_len, int H, int Lq,
                       int Lk, int causal, float scale_log2, int BH) {
-    constexpr int KT = 2048 / D;                    // keys per wave and step
-    constexpr int NKB = KT / 16;
+    constexpr int NKB = KT / 16;                    // KT keys per wave and step
     constexpr int NS = D / 16;                      // 16-float pieces of a K row
     constexpr int VE = (DV / 16 < 4) ? DV / 16 : 4; // value columns per load
     constexpr int NCV = DV / (16 * VE);
     constexpr int CS = D / DV;
     typedef float vfrag __attribute__((ext_vector_type(VE)));
-    __shared__ __attribute__((aligned(16))) float xo[NW * kFewRows * DV];
+    __shared__ __attribute__((aligned(16))) float xo[NW > 1 ? NW * kFewRows * DV : 4];
     __shared__ float ml[NW][2][kFewRows];
 
     const int slot = blockIdx.x / BH;
@@ -266,6 +264,23 @@ void attn_fwd_few_f32(const float *__restrict__ Q, const float *__restrict__ K,
     }
 
     const float l = sum_over_groups(st.l);
+    float *Oh = O + ((size_t)head * Lq + q0) * D + col0;
+    float *Lh = col0 == 0 ? LSE + (size_t)head * Lq + q0 : nullptr;
+    if constexpr (NW == 1) {   // the wave's state is the result
+        if (qi >= Lq) return;
+        const float inv = (l > 0.f) ? 1.f / l : 0.f;
+#pragma unroll
+        for (int c = 0; c < NCV; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                vfrag v;
+#pragma unroll
+                for (int e = 0; e < VE; ++e) v[e] = oacc[c][e][r] * inv;
+                *reinterpret_cast<vfrag *>(Oh + (size_t)il * D + 16 * VE * c + VE * (4 * g + r)) = v;
+            }
+        if (Lh != nullptr && g == 0) Lh[il] = row_lse(st.m, l);
+        return;
+    }
     if (g == 0) {
         ml[w][0][il] = st.m;
         ml[w][1][il] = l;
@@ -280,9 +295,7 @@ void attn_fwd_few_f32(const float *__restrict__ Q, const float *__restrict__ K,
                 xo[state_at<DV>(w, il, col >> 2) + (col & 3)] = oacc[c][e][r];
             }
     __syncthreads();
-    float *Oh = O + ((size_t)head * Lq + q0) * D + col0;
-    merge_and_store<NW, DV>(xo, ml, tid, min(kFewRows, Lq - q0),
-                            col0 == 0 ? LSE + (size_t)head * Lq + q0 : nullptr,
+    merge_and_store<NW, DV>(xo, ml, tid, min(kFewRows, Lq - q0), Lh,
                             [&](int q, int c, f32x4 v) {
                                 *reinterpret_cast<f32x4 *>(Oh + (size_t)q * D + c) = v;
                             });
@@ -431,35 +444,24 @@ void attn_fwd_few_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restric
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-long row_blocks(const AttnProblem &p) { return (long)cdiv(p.Lq, kFewRows) * p.B * p.H; }
-
-// Workgroups per (head, row block): the value columns are split (32 or more
-// each) until there is one workgroup per CU.  B8 H16 Lq1 Lk4096 d128 (128 row
-// blocks): bf16 39.6 -> 35.1 us, strict 86.7 -> 72.5 us; beyond 256 workgroups
-// the repeated scores cost more (B32 H16 Lq1: 184 -> 261 us).
-int column_splits(const AttnProblem &p) {
-    int cs = 1;
-    while (cs * 2 <= p.d / 32 && row_blocks(p) * cs * 2 <= 256) cs *= 2;
-    return cs;
-}
-
 // Eight waves per workgroup where one workgroup per CU must keep a long key
 // side's loads in flight, else four (two or more workgroups per CU; B2 H4
 // L1024 causal strict: 24.9 us with eight, 22.1 with four).
 int waves(const AttnProblem &p) {
-    return row_blocks(p) * column_splits(p) <= 256 && p.Lk >= 1024 ? 8 : 4;
+    return few_row_blocks(p) * few_column_splits(p) <= 256 && p.Lk >= 1024 ? 8 : 4;
 }
 
+template <int X>
+using Int = std::integral_constant<int, X>;
+
+// f(d, value columns, waves) of the kernel for p.
 template <typename F>
 hipError_t by_shape(const AttnProblem &p, F &&f) {
-    using std::integral_constant;
-    const int cs = column_splits(p), nw = waves(p);
-#define MG_CASE(DD, CS)                                                                         \
-    if (p.d == DD && cs == CS)                                                                  \
-        return nw == 8 ? f(integral_constant<int, DD>{}, integral_constant<int, DD / CS>{},     \
-                           integral_constant<int, 8>{})                                         \
-                       : f(integral_constant<int, DD>{}, integral_constant<int, DD / CS>{},     \
-                           integral_constant<int, 4>{})
+    const int cs = few_column_splits(p), nw = waves(p);
+#define MG_CASE(DD, CS)                                                  \
+    if (p.d == DD && cs == CS)                                           \
+        return nw == 8 ? f(Int<DD>{}, Int<DD / CS>{}, Int<8>{})          \
+                       : f(Int<DD>{}, Int<DD / CS>{}, Int<4>{})
     MG_CASE(32, 1);
     MG_CASE(64, 1);
     MG_CASE(64, 2);
@@ -472,49 +474,57 @@ hipError_t by_shape(const AttnProblem &p, F &&f) {
 
 }  // namespace
 
-// A decode step (Lq <= 16) always; more rows while their 16-row blocks are few
-// enough that spreading a head's keys over the waves pays for reading K and V
-// once per block.  Measured against the query-stationary forwards (GPU time,
-// this : those, us):
-//   strict, 256 blocks:  B4 H4 L256 d64 6.8 : 9.2, B1 H8 L512 d128 15.7 : 40.8;
-//     512: B1 H4 L2048 d128 93 : 150; d <= 64 for masks that shorten the rows
-//     and short key sides: B2 H8 L400 causal 11.2 : 12.5, B1 H8 L1000 causal
-//     22.0 : 22.7 (d = 32: 13.2 : 13.8), B8 H6 L150 padded 8.3 : 8.7, B4 H6
-//     Lq300 Lk77 6.1 : 6.7, but B4 H6 L300 12.6 : 10.9, B8 H8 L128 7.1 : 6.7,
-//     B16 H8 L64 5.9 : 5.1
-//   bf16, 256: B4 H4 L256 4.0 : 7.2; 512: B2 H4 L1024 9.8 : 16.1, B8 H8 L128
-//     4.1 : 4.9; 1024: B8 H8 L256 8.2 : 6.5
+// bf16 and accelerated: a decode step (Lq <= 16) always; more rows while their
+// 16-row blocks are few enough that spreading a head's keys over the waves pays
+// for reading K and V once per block.  Against the query-stationary forwards
+// (GPU time, this : those, us):
+//   bf16, 256 blocks: B4 H4 L256 4.0 : 7.2; 512: B2 H4 L1024 9.8 : 16.1, B8 H8
+//     L128 4.1 : 4.9; 1024: B8 H8 L256 8.2 : 6.5
 //   accelerated, 256: B4 H4 L256 5.4 : 8.8; 512: B1 H4 L2048 d128 76 : 54
 bool use_few_rows(const AttnProblem &p, mg_contract_t contract) {
-    const bool wide = contract == MG_CONTRACT_FAST_BF16 ||
-                      (contract == MG_CONTRACT_STRICT_F32 && p.d == 128);
-    const bool two_rounds =
-        wide || (contract == MG_CONTRACT_STRICT_F32 &&
-                 (p.causal || (p.d == 64 && p.Lk <= (p.key_len ? 160 : 96) && p.Lk > 64)));
-    return p.Lq <= kFewRows || row_blocks(p) <= (two_rounds ? 512 : 256);
+    return p.Lq <= kFewRows ||
+           few_row_blocks(p) <= (contract == MG_CONTRACT_FAST_BF16 ? 512 : 256);
+}
+
+// The grid of a kernel of NW waves and DV value columns per workgroup.
+template <typename Kern, typename T>
+static hipError_t launch_few(Kern kern, const AttnProblem &p, int dv, int nw, const T *Q,
+                             const T *K, const T *V, T *O, float *LSE, hipStream_t s) {
+    kern<<<dim3((unsigned)(few_row_blocks(p) * (p.d / dv))), dim3(64 * nw), 0, s>>>(
+        Q, K, V, O, LSE, p.key_len, p.H, p.Lq, p.Lk, p.causal, p.scale * kLog2e, p.B * p.H);
+    return hipGetLastError();
 }
 
 hipError_t launch_fwd_few_f32(const AttnProblem &p, const float *Q, const float *K, const float *V,
-                              float *O, float *LSE, bool round_f16, hipStream_t s) {
-    const dim3 grid((unsigned)(row_blocks(p) * column_splits(p))), block(64 * waves(p));
+                              float *O, float *LSE, FwdForm form, hipStream_t s) {
+    auto go = [&](auto kern, int dv, int nw) {
+        return launch_few(kern, p, dv, nw, Q, K, V, O, LSE, s);
+    };
+    if (form == FwdForm::kFewWave)
+        return p.d == 32   ? go(attn_fwd_few_f32<32, 32, 1, 16, false>, 32, 1)
+               : p.d == 64 ? go(attn_fwd_few_f32<64, 64, 1, 16, false>, 64, 1)
+                           : go(attn_fwd_few_f32<128, 128, 1, 16, false>, 128, 1);
+    if (form == FwdForm::kFew && p.d == 32) return go(attn_fwd_few_f32<32, 32, 4, 16, false>, 32, 4);
+    if (form == FwdForm::kFew && p.d == 64)
+        return few_column_splits(p) == 1 ? go(attn_fwd_few_f32<64, 64, 4, 16, false>, 64, 4)
+                                         : go(attn_fwd_few_f32<64, 32, 4, 16, false>, 32, 4);
     return by_shape(p, [&](auto dd, auto dv, auto nw) {
-        auto go = [&](auto kern) {
-            kern<<<grid, block, 0, s>>>(Q, K, V, O, LSE, p.key_len, p.H, p.Lq, p.Lk, p.causal,
-                                        p.scale * kLog2e, p.B * p.H);
-            return hipGetLastError();
-        };
-        return round_f16 ? go(attn_fwd_few_f32<dd(), dv(), nw(), true>)
-                         : go(attn_fwd_few_f32<dd(), dv(), nw(), false>);
+        return go(attn_fwd_few_f32<dd(), dv(), nw(), 2048 / dd(), false>, dv(), nw());
+    });
+}
+
+hipError_t launch_fwd_few_accel(const AttnProblem &p, const float *Q, const float *K,
+                                const float *V, float *O, float *LSE, hipStream_t s) {
+    return by_shape(p, [&](auto dd, auto dv, auto nw) {
+        return launch_few(attn_fwd_few_f32<dd(), dv(), nw(), 2048 / dd(), true>, p, dv(), nw(), Q,
+                          K, V, O, LSE, s);
     });
 }
 
 hipError_t launch_fwd_few_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
                                const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s) {
-    const dim3 grid((unsigned)(row_blocks(p) * column_splits(p))), block(64 * waves(p));
     return by_shape(p, [&](auto dd, auto dv, auto nw) {
-        attn_fwd_few_bf16<dd(), dv(), nw()><<<grid, block, 0, s>>>(
-            Q, K, V, O, LSE, p.key_len, p.H, p.Lq, p.Lk, p.causal, p.scale * kLog2e, p.B * p.H);
-        return hipGetLastError();
+        return launch_few(attn_fwd_few_bf16<dd(), dv(), nw()>, p, dv(), nw(), Q, K, V, O, LSE, s);
     });
 }
 

@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "../device_common.h"
+#include "../rows_f32.h"
 #include "../tiles_split.h"
 #include "conv_launch.h"
 
@@ -343,14 +344,16 @@ __device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &
             chk = fmaf(acc[i][r], 0.f, chk);   // NaN if not finite
         }
     if (!__all(finite_f32(chk))) {
-        const int kbase = k0 + 32 * wm + 4 * g;
+        int gp = g, first = st0;
+        hide(gp, first);
+        const int kbase = k0 + 32 * wm + 4 * gp;
         unsigned want = 0;
 #pragma unroll
         for (int x = 0; x < 8; ++x)
             if (kbase + 16 * (x >> 2) + (x & 3) < p.K && j < RSC && !finite_f32(acc[x >> 2][x & 3]))
                 want |= 1u << x;
         float sum[8];
-        wgrad_plain(sum, want, rdy, rx, p, dv, kbase, j < RSC ? j : 0, st0 * BK, min(st1 * BK, M));
+        wgrad_plain(sum, want, rdy, rx, p, dv, kbase, j < RSC ? j : 0, first * BK, min(st1 * BK, M));
 #pragma unroll
         for (int x = 0; x < 8; ++x)
             if (want >> x & 1) dst[(size_t)(kbase + 16 * (x >> 2) + (x & 3)) * RSC + j] = sum[x];
@@ -627,15 +630,17 @@ __device__ __forceinline__ void dgrad_tile(int bid, ConvLds &L, const DgradJob &
             chk = fmaf(acc[ii][r], 0.f, chk);   // NaN if not finite
         }
     if (!__all(finite_f32(chk))) {
+        int gp = g, first = st0;
+        hide(gp, first);
 #pragma unroll 1
         for (int ii = 0; ii < 2; ++ii) {
-            const int mo = m0 + 32 * wm + 16 * ii + 4 * g;
+            const int mo = m0 + 32 * wm + 16 * ii + 4 * gp;
             unsigned want = 0;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (mo + r < Mc && c < p.C && !finite_f32(ii ? acc[1][r] : acc[0][r])) want |= 1u << r;
             float sum[4];
-            dgrad_plain(sum, want, job, rdy, rw, p, dv, mo, c, st0 * BK, min(st1 * BK, RSKc));
+            dgrad_plain(sum, want, job, rdy, rw, p, dv, mo, c, first * BK, min(st1 * BK, RSKc));
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 if (!(want >> r & 1)) continue;

@@ -34,9 +34,10 @@ struct AttnProblem {
 int causal_rank_layer(const void *kernel, int block, long grid, int BH, int causal);
 
 // Forward, strict f32: O, LSE from Q, K, V (on the bf16 matrix cores, operands
-// split into three bf16 parts).
+// split into three bf16 parts), in a form of 32 or more rows (strict_fwd_form).
+enum class FwdForm;
 hipError_t launch_fwd_f32(const AttnProblem &p, const float *Q, const float *K,
-                          const float *V, float *O, float *LSE, hipStream_t s);
+                          const float *V, float *O, float *LSE, FwdForm form, hipStream_t s);
 // Forward, bf16 inputs/outputs, f32 accumulation.
 hipError_t launch_fwd_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
                            const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s);
@@ -46,12 +47,13 @@ hipError_t launch_fwd_bf16(const AttnProblem &p, const uint16_t *Q, const uint16
 hipError_t launch_fwd_accel(const AttnProblem &p, const float *Q, const float *K,
                             const float *V, float *O, float *LSE, hipStream_t s);
 
-// Forward for few query rows (use_few_rows), every contract; round_f16 is the
-// accelerated one.
+// Forward for few query rows: strict in the forms that say so, the other
+// contracts where use_few_rows does.
 bool use_few_rows(const AttnProblem &p, mg_contract_t contract);
 hipError_t launch_fwd_few_f32(const AttnProblem &p, const float *Q, const float *K,
-                              const float *V, float *O, float *LSE, bool round_f16,
-                              hipStream_t s);
+                              const float *V, float *O, float *LSE, FwdForm form, hipStream_t s);
+hipError_t launch_fwd_few_accel(const AttnProblem &p, const float *Q, const float *K,
+                                const float *V, float *O, float *LSE, hipStream_t s);
 hipError_t launch_fwd_few_bf16(const AttnProblem &p, const uint16_t *Q, const uint16_t *K,
                                const uint16_t *V, uint16_t *O, float *LSE, hipStream_t s);
 

@@ -13,6 +13,7 @@
 #include <string>
 
 #include "attn_bwd.h"
+#include "fwd_forms.h"
 #include "host_runtime.h"
 #include "launch.h"
 
@@ -214,31 +215,23 @@ mg_status_t mg_attn_fwd_cross(const void *Q, const void *K, const void *V, void 
     MG_TRY(check_tensors({{Q, "Q"}, {K, "K"}, {V, "V"}, {O, "O"}, {LSE, "LSE"}}));
     MG_TRY(check_key_len(key_len));
     const mg::AttnProblem p{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
-    if (mg::use_few_rows(p, contract)) {
-        MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
-            if (contract == MG_CONTRACT_FAST_BF16)
-                return mg::launch_fwd_few_bf16(p, (const uint16_t *)Q, (const uint16_t *)K,
-                                               (const uint16_t *)V, (uint16_t *)O, LSE, stream);
-            return mg::launch_fwd_few_f32(p, (const float *)Q, (const float *)K,
-                                          (const float *)V, (float *)O, LSE,
-                                          contract == MG_CONTRACT_ACCELERATED, stream);
-        }));
-    } else if (contract == MG_CONTRACT_STRICT_F32) {
-        MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
-            return mg::launch_fwd_f32(p, (const float *)Q, (const float *)K, (const float *)V,
-                                      (float *)O, LSE, stream);
-        }));
-    } else if (contract == MG_CONTRACT_ACCELERATED) {
-        MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
-            return mg::launch_fwd_accel(p, (const float *)Q, (const float *)K, (const float *)V,
-                                        (float *)O, LSE, stream);
-        }));
-    } else {
-        MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
-            return mg::launch_fwd_bf16(p, (const uint16_t *)Q, (const uint16_t *)K,
-                                       (const uint16_t *)V, (uint16_t *)O, LSE, stream);
-        }));
-    }
+    MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
+        if (contract == MG_CONTRACT_FAST_BF16) {
+            const auto launch =
+                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_bf16 : mg::launch_fwd_bf16;
+            return launch(p, (const uint16_t *)Q, (const uint16_t *)K, (const uint16_t *)V,
+                          (uint16_t *)O, LSE, stream);
+        }
+        const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
+        if (contract == MG_CONTRACT_ACCELERATED) {
+            const auto launch =
+                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_accel : mg::launch_fwd_accel;
+            return launch(p, q, k, v, (float *)O, LSE, stream);
+        }
+        const mg::FwdForm form = mg::strict_fwd_form(p);
+        const auto launch = mg::few_rows(form) ? mg::launch_fwd_few_f32 : mg::launch_fwd_f32;
+        return launch(p, q, k, v, (float *)O, LSE, form, stream);
+    }));
     return ok();
 }
 

@@ -1,0 +1,40 @@
+"""Choice of the strict forward's form (host only)."""
+import random
+
+import pytest
+
+from forms import FWD_ROWS, fwd_form
+
+
+def shapes(n):
+    rng = random.Random(5)
+    for _ in range(n):
+        H = int(2 ** rng.uniform(0, 11))
+        Lq = int(2 ** rng.uniform(0, 11))
+        Lk = Lq if rng.random() < 0.5 else int(2 ** rng.uniform(0, 12))
+        yield 1, H, Lq, Lk, rng.choice((32, 64, 128)), rng.choice(("causal", "full", "padded"))
+
+
+def test_a_tile_is_not_mostly_padding():
+    """A head's last tile may be cut, but no form of 128 or 256 rows is taken
+    that a head fills less than half (with far more keys than rows the waves
+    without rows help to stage them)."""
+    for s in shapes(5000):
+        rows = FWD_ROWS[fwd_form(*s)]
+        assert rows <= 64 or s[2] > rows // 2 or s[3] > 4 * s[2], s
+
+
+def test_every_instance_exists():
+    for s in shapes(5000):
+        d, form = s[4], fwd_form(*s)
+        assert form not in (("rows32", "rows32_quad") if d == 128 else ("rows256",)), s
+
+
+@pytest.mark.parametrize("shape,form", [
+    ((1, 1351, 55, 55, 128, "causal"), "rows64"), ((32, 51, 32, 32, 32, "full"), "few_wave"),
+    ((8, 8, 1024, 1024, 64, "causal"), "rows128"), ((2, 6, 1500, 1500, 64, "full"), "rows64_pair"),
+    ((2, 8, 1024, 1024, 128, "causal"), "rows64_pair"), ((4, 4, 256, 256, 64, "causal"), "few"),
+    ((8, 16, 1, 4096, 128, "padded"), "few_long"), ((1, 1, 64, 64, 32, "causal"), "few"),
+])
+def test_forms_of_named_shapes(shape, form):
+    assert fwd_form(*shape) == form
