@@ -538,34 +538,54 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-// Forms.  kWide: four waves of 32 query rows or 16 keys, for grids of two
-// workgroups per CU.  kPair: eight waves in two groups that share a 64-row tile
-// and take half of each streamed 64-row tile, for grids that leave the time to
-// the chain of tiles.  kEight (d = 128): eight waves that share a tile's split.
+// Forms.  kWide: four waves of 32 query rows or 16 keys.  kPair: eight waves in
+// two groups that share a 64-row tile and take half of each streamed 64-row
+// tile, for grids that leave the time to the chain of tiles.  kEight (d = 128):
+// eight waves that share a tile's split.
 //
 // d <= 64, where the alternative is the fused f32 kernel, which splits the query
-// tiles of a key tile over workgroups (whole backward, GPU us, that : this).
-// Wide: B8 H8 L1024 causal 207 : 173, B4 H16 L2048 1489 : 1100, d = 32 798 : 640.
-// Pair, from 448 64-key tiles or with short query sides: B4 H8 L1024 200 : 169,
-// B4 H16 L512 causal 75 : 66, B3 H6 Lq814 Lk1850 221 : 192, B8 H8 L256 causal
-// 42.7 : 32.6; not B2 H6 L1500 (288 tiles) 186 : 224, B1 H4 L2500 179 : 209, B2
-// H6 L1200 causal 86 : 105; nor one tile a head, where the fused kernel is the
-// whole backward: B16 H16 L64 causal 13.5 : 17.6 (Lq128 Lk60 29.1 : 26.5).
+// tiles of a key tile over workgroups: the whole backward of both over 1,616
+// problems (GPU us, fused : this).  A tile counts only where a head fills 60 %
+// of it; one tile a head (64 rows and keys) stays fused, which is the whole
+// backward in one launch (but d = 32 causal, many heads: B1 H768 L32 17.3 : 15.0).
+//   kWide from one 128-row query tile per CU and a third more key tiles (causal
+//     grids, whose tiles differ in length, and d = 32, whose workgroups are
+//     shorter, from more; two tiles a head from fewer): d = 64 B1 H192 L80 28 : 27,
+//     B8 H32 L128 42 : 38, B8 H16 L256 64 : 56, B8 H8 L1024 causal 207 : 173, B4 H16
+//     L2048 1489 : 1100; not B1 H128 L80 21 : 24.  With two rounds of both and
+//     more than 64 rows also where tiles are less filled (B1 H622 Lq629 Lk9 171 :
+//     149; but B1 H539 Lq8 Lk119 35 : 45).
+//   kPair from 192 64-row tiles of both sides while the chains are short, or 448:
+//     B8 H12 L128 31 : 25, B8 H8 L256 49 : 37, B8 H4 L512 73 : 58, B4 H16 L512
+//     causal 75 : 66, B3 H6 Lq814 Lk1850 221 : 192; not B2 H6 L1500 (288 tiles) 186
+//     : 224, B1 H4 L2500 179 : 209, B2 H6 L1200 causal 86 : 105, B1 H101 Lq149
+//     Lk1910 causal d32 106 : 133.
+// (Before, a tile counted whole: B1 H371 Lq25 Lk116 25 : 37, B1 H557 L20 24 : 31.)
 // d = 128, against separate f32 kernels: pair up to 128 128-row tiles (B2 H8
 // L1024 causal 354 -> 157, four-wave workgroups 198), then eight (B4 H8 L1024
 // 270, pair 316; B4 H16 L2048 3907 -> 2006).
-enum class Form { kNone, kWide, kPair, kEight };
-static Form split_form(const AttnProblem &p) {
+SplitBwdForm split_bwd_form(const AttnProblem &p) {
     const long BH = (long)p.B * p.H;
+    const bool causal = p.causal != 0;
     if (p.d == 128)
-        return std::max(cdiv(p.Lq, 128), cdiv(p.Lk, 128)) * BH > 128 ? Form::kEight : Form::kPair;
-    const long q64 = cdiv(p.Lq, 64) * BH, k64 = cdiv(p.Lk, 64) * BH;
-    if (cdiv(p.Lq, 128) * BH >= 512 && k64 >= 512) return Form::kWide;
-    if (p.Lq <= 64 && p.Lk <= 64) return Form::kNone;
-    if (q64 >= 224 && (k64 >= 448 || (k64 >= 224 && p.Lq <= 512))) return Form::kPair;
-    return Form::kNone;
+        return std::max(cdiv(p.Lq, 128), cdiv(p.Lk, 128)) * BH > 128 ? SplitBwdForm::kEight
+                                                                     : SplitBwdForm::kPair;
+    if (p.Lq <= 64 && p.Lk <= 64)
+        return p.d == 32 && causal && BH >= 512 ? SplitBwdForm::kWide : SplitBwdForm::kNone;
+    const long q128 = cdiv(p.Lq, 128) * BH, q64 = cdiv(p.Lq, 64) * BH, k64 = cdiv(p.Lk, 64) * BH;
+    if (p.Lq > 64 && q128 >= 512 && k64 >= 512) return SplitBwdForm::kWide;
+    // 60 % of the 64-row tiles of either side filled
+    if (5L * p.Lq < 3L * 64 * cdiv(p.Lq, 64) || 5L * p.Lk < 3L * 64 * cdiv(p.Lk, 64))
+        return SplitBwdForm::kNone;
+    const bool brief = p.Lq <= 96 && p.Lk <= 96;
+    const long wide = brief        ? (causal ? 512 : p.d == 32 ? 256 : 192)
+                      : p.d == 32 ? 512 : (causal ? 384 : 256);
+    if (q128 >= wide && 3 * k64 >= 4 * wide) return SplitBwdForm::kWide;
+    if (!brief && q64 >= 192 && k64 >= 192 && (k64 >= 448 || p.Lq <= 512) &&
+        (q64 >= 448 || p.Lk <= 512))
+        return SplitBwdForm::kPair;
+    return SplitBwdForm::kNone;
 }
-bool use_split_bwd(const AttnProblem &p) { return split_form(p) != Form::kNone; }
 
 hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float *K,
                                const float *V, const float *O, const float *dO, const float *LSE,
@@ -581,7 +601,7 @@ hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float
         return hipGetLastError();
     };
     // (none: the caller has no room for the fused kernel's partials)
-    const bool pair = split_form(p) == Form::kPair;
+    const bool pair = split_bwd_form(p) == SplitBwdForm::kPair;
     switch (p.d) {
     case 32:
         return pair ? go(attn_dq_f32x3<32, 1, 4, 64, 2>, 64, 512)
@@ -609,7 +629,7 @@ hipError_t launch_bwd_dkdv_f32x3(const AttnProblem &p, const float *Q, const flo
                                        padded_work_order(p));
         return hipGetLastError();
     };
-    const bool pair = split_form(p) == Form::kPair;
+    const bool pair = split_bwd_form(p) == SplitBwdForm::kPair;
     switch (p.d) {
     case 32:
         return pair ? go(attn_dkdv_f32x3<32, 4, 64, 2>, 64, 512)

@@ -93,11 +93,11 @@ hipError_t launch_bwd_reduce_f32(const AttnProblem &p, const float *dKVp, float 
 hipError_t launch_bwd_dq_reduce_f32(const AttnProblem &p, const float *dQp, float *dQ,
                                     hipStream_t s);
 
-// Backward step 3: dQ with the query tile stationary.
 // Strict backward on the bf16 matrix cores, operands split into three bf16
 // parts: the dQ kernel computes D and writes it to Dws; it runs first.
-// use_split_bwd: where it is taken although the fused kernel could be.
-bool use_split_bwd(const AttnProblem &p);
+// kNone: the fused kernel is taken where its partials have room.
+enum class SplitBwdForm { kNone, kWide, kPair, kEight };
+SplitBwdForm split_bwd_form(const AttnProblem &p);
 hipError_t launch_bwd_dq_f32x3(const AttnProblem &p, const float *Q, const float *K,
                                const float *V, const float *O, const float *dO,
                                const float *LSE, float *Dws, float *dQ, hipStream_t s);

@@ -150,7 +150,7 @@ mg_status_t attn_bwd_enqueue(const void *Q, const void *K, const void *V, const 
     if (contract == MG_CONTRACT_STRICT_F32) {
         const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
         const float *o = (const float *)O, *go = (const float *)dO;
-        if (mg::use_split_bwd(p) ||
+        if (mg::split_bwd_form(p) != mg::SplitBwdForm::kNone ||
             !use_fused_dq(B, H, Lq, Lk, d, causal, contract, partial_limit)) {
             MG_TRY(run_kernel(kernel_name("attn_dq", contract, d), stream, [&] {
                 return mg::launch_bwd_dq_f32x3(p, q, k, v, o, go, LSE, Dws, (float *)dQ, stream);

@@ -26,3 +26,10 @@ def _ask(name, B, H, Lq, Lk, d, mode):
 
 def fwd_form(*shape):
     return FWD_FORMS[_ask("strict_fwd_form", *shape)]
+
+
+BWD_FORMS = ("fused", "wide", "pair", "eight")
+
+
+def bwd_form(*shape):
+    return BWD_FORMS[_ask("split_bwd_form", *shape)]

@@ -6,6 +6,7 @@ bf16."""
 import numpy as np
 import pytest
 
+from forms import bwd_form, fwd_form
 from gpu_util import oracle_reference, run_gpu, say, to_host
 from workloads import make_inputs
 
@@ -114,10 +115,23 @@ def plain(Q, K, V, dO, scale):
             "dV": torch.matmul(P.transpose(-1, -2).contiguous(), dO)}
 
 
-# (B, H, L, d): forward and backward forms: 128 rows; 64 rows, wave groups; 32
-# rows and four groups before the f32 backward; d = 128 in both
-FORMS = [(8, 64, 130, 64), (4, 60, 193, 64), (1, 8, 700, 64), (8, 64, 130, 32), (8, 64, 130, 128),
-         (1, 30, 200, 128)]
+# (B, H, L, d) without a mask: forward forms of 32, 64 and 256 rows with one, two
+# and four key groups, backward forms wide, pair, fused (f32) and eight
+FORMS = [(8, 64, 130, 64), (1, 105, 125, 64), (1, 8, 700, 64), (8, 64, 130, 32), (2, 40, 250, 32),
+         (8, 64, 130, 128), (1, 40, 257, 128)]
+# ... and causal: wide, pair, eight
+CAUSAL_FORMS = [(8, 64, 130, 64), (1, 105, 125, 64), (2, 40, 250, 32), (8, 64, 130, 32),
+                (8, 64, 130, 128), (1, 40, 257, 128)]
+FORM_NAMES = [("rows64", "wide"), ("rows64_pair", "pair"), ("rows32_quad", "fused"),
+              ("rows64", "wide"), ("rows32", "pair"), ("rows256", "eight"), ("rows64_pair", "pair")]
+
+
+def test_forms_are_the_ones_named():
+    for (B, H, L, d), names in zip(FORMS, FORM_NAMES):
+        assert (fwd_form(B, H, L, L, d, "full"), bwd_form(B, H, L, L, d, "full")) == names
+    for B, H, L, d in CAUSAL_FORMS:
+        assert not fwd_form(B, H, L, L, d, "causal").startswith("few")
+        assert bwd_form(B, H, L, L, d, "causal") != "fused"
 
 
 @pytest.mark.parametrize("B,H,L,d", FORMS)
@@ -226,8 +240,7 @@ def test_finite_values_above_the_split(gpu_lib, what, B, H, L, d):
         assert ((v - r).norm(dim=-1) <= 4e-5 * r.norm(dim=-1)).all(), n
 
 
-@pytest.mark.parametrize("B,H,L,d", [(8, 64, 130, 64), (4, 60, 193, 64), (8, 64, 130, 32),
-                                     (8, 64, 130, 128), (1, 40, 257, 128)])
+@pytest.mark.parametrize("B,H,L,d", CAUSAL_FORMS)
 @pytest.mark.parametrize("what,value", [("V", np.inf), ("V", np.nan), ("K", np.nan), ("K", np.inf)])
 def test_masked_values_take_no_part(gpu_lib, what, value, B, H, L, d):
     """Under a causal mask an infinite or NaN key or value row j changes no row
