@@ -88,3 +88,19 @@ def test_bf16_two_group_backward(gpu_lib, Lq, Lk, mode, d):
                     key_len=[Lk - 33, 65] if mode == "padded" else None)
     errs = compare(run_gpu(x), oracle_reference(x), "fast_bf16")
     assert max(errs.values()) <= TOL["fast_bf16"], errs
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("Lq,Lk,mode", [
+    (1, 1, "full"), (32, 32, "causal"), (33, 33, "causal"), (33, 65, "causal"), (96, 64, "causal"),
+    (97, 31, "padded"), (128, 33, "full"), (65, 97, "padded"), (40, 129, "causal"), (129, 96, "full"),
+])
+def test_bf16_dq_where_waves_see_nothing(gpu_lib, Lq, Lk, mode, d):
+    """The bf16 dQ kernel leaves out the 32 keys that no row of a wave sees, and
+    all keys for waves without rows: lengths around its 32-row and 32-key steps."""
+    from gpu_util import compare, oracle_reference, run_gpu
+    say("bf16 dQ cut Lq=%d Lk=%d d=%d %s" % (Lq, Lk, d, mode))
+    x = make_inputs(2, 3, Lq, d, causal=mode == "causal", contract="fast_bf16", seed=Lq + Lk + d, Lk=Lk,
+                    key_len=[Lk, max(1, Lk - 33)] if mode == "padded" else None)
+    errs = compare(run_gpu(x), oracle_reference(x), "fast_bf16")
+    assert max(errs.values()) <= TOL["fast_bf16"], errs
