@@ -4,6 +4,7 @@ takes and fails when a rule retargets it."""
 import ctypes
 
 import paper_2608_01563_amd as mg
+from paper_2608_01563_amd import _binding
 
 FWD_FORMS = ("few_wave", "few", "few_long", "rows32", "rows32_quad", "rows64", "rows64_pair",
              "rows128", "rows256")
@@ -33,3 +34,11 @@ BWD_FORMS = ("fused", "wide", "pair", "eight")
 
 def bwd_form(*shape):
     return BWD_FORMS[_ask("split_bwd_form", *shape)]
+
+
+def few_rows(contract, B, H, Lq, Lk, d, mode):
+    """Whether a bf16 or accelerated forward takes 16 rows per workgroup."""
+    f = mg.load_library()._ZN2mg12use_few_rowsERKNS_11AttnProblemE13mg_contract_t
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.POINTER(Problem), ctypes.c_int]
+    return f(ctypes.byref(Problem(B, H, Lq, Lk, d, mode == "causal", 1.0, None)),
+             _binding.CONTRACTS[contract])

@@ -3,7 +3,7 @@ import random
 
 import pytest
 
-from forms import FWD_ROWS, fwd_form
+from forms import FWD_ROWS, few_rows, fwd_form
 
 
 def shapes(n):
@@ -38,3 +38,19 @@ def test_every_instance_exists():
 ])
 def test_forms_of_named_shapes(shape, form):
     assert fwd_form(*shape) == form
+
+
+@pytest.mark.parametrize("shape,few", [
+    ((8, 16, 1, 4096, 128, "full"), True), ((2, 4, 1024, 1024, 64, "causal"), True),
+    ((8, 8, 128, 128, 128, "full"), True), ((1, 55, 70, 70, 128, "full"), True), ((1, 200, 17, 4096, 32, "full"), True),
+    # a head's K and V would be read once per block from memory
+    ((1, 256, 32, 2048, 128, "full"), False), ((1, 73, 100, 1000, 128, "causal"), False),
+    ((1, 43, 128, 4000, 64, "full"), False),
+])
+def test_bf16_few_rows(shape, few):
+    assert few_rows("fast_bf16", *shape) == few
+
+
+def test_accelerated_few_rows():
+    assert few_rows("accelerated", 4, 4, 256, 256, 64, "causal")
+    assert not few_rows("accelerated", 1, 4, 2048, 2048, 128, "full")
