@@ -362,9 +362,9 @@ __device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &
 
 template <int VA, int VB>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void conv_wgrad_f32(WgradJob job, ConvProblem p, ConvDivs dv) {
+void conv_wgrad_f32(WgradJob job, ConvProblem p, ConvDivs dv, int first) {
     __shared__ __attribute__((aligned(16))) ConvLds lds;
-    wgrad_tile<VA, VB>(blockIdx.x, lds, job, p, dv);
+    wgrad_tile<VA, VB>(first + blockIdx.x, lds, job, p, dv);
 }
 
 // out[i] = sum over splits of part[split][i].  A group of G consecutive lanes
@@ -666,9 +666,9 @@ __device__ __forceinline__ int find_class(const DgradJobs &jobs, int &bid) {
 
 template <int VA, int VB>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void conv_dgrad_f32(DgradJobs jobs, ConvProblem p, ConvDivs dv) {
+void conv_dgrad_f32(DgradJobs jobs, ConvProblem p, ConvDivs dv, int first) {
     __shared__ __attribute__((aligned(16))) ConvLds lds;
-    int bid = blockIdx.x;
+    int bid = first + blockIdx.x;
     const int c = find_class(jobs, bid);
     dgrad_tile<VA, VB>(bid, lds, jobs.c[c], p, dv);
 }
@@ -677,9 +677,9 @@ void conv_dgrad_f32(DgradJobs jobs, ConvProblem p, ConvDivs dv) {
 // workgroups run the data gradient's class jobs, the rest the filter gradient.
 template <int VA, int VB>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void conv_bwd_f32(DgradJobs d, int dblocks, WgradJob w, ConvProblem p, ConvDivs dv) {
+void conv_bwd_f32(DgradJobs d, int dblocks, WgradJob w, ConvProblem p, ConvDivs dv, int first) {
     __shared__ __attribute__((aligned(16))) ConvLds lds;
-    int bid = blockIdx.x;
+    int bid = first + blockIdx.x;
     if (bid < dblocks) {
         const int c = find_class(d, bid);
         dgrad_tile<VA, VB>(bid, lds, d.c[c], p, dv);
@@ -827,20 +827,37 @@ hipError_t by_widths(const ConvProblem &p, Args &&...args) {
     return Launch<1, 1>::run(args...);
 }
 
+// launch(grid, first workgroup) over `blocks` workgroups of NT threads, in several
+// launches where one grid's 2^32 threads are too few (the grid's size wraps there
+// without an error).
+constexpr int kMaxBlocks = 1 << 22;
+static_assert((uint64_t)kMaxBlocks * NT < (1ull << 32), "threads of a grid");
+template <typename F>
+hipError_t in_grids(int blocks, F &&launch) {
+    for (int first = 0; first < blocks; first += kMaxBlocks) {
+        launch(dim3(std::min(kMaxBlocks, blocks - first)), first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int VA, int VB>
 struct LaunchW {
     static hipError_t run(const WgradJob &j, const ConvProblem &p, const ConvDivs &dv,
                           hipStream_t s) {
-        conv_wgrad_f32<VA, VB><<<dim3(j.blocks), dim3(NT), 0, s>>>(j, p, dv);
-        return hipGetLastError();
+        return in_grids(j.blocks, [&](dim3 grid, int first) {
+            conv_wgrad_f32<VA, VB><<<grid, dim3(NT), 0, s>>>(j, p, dv, first);
+        });
     }
 };
 template <int VA, int VB>
 struct LaunchD {
     static hipError_t run(const DgradJobs &j, const ConvProblem &p, const ConvDivs &dv,
                           hipStream_t s) {
-        conv_dgrad_f32<VA, VB><<<dim3(total_blocks(j)), dim3(NT), 0, s>>>(j, p, dv);
-        return hipGetLastError();
+        return in_grids(total_blocks(j), [&](dim3 grid, int first) {
+            conv_dgrad_f32<VA, VB><<<grid, dim3(NT), 0, s>>>(j, p, dv, first);
+        });
     }
 };
 template <int VA, int VB>
@@ -848,8 +865,9 @@ struct LaunchDW {
     static hipError_t run(const DgradJobs &d, const WgradJob &w, const ConvProblem &p,
                           const ConvDivs &dv, hipStream_t s) {
         const int db = total_blocks(d);
-        conv_bwd_f32<VA, VB><<<dim3(db + w.blocks), dim3(NT), 0, s>>>(d, db, w, p, dv);
-        return hipGetLastError();
+        return in_grids(db + w.blocks, [&](dim3 grid, int first) {
+            conv_bwd_f32<VA, VB><<<grid, dim3(NT), 0, s>>>(d, db, w, p, dv, first);
+        });
     }
 };
 

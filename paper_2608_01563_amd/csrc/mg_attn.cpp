@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <type_traits>
 
 #include "attn_bwd.h"
 #include "fwd_forms.h"
@@ -69,6 +70,37 @@ const char *kernel_name(const char *stage, mg_contract_t c, int d) {
     return mg::host::intern_name(buf);
 }
 
+// A grid holds fewer than 2^32 threads (its size in threads wraps beyond, and the
+// launch then runs a part of the workgroups without an error), so calls of more
+// heads than this run as several, one after another on the stream.  Sizes end at
+// 2^31 - 1 elements, so up to here there are at most 2^22 + 2^31 / 512 workgroups
+// of 256 threads, or 2^22 + 2^31 / 2048 of 512.
+constexpr int kMaxHeads = 1 << 22;
+
+// fn(part, first head) for parts of whole batches, or of one batch's
+// heads, in order.
+template <typename F>
+mg_status_t in_parts(const mg::AttnProblem &p, F &&fn) {
+    if ((int64_t)p.B * p.H <= kMaxHeads) return fn(p, (size_t)0);
+    const int nb = std::max(1, kMaxHeads / p.H), nh = std::min(p.H, kMaxHeads);
+    for (int b = 0; b < p.B; b += nb)
+        for (int h = 0; h < p.H; h += nh) {
+            mg::AttnProblem part = p;
+            part.B = std::min(nb, p.B - b);
+            part.H = std::min(nh, p.H - h);
+            if (p.key_len != nullptr) part.key_len = p.key_len + b;
+            MG_TRY(fn(part, (size_t)b * p.H + h));
+        }
+    return MG_OK;
+}
+
+// `heads` heads of L rows of `row` bytes further on.
+template <typename T>
+T *at_head(T *ptr, size_t heads, int L, size_t row) {
+    using Byte = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return reinterpret_cast<T *>(reinterpret_cast<Byte *>(ptr) + heads * L * row);
+}
+
 // The accelerated contract's backward is the strict-f32 backward (its
 // tensors are f32 and its backward matrices stay f32).
 mg_contract_t backward_contract(mg_contract_t c) {
@@ -98,6 +130,89 @@ size_t dkdv_partial_bytes(int B, int H, int Lq, int Lk, int d, int causal) {
     const mg::AttnProblem p{B, H, Lq, Lk, d, causal ? 1 : 0, 1.0f, nullptr};
     const int ns = mg::fused_dq_query_splits(p);
     return ns > 1 ? (size_t)2 * ns * B * H * Lk * d * sizeof(float) : 0;
+}
+
+mg_status_t enqueue_fwd(const mg::AttnProblem &p, const void *Q, const void *K, const void *V,
+                        void *O, float *LSE, mg_contract_t contract, hipStream_t stream) {
+    return run_kernel(kernel_name("attn_fwd", contract, p.d), stream, [&] {
+        if (contract == MG_CONTRACT_FAST_BF16) {
+            const auto launch =
+                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_bf16 : mg::launch_fwd_bf16;
+            return launch(p, (const uint16_t *)Q, (const uint16_t *)K, (const uint16_t *)V,
+                          (uint16_t *)O, LSE, stream);
+        }
+        const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
+        if (contract == MG_CONTRACT_ACCELERATED) {
+            const auto launch =
+                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_accel : mg::launch_fwd_accel;
+            return launch(p, q, k, v, (float *)O, LSE, stream);
+        }
+        const mg::FwdForm form = mg::strict_fwd_form(p);
+        const auto launch = mg::few_rows(form) ? mg::launch_fwd_few_f32 : mg::launch_fwd_f32;
+        return launch(p, q, k, v, (float *)O, LSE, form, stream);
+    });
+}
+
+mg_status_t enqueue_bwd(const mg::AttnProblem &p, const void *Q, const void *K, const void *V,
+                        const void *O, const float *LSE, const void *dO, void *dQ, void *dK,
+                        void *dV, mg_contract_t contract, void *workspace, size_t partial_limit,
+                        hipStream_t stream) {
+    float *Dws = (float *)workspace;
+    contract = backward_contract(contract);
+    const int d = p.d;
+    if (contract == MG_CONTRACT_STRICT_F32) {
+        const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
+        const float *o = (const float *)O, *go = (const float *)dO;
+        if (mg::split_bwd_form(p) != mg::SplitBwdForm::kNone ||
+            !use_fused_dq(p.B, p.H, p.Lq, p.Lk, d, p.causal, contract, partial_limit)) {
+            MG_TRY(run_kernel(kernel_name("attn_dq", contract, d), stream, [&] {
+                return mg::launch_bwd_dq_f32x3(p, q, k, v, o, go, LSE, Dws, (float *)dQ, stream);
+            }));
+            MG_TRY(run_kernel(kernel_name("attn_dkdv", contract, d), stream, [&] {
+                return mg::launch_bwd_dkdv_f32x3(p, q, k, v, go, LSE, Dws, (float *)dK,
+                                                 (float *)dV, stream);
+            }));
+            return MG_OK;
+        }
+        // small fused grids compute D in the kernel itself
+        if (!mg::fused_local_d(p))
+            MG_TRY(run_kernel(kernel_name("attn_rowdot", contract, d), stream,
+                              [&] { return mg::launch_bwd_rowdot_f32(p, o, go, Dws, stream); }));
+        char *base = (char *)workspace;
+        float *dQp = (float *)(base + round256((size_t)p.B * p.H * p.Lq * sizeof(float)));
+        float *dKVp = dkdv_partial_bytes(p.B, p.H, p.Lq, p.Lk, d, p.causal) == 0 ? nullptr
+            : (float *)((char *)dQp + round256(dq_partial_bytes(p.B, p.H, p.Lq, p.Lk, d, p.causal)));
+        // one key tile and no split: the kernel writes dQ itself
+        const bool direct = mg::fused_direct_dq(p);
+        MG_TRY(run_kernel(kernel_name("attn_dkdvq", contract, d), stream, [&] {
+            return mg::launch_bwd_dkdvq_f32(p, q, k, v, o, go, LSE, Dws, (float *)dK,
+                                            (float *)dV, direct ? (float *)dQ : dQp, dKVp,
+                                            stream);
+        }));
+        if (dKVp != nullptr)
+            MG_TRY(run_kernel(kernel_name("attn_bwdreduce", contract, d), stream, [&] {
+                return mg::launch_bwd_reduce_f32(p, dKVp, (float *)dK, (float *)dV, dQp,
+                                                 (float *)dQ, stream);
+            }));
+        else if (!direct)
+            MG_TRY(run_kernel(kernel_name("attn_dqreduce", contract, d), stream, [&] {
+                return mg::launch_bwd_dq_reduce_f32(p, dQp, (float *)dQ, stream);
+            }));
+    } else {
+        const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K,
+                       *v = (const uint16_t *)V;
+        const uint16_t *o = (const uint16_t *)O, *go = (const uint16_t *)dO;
+        // The dQ kernel computes D for its query rows on the way (it holds
+        // each row's dO already) and writes it for the dK/dV kernel.
+        MG_TRY(run_kernel(kernel_name("attn_dq", contract, d), stream, [&] {
+            return mg::launch_bwd_dq_bf16(p, q, k, v, o, go, LSE, Dws, (uint16_t *)dQ, stream);
+        }));
+        MG_TRY(run_kernel(kernel_name("attn_dkdv", contract, d), stream, [&] {
+            return mg::launch_bwd_dkdv_bf16(p, q, k, v, go, LSE, Dws, (uint16_t *)dK,
+                                            (uint16_t *)dV, stream);
+        }));
+    }
+    return MG_OK;
 }
 
 }  // namespace
@@ -144,61 +259,19 @@ mg_status_t attn_bwd_enqueue(const void *Q, const void *K, const void *V, const 
                              const int32_t *key_len, int B, int H, int Lq, int Lk, int d,
                              int causal, float scale, mg_contract_t contract, void *workspace,
                              size_t partial_limit, hipStream_t stream) {
-    const mg::AttnProblem p{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
-    float *Dws = (float *)workspace;
-    contract = backward_contract(contract);
-    if (contract == MG_CONTRACT_STRICT_F32) {
-        const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
-        const float *o = (const float *)O, *go = (const float *)dO;
-        if (mg::split_bwd_form(p) != mg::SplitBwdForm::kNone ||
-            !use_fused_dq(B, H, Lq, Lk, d, causal, contract, partial_limit)) {
-            MG_TRY(run_kernel(kernel_name("attn_dq", contract, d), stream, [&] {
-                return mg::launch_bwd_dq_f32x3(p, q, k, v, o, go, LSE, Dws, (float *)dQ, stream);
-            }));
-            MG_TRY(run_kernel(kernel_name("attn_dkdv", contract, d), stream, [&] {
-                return mg::launch_bwd_dkdv_f32x3(p, q, k, v, go, LSE, Dws, (float *)dK,
-                                                 (float *)dV, stream);
-            }));
-            return ok();
-        }
-        // small fused grids compute D in the kernel itself
-        if (!mg::fused_local_d(p))
-            MG_TRY(run_kernel(kernel_name("attn_rowdot", contract, d), stream,
-                              [&] { return mg::launch_bwd_rowdot_f32(p, o, go, Dws, stream); }));
-        char *base = (char *)workspace;
-        float *dQp = (float *)(base + round256((size_t)B * H * Lq * sizeof(float)));
-        float *dKVp = dkdv_partial_bytes(B, H, Lq, Lk, d, causal) == 0 ? nullptr
-            : (float *)((char *)dQp + round256(dq_partial_bytes(B, H, Lq, Lk, d, causal)));
-        // one key tile and no split: the kernel writes dQ itself
-        const bool direct = mg::fused_direct_dq(p);
-        MG_TRY(run_kernel(kernel_name("attn_dkdvq", contract, d), stream, [&] {
-            return mg::launch_bwd_dkdvq_f32(p, q, k, v, o, go, LSE, Dws, (float *)dK,
-                                            (float *)dV, direct ? (float *)dQ : dQp, dKVp,
-                                            stream);
-        }));
-        if (dKVp != nullptr)
-            MG_TRY(run_kernel(kernel_name("attn_bwdreduce", contract, d), stream, [&] {
-                return mg::launch_bwd_reduce_f32(p, dKVp, (float *)dK, (float *)dV, dQp,
-                                                 (float *)dQ, stream);
-            }));
-        else if (!direct)
-            MG_TRY(run_kernel(kernel_name("attn_dqreduce", contract, d), stream, [&] {
-                return mg::launch_bwd_dq_reduce_f32(p, dQp, (float *)dQ, stream);
-            }));
-    } else {
-        const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K,
-                       *v = (const uint16_t *)V;
-        const uint16_t *o = (const uint16_t *)O, *go = (const uint16_t *)dO;
-        // The dQ kernel computes D for its query rows on the way (it holds
-        // each row's dO already) and writes it for the dK/dV kernel.
-        MG_TRY(run_kernel(kernel_name("attn_dq", contract, d), stream, [&] {
-            return mg::launch_bwd_dq_bf16(p, q, k, v, o, go, LSE, Dws, (uint16_t *)dQ, stream);
-        }));
-        MG_TRY(run_kernel(kernel_name("attn_dkdv", contract, d), stream, [&] {
-            return mg::launch_bwd_dkdv_bf16(p, q, k, v, go, LSE, Dws, (uint16_t *)dK,
-                                            (uint16_t *)dV, stream);
-        }));
-    }
+    const mg::AttnProblem whole{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
+    const size_t row = (size_t)d * (contract == MG_CONTRACT_FAST_BF16 ? 2 : 4);
+    // Every part uses the workspace from its start; without room for the whole
+    // call's partials there is none for a part's.
+    if (!use_fused_dq(B, H, Lq, Lk, d, causal, backward_contract(contract), partial_limit))
+        partial_limit = 0;
+    MG_TRY(in_parts(whole, [&](const mg::AttnProblem &p, size_t head) {
+        return enqueue_bwd(p, at_head(Q, head, Lq, row), at_head(K, head, Lk, row),
+                           at_head(V, head, Lk, row), at_head(O, head, Lq, row),
+                           at_head(LSE, head, Lq, 4), at_head(dO, head, Lq, row),
+                           at_head(dQ, head, Lq, row), at_head(dK, head, Lk, row),
+                           at_head(dV, head, Lk, row), contract, workspace, partial_limit, stream);
+    }));
     return ok();
 }
 
@@ -214,23 +287,12 @@ mg_status_t mg_attn_fwd_cross(const void *Q, const void *K, const void *V, void 
     MG_TRY(check_key_len_alignment(key_len));
     MG_TRY(check_tensors({{Q, "Q"}, {K, "K"}, {V, "V"}, {O, "O"}, {LSE, "LSE"}}));
     MG_TRY(check_key_len(key_len));
-    const mg::AttnProblem p{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
-    MG_TRY(run_kernel(kernel_name("attn_fwd", contract, d), stream, [&] {
-        if (contract == MG_CONTRACT_FAST_BF16) {
-            const auto launch =
-                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_bf16 : mg::launch_fwd_bf16;
-            return launch(p, (const uint16_t *)Q, (const uint16_t *)K, (const uint16_t *)V,
-                          (uint16_t *)O, LSE, stream);
-        }
-        const float *q = (const float *)Q, *k = (const float *)K, *v = (const float *)V;
-        if (contract == MG_CONTRACT_ACCELERATED) {
-            const auto launch =
-                mg::use_few_rows(p, contract) ? mg::launch_fwd_few_accel : mg::launch_fwd_accel;
-            return launch(p, q, k, v, (float *)O, LSE, stream);
-        }
-        const mg::FwdForm form = mg::strict_fwd_form(p);
-        const auto launch = mg::few_rows(form) ? mg::launch_fwd_few_f32 : mg::launch_fwd_f32;
-        return launch(p, q, k, v, (float *)O, LSE, form, stream);
+    const mg::AttnProblem whole{B, H, Lq, Lk, d, causal ? 1 : 0, scale, key_len};
+    const size_t row = (size_t)d * (contract == MG_CONTRACT_FAST_BF16 ? 2 : 4);
+    MG_TRY(in_parts(whole, [&](const mg::AttnProblem &p, size_t head) {
+        return enqueue_fwd(p, at_head(Q, head, Lq, row), at_head(K, head, Lk, row),
+                           at_head(V, head, Lk, row), at_head(O, head, Lq, row),
+                           at_head(LSE, head, Lq, 4), contract, stream);
     }));
     return ok();
 }
