@@ -255,7 +255,7 @@ LDS_BLOCK_PATTERNS = [
     (10, "bf16 dQ K^T (32x32x16 transpose reads)"),
     (11, "bf16 forward V^T (32x32x16 transpose reads, 64-column blocks)"),
 ]
-# The strict f32 forward's chunk-permuted d = 64 tiles (pattern, what, the
+# Chunk-permuted f32 d = 64 tiles, as an f32 forward holds them (pattern, what, the
 # same read shape on unpermuted 256-byte rows: (pattern, row bytes)).
 LDS_F32_FWD_PATTERNS = [
     (17, "f32 forward K (16x16x4 operand groups)", (1, 256)),

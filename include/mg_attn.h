@@ -274,17 +274,17 @@ mg_status_t mg_mfma_peak(int kind, int iters, double *tflops, hipStream_t stream
  * j ^ swz(r)); `row_bytes` must be that block row (128 for 11 and 16, else
  * 64):
  *   7: 16-byte read, row l%16, columns 8*(l/16)..+7, swz = (r/2)%4
- *      (dK/dV Q and dO tiles)
+ *      (dQ and dK/dV tiles, and the strict kernels')
  *   8: transpose read of the same tile, row 4*(l/16) + (l%16)/4, columns
  *      4*(l%4)..+3
  *   9: 16-byte read, row l%32, columns 8*(l/32)..+7, swz = (r/4)%4
- *      (forward K, dQ K and V)
+ *      (forward K)
  *  10: transpose read of that tile, row 4*(l/32) + (l%16)/4, columns
- *      16*((l/16)%2) + 4*(l%4)..+3                (dQ K^T)
+ *      16*((l/16)%2) + 4*(l%4)..+3
  *  11: as 10 on 64-column blocks, swz = 4*((r/2)%2) (forward V^T)
  *  12..16: patterns 7..11 with no chunk permutation (swz = 0).
- * Patterns 17 and 18 read the strict f32 forward's d = 64 tiles: 256-byte
- * rows whose 16-byte chunk j of row r sits at j ^ (r % 16); `row_bytes` must
+ * Patterns 17 and 18 read f32 tiles as an f32 16x16x4 forward at d = 64 can
+ * hold them (none here does): 256-byte rows whose 16-byte chunk j of row r sits at j ^ (r % 16); `row_bytes` must
  * be 256:
  *  17: 16-byte read, row l%16, floats 16*(l/16)..+3  (K, 16x16x4 operands)
  *  18: 4-byte read, row 4*(l/16), float l%16        (V, products over rows)

@@ -25,8 +25,6 @@
 namespace mg {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
@@ -35,17 +33,6 @@ constexpr int kKeys = 64;            // keys per streamed tile
 
 __device__ __forceinline__ f32x16 mfma32x32x16f16(f16x8 a, f16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
-
-// Eight f32 -> eight f16 (nearest even).
-__device__ __forceinline__ f16x8 to_f16x8(f32x4 lo, f32x4 hi) {
-    f16x8 v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[e] = (_Float16)lo[e];
-        v[4 + e] = (_Float16)hi[e];
-    }
-    return v;
 }
 
 // Accumulator registers [8t, 8t+8) of a 32x32 block rounded to f16, as the B
@@ -516,8 +503,6 @@ void attn_fwd_accel_pipe(const float *__restrict__ Q, const float *__restrict__ 
         if (h == 0) LSE[(size_t)head * Lq + qi] = (l > 0.f) ? (m2f + log2f(l)) * kLn2 : -INFINITY;
     }
 }
-
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 

@@ -877,8 +877,6 @@ void attn_dq_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K
     }
 }
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 // The backward's two-group forms (eight waves, each group half of every streamed
 // tile) where one round of workgroups leaves the time to the chain of tiles:
 // at most one workgroup per CU and 768 or more streamed rows.  One against two

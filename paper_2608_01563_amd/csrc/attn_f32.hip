@@ -70,8 +70,6 @@ struct Cfg {
     static constexpr int NT = 64 * NW_;        // threads per workgroup
     static constexpr int ROWS = 16 * NW_;      // stationary rows per workgroup
     static constexpr int OCC = OCC_ > 0 ? OCC_ : 1;
-    // the occupancy request only holds without spills for d <= 64
-    template <int D> static constexpr int occ() { return D <= 64 ? OCC : 1; }
     static constexpr int NBUF = DB_ ? 2 : 1;   // LDS buffers for the streamed tile
 };
 using DkdvCfg = Cfg<MG_DKDV_CFG>;
@@ -97,16 +95,15 @@ __global__ __launch_bounds__(256) void attn_rowdot_f32(const float *__restrict__
 }
 
 // ---------------------------------------- backward: dK, dV and dQ partials
-// The key-stationary kernel above, extended with the dQ product: after dS of
-// a query tile is known, it goes through LDS and the workgroup multiplies it
+// A workgroup keeps a key tile's K and V and walks the query tiles.  After dS
+// of a query tile is known, it goes through LDS and the workgroup multiplies it
 // by its own key tile, dQ_part[i][:] = sum_{j in tile} dS[i][j] K[j][:].
 // Each (key tile, query row) partial is written once to the workspace and
 // attn_dq_reduce_f32 adds the partials of a row in key-tile order: no atomics,
 // bitwise-reproducible, and no second recompute of S and dP.
 //
 // The Q and dO tiles, and the LSE and D values of their rows, reach LDS by
-// row-wise direct-to-LDS loads (no staging registers, padded rows as in the
-// kernel above); dQ partials leave through raw buffer stores whose
+// row-wise direct-to-LDS loads (no staging registers, padded rows); dQ partials leave through raw buffer stores whose
 // descriptor ends at row Lq.  With two LDS buffers (C::NBUF == 2) the next tile is fetched
 // during the whole current iteration; with one, during the dQ product.  A
 // tile's dQ partials are stored at the start of the next iteration, so the
@@ -120,7 +117,7 @@ __global__ __launch_bounds__(256) void attn_rowdot_f32(const float *__restrict__
 // tile's query range get zeros, and no reduction follows (LOCALD grids only,
 // so that the large-grid instances carry none of this).
 template <int D, int NIB, class C, bool LOCALD>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::template occ<D>(), 8)))
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC, 8)))
 void attn_dkdvq_f32(const float *__restrict__ Q, const float *__restrict__ K,
                     const float *__restrict__ V, const float *__restrict__ O,
                     const float *__restrict__ dO, const float *__restrict__ LSE,
@@ -510,8 +507,6 @@ __global__ __launch_bounds__(256) void attn_bwd_reduce_f32(
                         Lq, Lk, causal, scale, BH, key_rows);
 }
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
@@ -522,7 +517,6 @@ hipError_t launch_bwd_rowdot_f32(const AttnProblem &p, const float *O, const flo
     switch (p.d) {
     case 32: attn_rowdot_f32<32><<<dim3(cdiv(rows, 256 / 8)), block, 0, s>>>(O, dO, Dws, rows); break;
     case 64: attn_rowdot_f32<64><<<dim3(cdiv(rows, 256 / 16)), block, 0, s>>>(O, dO, Dws, rows); break;
-    case 128: attn_rowdot_f32<128><<<dim3(cdiv(rows, 256 / 32)), block, 0, s>>>(O, dO, Dws, rows); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

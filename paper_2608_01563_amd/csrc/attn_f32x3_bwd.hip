@@ -534,8 +534,6 @@ void attn_dkdv_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                            causal, diag, scale, scale_log2, lane);
 }
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 }  // namespace
 
 // Forms.  kWide: four waves of 32 query rows or 16 keys.  kPair: eight waves in

@@ -373,8 +373,6 @@ void attn_fwd_f32x3(const float *__restrict__ Q, const float *__restrict__ K,
                           scale_log2, lane);
 }
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 }  // namespace
 
 // Instances per form.  With one key group a tile is split once for all the

@@ -102,16 +102,6 @@ __device__ __forceinline__ void merge_and_store(const float *xo, const float (*m
     }
 }
 
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f16x4 to_f16x4(f32x4 v) {
-    return f16x4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
-}
-__device__ __forceinline__ f16x8 to_f16x8(f32x4 a, f32x4 b) {
-    const f16x4 x = to_f16x4(a), y = to_f16x4(b);
-    return f16x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-}
 
 // ---------------------------------------------------------------------- f32 --
 template <int D, int DV, int NW, int KT, bool ROUND>
@@ -441,8 +431,6 @@ void attn_fwd_few_bf16(const uint16_t *__restrict__ Q, const uint16_t *__restric
                             col0 == 0 ? LSE + (size_t)head * Lq + q0 : nullptr,
                             [&](int q, int c, f32x4 v) { store_bf16x4(Oh + (size_t)q * D + c, v); });
 }
-
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // Eight waves per workgroup where one workgroup per CU must keep a long key
 // side's loads in flight, else four (two or more workgroups per CU; B2 H4

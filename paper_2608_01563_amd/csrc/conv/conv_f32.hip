@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "../cdiv.h"
 #include "../device_common.h"
 #include "../rows_f32.h"
 #include "../tiles_split.h"
@@ -113,16 +114,6 @@ __device__ __forceinline__ void store_split4(uint16_t *t, const int (&o)[4], f32
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             t[k * RedTile::kSize + o[e]] = (uint16_t)(p[k][e >> 1] >> (16 * (e & 1)));
-}
-
-// acc[i] += A[16i + .][:] B[:][.] over one 32-deep step, six
-// products of bf16 parts each (kUp^2 times the sum).
-__device__ __forceinline__ void mma_step(f32x4 (&acc)[2], const Split8 (&a)[2], const Split8 &b) {
-    constexpr int I[6] = {2, 1, 1, 0, 0, 0}, J[6] = {0, 1, 0, 2, 1, 0};
-#pragma unroll
-    for (int t = 0; t < 6; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i] = mfma16x16x32bf16(a[i].p[I[t]], b.p[J[t]], acc[i]);
 }
 
 // Work of one filter-gradient launch: grid (k tile, j tile, split), split fastest.
@@ -322,7 +313,7 @@ __device__ __forceinline__ void wgrad_tile(int bid, ConvLds &L, const WgradJob &
         if (st + NP < st1) load(st + NP, fr);
         const Split8 a[2] = {load_split_tr<RedTile>(L.A[cur], ta[0], ta[0] + 32 * 16),
                              load_split_tr<RedTile>(L.A[cur], ta[1], ta[1] + 32 * 16)};
-        mma_step(acc, a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16));
+        mfma_split(a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16), acc);
         if (st + 1 < st1) store(cur ^ 1, nx);
         __syncthreads();
     };
@@ -603,7 +594,7 @@ __device__ __forceinline__ void dgrad_tile(int bid, ConvLds &L, const DgradJob &
         if (st + NP < st1) load(st + NP, fr);
         const Split8 a[2] = {load_split<PixTile>(L.A[cur], ta[0]),
                              load_split<PixTile>(L.A[cur], ta[1])};
-        mma_step(acc, a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16));
+        mfma_split(a, load_split_tr<RedTile>(L.B[cur], tb, tb + 32 * 16), acc);
         if (st + 1 < st1) store(cur ^ 1, nx);
         __syncthreads();
     };
@@ -687,8 +678,6 @@ void conv_bwd_f32(DgradJobs d, int dblocks, WgradJob w, ConvProblem p, ConvDivs 
         wgrad_tile<VA, VB>(bid - dblocks, lds, w, p, dv);
     }
 }
-
-int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 ConvDivs make_divs(const ConvProblem &p) {
     return ConvDivs{make_fastdiv(p.P * p.Q), make_fastdiv(p.Q), make_fastdiv(p.K),

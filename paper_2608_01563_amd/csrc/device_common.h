@@ -27,8 +27,19 @@ namespace mg {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// f32 -> f16 (nearest even).
+__device__ __forceinline__ f16x4 to_f16x4(f32x4 v) {
+    return f16x4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+}
+__device__ __forceinline__ f16x8 to_f16x8(f32x4 a, f32x4 b) {
+    const f16x4 x = to_f16x4(a), y = to_f16x4(b);
+    return f16x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+}
 
 constexpr float kLog2e = 1.4426950408889634f;
 // Online-softmax slack (base 2): a forward may keep a running maximum up to

@@ -7,7 +7,6 @@
 namespace mg {
 namespace {
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 constexpr int kCUs = 256;
 
 // Cost of a form, in us: `chain` per key tile of a workgroup alone on its CU;

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
 
+#include "cdiv.h"
 #include "mg_attn.h"
 
 namespace mg {

@@ -33,13 +33,14 @@ constexpr int kReadsPerStep = 8;
 
 // The bf16 kernels' tile layouts ([64 rows][128 columns] in column blocks),
 // and the same blocks without the chunk swizzle.
-using KvTile = Bf16Tile<64, 128, 4, 32, 1, 3, 1>;      // dK/dV: Q, dO
-using RowTile = Bf16Tile<64, 128, 4, 32, 2, 3, 1>;     // forward K, dQ K and V
+using KvTile = Bf16Tile<64, 128, 4, 32, 1, 3, 1>;      // dQ, dK/dV and the strict kernels
+using RowTile = Bf16Tile<64, 128, 4, 32, 2, 3, 1>;     // forward K
 using TrTile = Bf16Tile<64, 128, 4, 64, 1, 1, 4>;      // forward V
 using Plain32 = Bf16Tile<64, 128, 4, 32, 0, 0, 0>;
 using Plain64 = Bf16Tile<64, 128, 4, 64, 0, 0, 0>;
-// A tile of unpadded f32 rows at d = 64 (256 bytes, the 16-byte chunks of row r
-// permuted by j -> j ^ (r % 16)): byte offset of element (row, col).
+// An f32 tile without padding, for f32 16x16x4 products at d = 64: rows of 256
+// bytes, the 16-byte chunks of row r permuted by j -> j ^ (r % 16).  No kernel
+// here holds its operands so; it is what padded rows compare with.  Byte offset of element (row, col).
 __host__ __device__ inline int f32_tile_at(int row, int col) {
     return 256 * row + 16 * ((col >> 2) ^ (row & 15)) + 4 * (col & 3);
 }

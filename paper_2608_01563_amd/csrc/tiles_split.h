@@ -1,5 +1,8 @@
 // tiles_split.h -- f32 products on the bf16 matrix cores: operands split into
-// three bf16 parts, tiles of such parts in LDS.
+// three bf16 parts, tiles of such parts in LDS.  The method is Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations" (IEEE ARITH 2019): f32 as three bf16 terms,
+// six products.
 //
 // An f32 value x is written as x = h + m + l with h = bf16(x),
 // m = bf16(x - h), l = bf16(x - h - m), all rounded to nearest even; both
@@ -95,15 +98,26 @@ __device__ __forceinline__ Split8 split8(f32x4 a, f32x4 b) {
 // Parts of an operand as it lies in memory, kUp times it.
 __device__ __forceinline__ Split8 split8_up(f32x4 a, f32x4 b) { return split8(a * kUp, b * kUp); }
 
-// acc[n] += a * b[n] in six terms, smallest first; consecutive instructions
-// share an operand.
+// The six terms (part of a, part of b), smallest first.
+constexpr int kTermA[6] = {2, 1, 1, 0, 0, 0}, kTermB[6] = {0, 1, 0, 2, 1, 0};
+
+// acc[n] += a * b[n], consecutive instructions sharing an operand ...
 template <int N>
 __device__ __forceinline__ void mfma_split(const Split8 &a, const Split8 (&b)[N], f32x4 (&acc)[N]) {
-    constexpr int I[6] = {2, 1, 1, 0, 0, 0}, J[6] = {0, 1, 0, 2, 1, 0};
 #pragma unroll
     for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int n = 0; n < N; ++n) acc[n] = mfma16x16x32bf16(a.p[I[t]], b[n].p[J[t]], acc[n]);
+        for (int n = 0; n < N; ++n)
+            acc[n] = mfma16x16x32bf16(a.p[kTermA[t]], b[n].p[kTermB[t]], acc[n]);
+}
+// ... or acc[n] += a[n] * b.
+template <int N>
+__device__ __forceinline__ void mfma_split(const Split8 (&a)[N], const Split8 &b, f32x4 (&acc)[N]) {
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+            acc[n] = mfma16x16x32bf16(a[n].p[kTermA[t]], b.p[kTermB[t]], acc[n]);
 }
 
 // An f32 [ROWS][D] tile that passes through registers, is split and lands in

@@ -81,8 +81,8 @@ def test_rows_that_see_no_key(gpu_lib, contract):
 @pytest.mark.parametrize("d", [32, 64])
 @pytest.mark.parametrize("Lq,Lk", [(300, 1000), (1000, 520)])
 def test_cross_wide_key_tiles(gpu_lib, Lq, Lk, d):
-    """Causal problems with ceil(Lk/128)*B*H >= 512 take the 128-key fused
-    backward; both signs of Lk - Lq and ragged tails on both sides."""
+    """Causal cross problems of 512 and more 128-key tiles: both signs of
+    Lk - Lq, ragged tails on both sides and key lengths from 1 up."""
     B, H = 8, (8 if Lk >= 1000 else 16)   # 512 and 640 tiles of 128 keys
     kl = [Lk, Lk // 3, 128, 1, Lk, Lk - 1, 64, 2][:B]
     say("cross wide key tiles B%d H%d Lq%d Lk%d d%d" % (B, H, Lq, Lk, d))

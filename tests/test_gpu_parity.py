@@ -341,9 +341,8 @@ def test_strict_separate_dq_fallback_sampled_heads(gpu_lib):
 @pytest.mark.parametrize("d", [32, 64])
 @pytest.mark.parametrize("padded", [False, True])
 def test_wide_key_tiles_ragged(gpu_lib, d, padded):
-    """Causal problems with ceil(L/128)*B*H >= 512 take the 128-key fused
-    backward (8 waves); a ragged L exercises its tail tiles, key padding its
-    masked waves."""
+    """Causal problems of 512 and more 128-key tiles: a ragged L exercises the
+    tail tiles, key padding the masked waves."""
     B, H, L = 4, 16, 1000
     kl = [1000, 517, 128, 1] if padded else None
     say("wide key tiles B%d H%d L%d d%d padded=%s" % (B, H, L, d, padded))

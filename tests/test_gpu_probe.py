@@ -72,8 +72,8 @@ def test_lds_probe_block_layouts_at_the_minimum(gpu_lib):
 
 
 def test_lds_probe_f32_forward_tiles_at_the_best_padding(gpu_lib):
-    """The strict f32 forward's chunk-permuted K and V tiles (d = 64): each
-    read costs no more than the cheapest padded stride achieves for the same
+    """Chunk-permuted f32 tiles (d = 64, what an f32 16x16x4 forward holds its K
+    and V in): each read costs no more than the cheapest padded stride achieves for the same
     read shape, and the 16x16x4 operand groups cost several times more on
     unpermuted 256-byte rows."""
     import paper_2608_01563_amd as mg

@@ -1,8 +1,7 @@
-"""GPU parity of the strict-f32 kernels that run on split bf16 operands, on
-grids large enough to reach every form (d <= 64 backward: 512 or more 128-row
-query tiles and 64-key tiles), and their results for operands that the split
-cannot carry: infinities, NaN, and finite values that round to an infinite
-bf16."""
+"""GPU parity of the strict-f32 kernels that run on split bf16 operands, and
+their results for operands that the split cannot carry (infinities, NaN, and
+finite values that round to an infinite bf16) or that it must scale (values
+near the smallest normal number)."""
 import numpy as np
 import pytest
 
@@ -17,11 +16,12 @@ pytestmark = pytest.mark.gpu
 # twice that for the chain of two products.
 REL = 2e-6
 
-# (B, H, Lq, Lk, mode): rows and keys off the 16-, 32-, 64- and 128-row tiles
+# (B, H, Lq, Lk, mode): many heads, rows and keys off the 16-, 32-, 64- and
+# 128-row tiles
 LARGE = [
     (2, 260, 33, 33, "causal"), (2, 256, 130, 65, "causal"), (2, 256, 65, 193, "causal"),
     (4, 128, 97, 70, "padded"), (2, 260, 64, 64, "full"),
-    # two wave groups: 224 or more 64-row tiles of either side
+    # fewer, which two wave groups may take
     (1, 230, 50, 64, "causal"), (2, 115, 65, 33, "full"), (4, 60, 193, 100, "padded"),
     (1, 113, 130, 257, "causal"),
 ]
@@ -42,8 +42,7 @@ def test_large_grids(gpu_lib, B, H, Lq, Lk, mode, d):
         assert rel <= REL, (n, rel)
 
 
-# (B, H, Lq, Lk, mode): the forward's forms of 32 query rows, four key groups
-# (long chains) and two (short key sides), above the few-rows kernel's limit
+# (B, H, Lq, Lk, mode): heads of middle length on short and on long key sides
 SMALL = [
     (2, 6, 1100, 1100, "causal"), (1, 8, 600, 301, "full"), (1, 8, 523, 33, "full"),
     (8, 8, 250, 250, "causal"), (8, 12, 150, 150, "padded"), (16, 9, 66, 61, "full"),

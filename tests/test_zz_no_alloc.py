@@ -4,12 +4,12 @@ ABI: two calls in a row per case, the second on a smaller problem, so the
 second call reuses the array the first one left behind.
 
 Where the caller-workspace layout fits in the array, the same kernels run
-on the same data and the outputs must be bitwise equal.  Where it does not
-(the strict B8 H8 L1024 workload needs 128 MiB of dQ partials), the call
-keeps only D in the array and runs the separate dK/dV and dQ passes, whose
-sums run in another order: every output must then agree with the
-caller-workspace call within the contract's tolerance (normwise 1e-4 for
-strict f32).
+on the same data and the outputs must be bitwise equal.  Where it does not,
+the call keeps only D in the array and runs the separate dK/dV and dQ passes.
+The strict B8 H8 L1024 workload runs those with a workspace too; for a problem
+that would otherwise write dQ partials (in test_gpu_backward_forms.py) the sums
+run in another order.  Every output must agree with the caller-workspace call
+within the contract's tolerance (normwise 1e-4 for strict f32).
 """
 import ctypes
 
