@@ -118,7 +118,8 @@ def kernel_source_digest(conv=False):
     base = os.path.join(ROOT, KERNEL_SOURCE_DIR)
     if conv:
         names = ["conv/" + n for n in sorted(os.listdir(os.path.join(base, "conv")))]
-        names += ["device_common.h", "host_runtime.h", "host_runtime.cpp"]
+        names += ["cdiv.h", "device_common.h", "host_runtime.h", "host_runtime.cpp",
+                  "rows_f32.h", "tiles_bf16.h", "tiles_split.h"]
     else:
         # the MFMA and LDS probes are measuring tools, not attention code
         names = sorted(n for n in os.listdir(base) if n not in ("mfma_probe.hip", "lds_probe.hip"))
