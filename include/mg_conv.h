@@ -24,9 +24,9 @@
  * backward matrices stay f32, Sec. 4.2) both form f32 products (each f32
  * operand, scaled by a power of two, as the sum of three bf16 parts, six bf16
  * matrix products per f32 product; outputs these cannot carry are recomputed in
- * f32, up to four times as long) with f32 accumulation and give identical results; MG_CONTRACT_FAST_BF16 returns
- * MG_ERR_UNSUPPORTED.  Status codes, the error detail and the per-launch
- * timing hooks are those of mg_attn.h.
+ * f32, up to four times as long) with f32 accumulation and give identical
+ * results; MG_CONTRACT_FAST_BF16 returns MG_ERR_UNSUPPORTED.  Status codes, the
+ * error detail and the per-launch timing hooks are those of mg_attn.h.
  *
  * Ownership, asynchrony and errors: as for mg_attn.h.  The caller owns every
  * buffer; all work is enqueued on `stream` (0 = null stream) and the calls
