@@ -103,11 +103,12 @@ __global__ __launch_bounds__(256) void attn_rowdot_f32(const float *__restrict__
 // bitwise-reproducible, and no second recompute of S and dP.
 //
 // The Q and dO tiles, and the LSE and D values of their rows, reach LDS by
-// row-wise direct-to-LDS loads (no staging registers, padded rows); dQ partials leave through raw buffer stores whose
-// descriptor ends at row Lq.  With two LDS buffers (C::NBUF == 2) the next tile is fetched
-// during the whole current iteration; with one, during the dQ product.  A
-// tile's dQ partials are stored at the start of the next iteration, so the
-// wait for the next tile never waits on a just-issued store.
+// row-wise direct-to-LDS loads (no staging registers, padded rows); dQ partials
+// leave through raw buffer stores whose descriptor ends at row Lq.  With two LDS
+// buffers (C::NBUF == 2) the next tile is fetched during the whole current
+// iteration; with one, during the dQ product.  A tile's dQ partials are stored
+// at the start of the next iteration, so the wait for the next tile never waits
+// on a just-issued store.
 //
 // Small grids (LOCALD): the O rows of each query tile arrive with its Q and
 // dO rows, and the workgroup computes D_i = sum_k dO_ik O_ik in LDS before

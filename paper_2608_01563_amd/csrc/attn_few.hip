@@ -471,10 +471,11 @@ hipError_t by_shape(const AttnProblem &p, F &&f) {
 //   bf16, up to 256 blocks: B4 H4 L256 4.0 : 7.2, Lq17 to 128 by Lk256 to 4096 0.3
 //     to 0.8; up to 512 (1024: B8 H8 L256 8.2 : 6.5) where the blocks of a head
 //     share its K and V in an L2: d = 32 (0.5 to 0.8), d = 64 to 512 keys (0.8 to
-//     1.0), d = 128 to 128 keys (0.8 to 1.1), else with eight blocks a head, or four of growing length, that land on
-//     at most two XCDs (heads a multiple of four) or on few bytes in all: B2 H4
-//     L1024 causal 9.8 : 16.1, B8 H8 L128 4.1 : 4.9; but d = 128 B1 H256 Lq32 Lk2048
-//     1.48, B1 H73 Lq100 Lk1000 1.42, B1 H43 Lq128 Lk4000 1.29
+//     1.0), d = 128 to 128 keys (0.8 to 1.1), else with eight blocks a head, or
+//     four of growing length, that land on at most two XCDs (heads a multiple of
+//     four) or on few bytes in all: B2 H4 L1024 causal 9.8 : 16.1, B8 H8 L128 4.1 :
+//     4.9; but d = 128 B1 H256 Lq32 Lk2048 1.48, B1 H73 Lq100 Lk1000 1.42, B1 H43
+//     Lq128 Lk4000 1.29
 bool use_few_rows(const AttnProblem &p, mg_contract_t contract) {
     const long blocks = few_row_blocks(p);
     if (p.Lq <= kFewRows || blocks <= 256) return true;

@@ -78,11 +78,13 @@ float estimate(const AttnProblem &p, const FormCost &c) {
     return std::sqrt(std::sqrt(chain * chain * chain * chain + rate * rate * rate * rate));
 }
 
+// The cheapest form, of at least `rows` rows.
 template <int N>
-FwdForm cheapest(const AttnProblem &p, const FormCost (&costs)[N]) {
+FwdForm cheapest(const AttnProblem &p, const FormCost (&costs)[N], int rows = 16) {
     FwdForm best = costs[0].form;
     float least = INFINITY;
     for (const FormCost &c : costs) {
+        if (c.rows < rows) continue;
         // beyond a few steps a lone wave's chain is longer than the model has it
         if (c.form == FwdForm::kFewWave && p.Lk > 96) continue;
         const float t = estimate(p, c);
@@ -94,8 +96,12 @@ FwdForm cheapest(const AttnProblem &p, const FormCost (&costs)[N]) {
     return best;
 }
 
-// Rows and keys beyond 256 (keys beyond 1024: rows beyond 64): tiles are full, and what decides is whether the grid
-// gives every CU its share (GPU time in us at d = 64 unless named).
+// Share of its tiles that a side of L fills.
+float filled(int L, int tile) { return (float)L / (tile * cdiv(L, tile)); }
+
+// Rows and keys beyond 256 (keys beyond 1024: rows beyond 64): tiles are full, and
+// what decides is whether the grid gives every CU its share (GPU time in us at
+// d = 64 unless named).
 //   few: a causal grid of up to 512 16-row blocks, else 256: B4 H4 L256 6.8
 //     (64-row forward 9.2), B1 H4 L2048 d128 93 (150).
 //   128 rows while they give two workgroups per CU: B8 H8 L1024 causal 54.7,
@@ -152,20 +158,37 @@ int form_rows(FwdForm f) {
 // One step of keys needs no second wave (until the lone waves are so many that
 // starting them takes longer than 64-row workgroups: d = 64 B1 H463 Lq1154 Lk14
 // 82 us, 64 rows 64); a decode step reads a long cache with the most loads in
-// flight; and a grid of many rounds of full 128-row tiles splits each key tile
-// for the most rows (d = 64 B1 H1377 L229 148 -> 138 us).
+// flight.  The model's 10 % does not tell forms apart that are alike but for
+// tiles that a problem without masks and lengths fills (GPU us):
+//   128 rows and 64 keys at a time where both sides fill them, from one tile per
+//     CU (d = 32 B8 H32 L128 9.3 -> 8.0, L256 21.2 -> 18.2, d = 64 32.5 -> 29.7), or
+//     most of them over many rounds (d = 64 B1 H1377 L229 148 -> 138); not
+//     with lengths (d = 64 B64 H16 L128 1.13 times the 64 rows' time)
+//   32 full rows in one round of one workgroup per CU instead of two of 16 rows
+//     (B8 H8 L128 8.1 -> 7.7, B4 H8 L256 10.8 -> 10.2; causal in two rounds, d = 32
+//     B8 H8 L256 8.6 -> 8.0)
+// and it has no cost of K and V read again: 32 and more rows (d <= 64) where two
+// rounds and more of 16-row workgroups each read 1024 keys (B1 H384 Lq17 Lk2048
+// 0.73 of their time, with lengths 0.80, B1 H256 Lq48 Lk1024 0.96).
 FwdForm strict_fwd_form(const AttnProblem &p) {
     if (p.Lk <= 16)
         return p.d <= 64 && p.Lq >= 64 && few_row_blocks(p) >= 4096 ? FwdForm::kRows64
                                                                     : FwdForm::kFewWave;
     if (p.Lq <= kFewRows && p.Lk >= 512) return FwdForm::kFewLong;
     if (p.Lk > 1024 ? p.Lq > 64 : p.Lq > 256 && p.Lk > 256) return long_form(p);
-    const int tiles128 = cdiv(p.Lq, 128);
-    if (p.d <= 64 && !p.causal && p.Lk > 96 && (long)tiles128 * p.B * p.H >= 1024 &&
-        20 * p.Lq >= 17 * 128 * tiles128)
+    const bool plain = p.d <= 64 && !p.causal && p.key_len == nullptr;
+    const long BH = (long)p.B * p.H, tiles128 = cdiv(p.Lq, 128) * BH, tiles32 = cdiv(p.Lq, 32) * BH;
+    const float full = std::min(filled(p.Lq, 128), filled(p.Lk, 64));
+    if (plain && p.Lk > 96 &&
+        ((tiles128 >= kCUs && full >= 0.9375f) || (tiles128 >= 4 * kCUs && full >= 0.85f)))
         return FwdForm::kRows128;
-    const FwdForm form = p.d == 32   ? cheapest(p, kCost32)
-                         : p.d == 64 ? cheapest(p, kCost64) : cheapest(p, kCost128);
+    const bool full32 = p.Lk >= 128 && filled(p.Lk, 64) >= 0.9375f && filled(p.Lq, 32) >= 0.9375f;
+    const bool round32 = plain ? tiles32 <= kCUs && tiles32 > kCUs * 7 / 8
+                               : p.causal && tiles32 > 2 * kCUs * 7 / 8;
+    const bool again = p.Lk >= 1024 && few_row_blocks(p) > 2 * kCUs;
+    const int rows = (full32 && round32) || again ? 32 : 16;
+    const FwdForm form = p.d == 32   ? cheapest(p, kCost32, rows)
+                         : p.d == 64 ? cheapest(p, kCost64, rows) : cheapest(p, kCost128);
     return form == FwdForm::kFew && p.Lk > 1024 ? FwdForm::kFewLong : form;
 }
 

@@ -35,6 +35,13 @@ def test_every_instance_exists():
     ((8, 8, 1024, 1024, 64, "causal"), "rows128"), ((2, 6, 1500, 1500, 64, "full"), "rows64_pair"),
     ((2, 8, 1024, 1024, 128, "causal"), "rows64_pair"), ((4, 4, 256, 256, 64, "causal"), "few"),
     ((8, 16, 1, 4096, 128, "padded"), "few_long"), ((1, 1, 64, 64, 32, "causal"), "few"),
+    # both sides fill their tiles; and where they do not, or lengths cut them
+    ((8, 32, 128, 128, 32, "full"), "rows128"), ((8, 32, 256, 256, 64, "full"), "rows128"),
+    ((8, 32, 110, 128, 32, "full"), "rows64"), ((64, 16, 128, 128, 64, "padded"), "rows64"),
+    ((8, 8, 128, 128, 64, "full"), "rows32"), ((8, 8, 112, 112, 64, "full"), "few"),
+    ((8, 8, 256, 256, 32, "causal"), "rows32"), ((8, 8, 200, 200, 32, "causal"), "few"),
+    # K and V read again by every 16 rows
+    ((1, 384, 17, 2048, 64, "full"), "rows32"), ((64, 16, 7, 2048, 64, "padded"), "few_long"),
 ])
 def test_forms_of_named_shapes(shape, form):
     assert fwd_form(*shape) == form

@@ -29,6 +29,10 @@ CASES = [
     ("rows128", 8, 64, 270, 270, "causal", (32, 64)), ("rows128", 1, 130, 257, 257, "full", (128,)),
     ("rows128", 1, 1100, 110, 110, "full", (32, 64)),
     ("rows256", 1, 600, 257, 257, "causal", (128,)),
+    # tiles that both sides fill
+    ("rows128", 1, 257, 125, 127, "full", (32, 64)), ("rows128", 2, 64, 250, 190, "full", (32, 64)),
+    ("rows32", 1, 520, 17, 1100, "full", (64,)), ("rows32", 8, 8, 254, 256, "causal", (32,)),
+    ("rows32", 2, 32, 127, 128, "full", (64,)), ("rows32_quad", 1, 32, 255, 254, "full", (32, 64)),
 ]
 
 
